@@ -21,10 +21,11 @@
  * round16 is one round-to-nearest-even to the 16-bit type `dtype`.
  *
  * Supported domain: bits in {2,3,4}; group_size in {32,64,128,256}; 1 <= M <= 128
- * (a launch works on up to 32 activation rows, at 4 bits on up
- * to 64; more are served in slices of that many rows, one launch each on the caller's stream, so the
- * weights are streamed once per slice; a 33..64-row launch is preceded by a small launch that copies
- * the slice's activations into the workspace in the order the matrix instruction reads them);
+ * (one launch on the caller's stream, the weights streamed once.  Beyond 32 rows that is a kernel of its
+ * own with no plan to choose; a call with a plan, with a registered plan that fits slices of 32 rows, or
+ * with one table per output row is served in slices instead, one launch each: 32 rows, or, at 4 bits where the plan
+ * asks for LUTQ_SCHED_ROWS, 64 rows, each such launch preceded by a small one that copies the slice's
+ * activations into the workspace in the order the matrix instruction reads them);
  * N a multiple of 16; K a multiple of the K-tile of the bit width (128 for
  * 4-bit, 256 for 2- and 3-bit) and of group_size; device pointers 16-byte aligned.
  *
@@ -193,7 +194,8 @@ typedef struct {
 #define LUTQ_SCHED_QUEUE 2
 #define LUTQ_SCHED_ROWS 3
 
-/* Fills *plan with the library's choice for this problem on the current device. */
+/* Fills *plan with the library's choice for this problem on the current device.  For M > 32 that is the
+ * decomposition of the slices, the one a plan can ask for (a call without a plan takes all rows in one launch). */
 lutq_status lutq_plan_default(int bits, int group_size, int64_t M, int64_t N, int64_t K,
                               lutq_dtype dtype, lutq_plan* plan);
 

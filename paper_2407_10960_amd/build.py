@@ -1,7 +1,7 @@
 """Builds liblutq.so (HIP kernels for gfx950 + the C ABI) in-tree with hipcc.
 
-The kernels are compiled once per (bit width, dtype) pair from the same source so that the six
-translation units build in parallel.  Run as `python -m paper_2407_10960_amd.build`.
+The matmul kernels are compiled once per (bit width, dtype) pair from the same two sources so that the
+twelve translation units build in parallel.  Run as `python -m paper_2407_10960_amd.build`.
 """
 from __future__ import annotations
 
@@ -48,10 +48,11 @@ def build(verbose: bool = False, jobs: int | None = None) -> str:
     objs = []
     for bits in (2, 3, 4):
         for dt in ("F16", "BF16"):
-            obj = os.path.join(BUILD_DIR, f"kernels_b{bits}_{dt.lower()}.o")
-            objs.append(obj)
-            steps.append([hipcc, *HIP_FLAGS, f"-DLUTQ_INST_BITS={bits}", f"-DLUTQ_INST_DT={dt}",
-                          "-c", os.path.join(CSRC, "lutq_kernels.hip"), "-o", obj])
+            for unit in ("kernels", "panel"):
+                obj = os.path.join(BUILD_DIR, f"{unit}_b{bits}_{dt.lower()}.o")
+                objs.append(obj)
+                steps.append([hipcc, *HIP_FLAGS, f"-DLUTQ_INST_BITS={bits}", f"-DLUTQ_INST_DT={dt}",
+                              "-c", os.path.join(CSRC, f"lutq_{unit}.hip"), "-o", obj])
     for src in ("lutq_api.hip", "lutq_calib.hip", "lutq_quantize.hip", "lutq_trace.hip"):
         if not os.path.exists(os.path.join(CSRC, src)):
             continue

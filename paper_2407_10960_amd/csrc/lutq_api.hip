@@ -725,6 +725,11 @@ rows_launcher pick_rows(int bits, lutq_dtype dt) {
     if (dt == LUTQ_F16) return bits == 2 ? launch_rows_b2_F16 : bits == 3 ? launch_rows_b3_F16 : launch_rows_b4_F16;
     return bits == 2 ? launch_rows_b2_BF16 : bits == 3 ? launch_rows_b3_BF16 : launch_rows_b4_BF16;
 }
+typedef hipError_t (*panel_launcher)(int, int, int, const PanelParams&, hipStream_t);
+panel_launcher pick_panel(int bits, lutq_dtype dt) {
+    if (dt == LUTQ_F16) return bits == 2 ? launch_panel_b2_F16 : bits == 3 ? launch_panel_b3_F16 : launch_panel_b4_F16;
+    return bits == 2 ? launch_panel_b2_BF16 : bits == 3 ? launch_panel_b3_BF16 : launch_panel_b4_BF16;
+}
 dequant_launcher pick_dequant(int bits, lutq_dtype dt) {
     if (dt == LUTQ_F16) return bits == 2 ? launch_dequant_b2_F16 : bits == 3 ? launch_dequant_b3_F16 : launch_dequant_b4_F16;
     return bits == 2 ? launch_dequant_b2_BF16 : bits == 3 ? launch_dequant_b3_BF16 : launch_dequant_b4_BF16;
@@ -1352,6 +1357,101 @@ int slice_rows(int bits, int group_size, int64_t M, int64_t N, int64_t K, bool b
     return have && take ? 64 : 32;
 }
 
+// Panel launch (panel_kernel): 33..128 activation rows in one pass over the weights.
+struct PanelDecomp {
+    int mb, rp, ks;           // blocks of 32 activation rows, panel height / 32, K slices
+    int64_t shares;           // workgroups side by side: 64 rp output channels each
+};
+
+// Every call of 33 rows or more without a plan: one pass over the weights measured faster than slices of 32 or 64 rows on
+// every shape tried (us, HBM-cold weights, MI355X, slices -> panel): 8B gate+up W4 fp16 M = 33 / 64 / 96 / 128 28.9 / 33.0 /
+// 54.3 / 65.0 -> 24.9 / 27.3 / 34.6 / 41.8, O 13.1 / 14.6 / 25.2 / 28.8 -> 11.8 / 12.3 / 15.9 / 19.1, down 29.0 / 33.9 / 51.0 /
+// 66.3 -> 19.8 / 21.0 / 27.9 / 31.9, 1024 x 4096 13.7 / 18.6 / 27.8 / 36.7 -> 9.7 / 9.8 / 12.2 / 14.2, 70B gate+up 90 / 104 / 163 /
+// 205 -> 89 / 97 / 124 / 153; W3 bf16 8B down 27.9 / 37.3 / 55.3 / 73.2 -> 20.4 / 21.1 / 27.3 / 32.7, 70B O 27.9 / 36.6 / 54.9 / 73.3 ->
+// 21.6 / 22.8 / 29.6 / 34.0.  (70B QKV W4 at M = 33 24.1 -> 24.6.)
+// The panel height (32 or 64 channels per wavefront) and the number of K slices are those of the least estimated time: a launch
+// costs a fixed part, a part per K tile that a wavefront works on (t0 + t1 per 32 activation rows; the taller panel takes less per
+// weight), more where the chip is full, and with K slices the exchange of partial sums.  The constants are fitted to 380
+// measurements (twelve shapes from 1024 x 4096 to 57344 x 8192, M = 33, 64, 96, 128; 4 bits, and 3 bits in bf16, whose wider tiles
+// count twice); the choice is within 1.3 % of the fastest plan on average, 10 % at worst.
+// `room`: bytes of scratch for the slices' partial sums.
+bool panel_decomp(int bits, int64_t M, int64_t N, int64_t K, int cus, size_t room, PanelDecomp* out) {
+    if (M <= 32 || M > 128 || M * K * 2 >= (int64_t)1 << 31) return false;
+    const int64_t nb = N / 16, kt = K / tile_k(bits);
+    const int mb = (int)((M + 31) / 32);
+    struct Fit { double fixed, t0[2], t1[2], full, slices, exchange, share; };
+    static const Fit fits[2] = {{4.47, {0.24, 1.154}, {0.549, 0.474}, 0.177, 1.138, 1.234, 0.126},
+                                {3.573, {0.606, 1.532}, {0.496, 0.525}, 0.041, 1.113, 1.049, 0.236}};
+    const Fit& f = fits[bits == 4 ? 0 : 1];
+    double best = 0.;
+    out->ks = 0;
+    for (int rp = 1; rp <= 2; ++rp) {
+        const int64_t shares = (nb + 4 * rp - 1) / (4 * rp);
+        for (int64_t ks = 1; ks <= 32; ++ks) {
+            // (one workgroup per compute unit where K is cut, and a K tile for every wavefront)
+            if (ks > 1 && (shares * ks > cus || ks * kPanelWK > kt || shares * 64 > (int64_t)kCounterBytes ||
+                           (size_t)(shares * ks) * panel_slot_bytes(mb, rp) > room))
+                break;
+            const int64_t grid = shares * ks, rounds = (grid + cus - 1) / cus;
+            const int64_t tiles = ((kt + ks - 1) / ks + kPanelWK - 1) / kPanelWK * (tile_k(bits) / 128);
+            const double filled = (double)grid / (double)(rounds * cus);
+            const double us = (double)rounds * (f.fixed * (1. + f.share * mb * rp) +
+                                                (double)tiles * (f.t0[rp - 1] + f.t1[rp - 1] * mb) * (1. + f.full * filled)) +
+                              (ks > 1 ? f.slices + f.exchange * rp * mb * filled : 0.);
+            if (out->ks == 0 || us < best) {
+                best = us;
+                *out = PanelDecomp{mb, rp, (int)ks, shares};
+            }
+        }
+    }
+    return true;
+}
+
+// Whether a call of M > 32 rows goes to the panel kernel: no plan from the caller, and none registered that its slices
+// of 32 rows would take.
+bool panel_plan(int bits, int group_size, int64_t M, int64_t N, int64_t K, lutq_dtype dtype, const lutq_plan* user_plan, int cus,
+                size_t workspace_bytes, PanelDecomp* out) {
+    if (user_plan && (user_plan->scheduling || user_plan->row_blocks_per_wave || user_plan->grid || user_plan->waves_per_workgroup ||
+                      user_plan->tiles_in_flight || user_plan->row_groups_per_workgroup || user_plan->tiles_per_item))
+        return false;
+    lutq_plan registered;
+    if (!user_plan && plan_table_find(bits, group_size, 32, N, K, dtype, &registered)) return false;
+    return panel_decomp(bits, M, N, K, cus, workspace_bytes > kCounterBytes ? workspace_bytes - kCounterBytes : 0, out);
+}
+
+lutq_status launch_panel(const void* X, const void* packed, const void* scales, const void* lut, int bits, int group_size,
+                         int64_t M, int64_t N, int64_t K, lutq_dtype dtype, void* Y, void* workspace, void* stream, bool pairs,
+                         const PanelDecomp& d) {
+    const int64_t nb = N / 16, kt = K / tile_k(bits);
+    PanelParams q{};
+    q.X = static_cast<const uint16_t*>(X);
+    q.packed = static_cast<const uint8_t*>(packed);
+    q.scales = static_cast<const uint16_t*>(scales);
+    q.lut = static_cast<const uint16_t*>(lut);
+    q.Y = static_cast<uint16_t*>(Y);
+    q.packed_bytes = (uint32_t)(N * K * bits / 8);
+    q.scale_bytes = (uint32_t)(N * (K / group_size) * 2);
+    q.x_bytes = (uint32_t)(M * K * 2);
+    q.M = (int)M; q.N = (int)N; q.K = (int)K; q.NB = (int)nb;
+    q.SG2 = (int)(K / group_size) * 2;
+    q.SBL = ilog2(super_block(nb));
+    const uint32_t tile_bytes = bits == 3 ? 1536u : 1024u;
+    q.tile_stride = tile_bytes << q.SBL;
+    q.sblock_bytes = (uint32_t)kt * q.tile_stride;
+    q.G = (int)(d.shares * d.ks); q.KS = d.ks; q.TS = (int)(kt / d.ks); q.KSB = (int)(kt % d.ks);
+    const int threads = 64 * kPanelWaves;
+    q.lut_ltpe = (bits == 2 ? lut_log2_threads_per_row<2>(threads) : bits == 3 ? lut_log2_threads_per_row<3>(threads)
+                                                                               : lut_log2_threads_per_row<4>(threads)) |
+                 (pairs ? kLutPairsFlag : 0);
+    q.counters = static_cast<uint32_t*>(workspace);
+    q.slots = reinterpret_cast<float*>(static_cast<char*>(workspace) + kCounterBytes);
+    q.slot_bytes = d.ks > 1 ? (uint32_t)((size_t)q.G * panel_slot_bytes(d.mb, d.rp)) : 0u;
+    if (env_switches().verbose)
+        std::fprintf(stderr, "lutq_matmul: panels of %d rows, %d x 32 activation rows, grid=%d (%d K slices)\n", 32 * d.rp, d.mb, q.G, d.ks);
+    const hipError_t e = pick_panel(bits, dtype)(group_size, d.mb, d.rp, q, static_cast<hipStream_t>(stream));
+    return e == hipSuccess ? LUTQ_OK : LUTQ_ERR_DEVICE;
+}
+
 lutq_status matmul_sliced(const void* X, const void* packed, const void* scales, const void* lut,
                           int bits, int group_size, int64_t M, int64_t N, int64_t K,
                           lutq_dtype dtype, void* Y, void* workspace, size_t workspace_bytes,
@@ -1371,6 +1471,16 @@ lutq_status matmul_sliced(const void* X, const void* packed, const void* scales,
         if (dtype != LUTQ_F16 && dtype != LUTQ_BF16) return LUTQ_ERR_DTYPE;
         const DeviceInfo di = device_info();
         if (!di.ok) return LUTQ_ERR_DEVICE;
+        PanelDecomp pd;
+        if (!rowlut && panel_plan(bits, group_size, M, N, K, dtype, user_plan, di.cus, fitted_workspace ? workspace_bytes : kWorkspaceBytes, &pd)) {
+            // one launch for all rows (the checks are those of a slice's)
+            if (!packed || !scales || !lut) return LUTQ_ERR_NULL;
+            if (!aligned16(X) || !aligned16(packed) || !aligned16(scales) || !aligned16(Y) || !aligned16(workspace) ||
+                (reinterpret_cast<uintptr_t>(lut) & 1u) != 0)
+                return LUTQ_ERR_ALIGN;
+            if (!workspace || workspace_bytes < (fitted_workspace ? kCounterBytes : kWorkspaceBytes)) return LUTQ_ERR_WORKSPACE;
+            return launch_panel(X, packed, scales, lut, bits, group_size, M, N, K, dtype, Y, workspace, stream, pairs, pd);
+        }
         step = slice_rows(bits, group_size, M, N, K, dtype == LUTQ_BF16, user_plan, rowlut, di.cus, &st);
         if (st != LUTQ_OK) return st;
     }

@@ -7,6 +7,7 @@
 #include "lutq_matmul_kernel.hpp"
 #include "lutq_decode_kernel.hpp"
 #include "lutq_rows_kernel.hpp"
+#include "lutq_panel_kernel.hpp"
 
 namespace lutq {
 
@@ -40,7 +41,8 @@ inline bool matmul_instance_exists(int bits, bool bf16, int r, int mb, int stage
     hipError_t launch_decode_b##B##_##DT(int group, int r, bool rowlut, const DecodeParams& p, int lds_bytes, \
                                          hipStream_t stream);                                        \
     hipError_t launch_rows_b##B##_##DT(int group, int mb, int amax, bool rowlut, const RowsParams& p, int lds_bytes, \
-                                       hipStream_t stream);
+                                       hipStream_t stream);                                         \
+    hipError_t launch_panel_b##B##_##DT(int group, int mb, int rp, const PanelParams& p, hipStream_t stream);
 
 // Measurement builds (phase timestamps, see TraceStamp) of the 4-bit instances that serve M <= 4 under the
 // default plans: group 64 or 128, R = 1 or 2, two tiles in flight, chunked scales, 128-register build.
