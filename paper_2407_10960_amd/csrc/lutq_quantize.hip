@@ -8,14 +8,23 @@
 // type; u = W / scale is one IEEE fp64 division; the index is the first c that minimises the fp64
 // value |u - T[c]|; a group whose scale is zero takes u = 0.
 //
-// The minimum is found by scanning all 2^b entries, except for a strictly increasing fp16 table of 8
-// or 16 entries (the NormalFloat tables and sorted learned tables are; with 4 entries the scan is the
-// faster of the two): there a binary search over a copy of the table in LDS brackets u between two neighbours and only their two distances are compared.  This gives
-// the same index as the scan: |u| < 2 and fp16 magnitudes are at most 65504, so a distance
-// is below 2^17 and its fp64 rounding error below 2^-36, while two different fp16 values are at least
-// 2^-24 apart -- rounding keeps the distances to different entries in their exact order, the nearest
-// entry is one of the two neighbours, and a tie between them goes to the lower one, which is the
-// lower index.  bf16 values can be closer together than a rounding error, so bf16 tables are scanned.
+// The index is found without a division or a scan for all but a few weights.  |u| is at most 1 + 2^-9 wherever the scale is a
+// normal number (it is the rounded absmax), so the range of u is cut into 512 cells, and a table in LDS says for each cell
+// which index applies below and above the one decision threshold in it (the midpoint of two table entries that are neighbours by
+// value; a cell without one has a threshold that no u reaches).  A weight takes u32 = w * rcp(scale) in fp32, one table read and
+// one comparison.  u32, the threshold (whose low eight mantissa bits hold the two indices: off by at most 2^-17 below 1) and
+// their difference are off by less than kNear together, so a weight whose u32 is kNear or further from its cell's threshold is
+// decided as the fp64 rule decides it.  The others -- about one in eight thousand with a NormalFloat table of 16 entries --, cells
+// with more than one threshold, and groups whose scale is not a normal number of ordinary size go through the fp64 rule itself, lane by lane.
+// That the decision away from thresholds is the nearest entry by value, and the lowest of equal entries, needs that rounding
+// never reorders the smallest distances: with one entry of magnitude up to 1000 the smallest distance is below 1002, an entry
+// beyond 2100 in magnitude is never nearest, the others' distances are below 2^12 and round by less than 2^-41, and different ones
+// among them have to be 2^-40 or more apart; any other table has no thresholds and every weight goes through the fp64 rule.
+//
+// What bounds it: the memory traffic, with the vector unit close behind (twelve instructions a weight).  The table is built
+// per workgroup, so workgroups are few (two per compute unit) and large (eight wavefronts), each walking many units.
+// 8192 x 28672 bf16 to 4 bits, group 64: 138 us, 4.3 TB/s (658 us with an fp64 division and a scan of the sixteen entries per
+// weight); 28672 x 4096 fp32 to 4 bits fp16 189 -> 119 us, fp16 200 -> 68; 1024 x 4096 bf16 17.7 -> 8.8.
 //
 // Work unit: 16 rows x UC columns, UC = max(K tile, group), one wavefront per unit.  Lane l = 16 o + i
 // holds, for every 32-column step t of the unit, the 8 weights W[16 rb + i][col0 + 32 t + 8 o + j] --
@@ -38,7 +47,8 @@ struct QuantParams {
     uint8_t* packed;
     int N, K, KT, SG, SB;     // KT = K / TK, SG = K / group, SB = row blocks per super-block
     int upr;                  // units per row block = K / UC
-    long long units;
+    int nb;                   // row blocks
+    int drb, duc;             // stride of a wavefront: all wavefronts' units, as row blocks and units of a row block
     int bf16;                 // 16-bit type of lut, scales (and of W unless fp32)
 };
 
@@ -59,8 +69,48 @@ __device__ __forceinline__ uint32_t round16(float v, bool bf16) {
     return (uint32_t)__builtin_bit_cast(uint16_t, (_Float16)v);
 }
 
-template <int BITS, int GROUP, bool WF32>
-__global__ __launch_bounds__(256) void quantize_kernel(const QuantParams p) {
+typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+
+constexpr int kQuantWaves = 8;
+constexpr int kCells = 512, kCellCopies = 32;          // one 4-byte entry per lane pair (l, l + 32): every lane has its own bank
+constexpr float kCellScale = 254.f;                    // cell = 256 + round(u * 254): 1 .. 511 for |u| <= 1 + 2^-9
+constexpr float kNear = 8.2e-6f;                       // 2^-17 (threshold) + 2^-22 (u32) + 2^-24 (difference), rounded up
+
+// The fp64 rule: the first entry that minimises |u - T[c]|.
+template <int E>
+__device__ __forceinline__ uint32_t nearest_entry(double u, const double* T) {
+    double best = __builtin_fabs(u - T[0]);
+    uint32_t arg = 0;
+#pragma unroll
+    for (int c = 1; c < E; ++c) {
+        const double d = __builtin_fabs(u - T[c]);
+        const bool less = d < best;
+        best = less ? d : best;
+        arg = less ? (uint32_t)c : arg;
+    }
+    return arg;
+}
+
+// Entry of one cell: threshold with the index below it in bits 0..3 and the index above it in bits 4..7; a quiet NaN where the
+// cell cannot be decided by one threshold below 1.
+template <int E>
+__device__ __forceinline__ uint32_t cell_entry(int cell, const double* T) {
+    // (the margin covers how far u is from the value the cell was chosen with)
+    const double centre = (double)(cell - 256) / (double)kCellScale, half = 0.5 / (double)kCellScale + 2e-5;
+    const uint32_t below = nearest_entry<E>(centre - half, T), above = nearest_entry<E>(centre + half, T);
+    const uint32_t code = below | (above << 4);
+    if (below == above) return 0x7f000000u | code;
+    const double mid = 0.5 * (T[below] + T[above]);
+    const uint32_t at = nearest_entry<E>(mid, T);      // a third entry between the two would be nearest to their midpoint
+    if ((at != below && at != above) || !(__builtin_fabs(mid) < 1.0)) return 0x7fc00000u | code;
+    // the float nearest to the midpoint among those with these low bits (rounding in magnitude; stays below 1 + 2^-16)
+    const uint32_t m = __builtin_bit_cast(uint32_t, (float)mid);
+    return m + 128u < code ? code : ((m + 128u - code) & 0xffffff00u) + code;    // (a midpoint of zero: the smallest denormals)
+}
+
+// WT: how W is held: 0 fp32, 1 fp16, 2 bf16 (the latter two are also the type of the table and the scales)
+template <int BITS, int GROUP, int WT>
+__global__ __launch_bounds__(64 * kQuantWaves) void quantize_kernel(const QuantParams p) {
     constexpr int TK = BITS == 4 ? 128 : 256;
     constexpr int TILE_BYTES = BITS == 3 ? 1536 : 1024;
     constexpr int UC = GROUP > TK ? GROUP : TK;       // columns of one unit
@@ -69,66 +119,83 @@ __global__ __launch_bounds__(256) void quantize_kernel(const QuantParams p) {
     constexpr int SPG = GROUP / 32;                   // steps of one group
     constexpr int NG = UC / GROUP;                    // groups of one unit (per row)
     constexpr int E = 1 << BITS;
-    const bool bf16 = p.bf16 != 0;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    constexpr bool WF32 = WT == 0;
+    const bool bf16 = WF32 ? p.bf16 != 0 : WT == 2;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int i = lane & 15, o = lane >> 4;
 
-    double T[E];
-#pragma unroll
-    for (int c = 0; c < E; ++c) T[c] = (double)widen16(p.lut[c], bf16);
-    __shared__ double Ts[E];
-    bool sorted = !bf16 && BITS >= 3;
-#pragma unroll
-    for (int c = 0; c + 1 < E; ++c) sorted = sorted && T[c] < T[c + 1];
-    if (threadIdx.x < E) {
-        double v = T[0];
-#pragma unroll
-        for (int c = 1; c < E; ++c) v = (int)threadIdx.x == c ? T[c] : v;
-        Ts[threadIdx.x] = v;
+    extern __shared__ __align__(16) char smem[];      // [cells][Ts]
+    double* Ts = reinterpret_cast<double*>(smem + kCells * kCellCopies * 4);
+    if (threadIdx.x < E) Ts[threadIdx.x] = (double)widen16(p.lut[threadIdx.x], bf16);
+    __syncthreads();
+    bool close = false, small = false;                // one pair of entries per thread
+    if (threadIdx.x < E * E) {
+        const double a = Ts[threadIdx.x / E], b = Ts[threadIdx.x % E];
+        small = __builtin_fabs(a) <= 1000.0;
+        close = __builtin_fabs(a) <= 2100.0 && __builtin_fabs(b) <= 2100.0 && a != b && __builtin_fabs(a - b) < 0x1p-40;
+    }
+    const bool thresholds = __syncthreads_or(close) == 0 && __syncthreads_or(small) != 0;
+    for (int cell = threadIdx.x; cell < kCells; cell += 64 * kQuantWaves) {
+        const uint32_t v = thresholds ? cell_entry<E>(cell, Ts) : 0x7fc00000u;
+#pragma unroll 1
+        for (int k = 0; k < kCellCopies / 4; ++k)     // (skewed, so that the lanes of one store hit different banks)
+            *reinterpret_cast<u32x4*>(smem + cell * (kCellCopies * 4) + 16 * ((k + cell) & (kCellCopies / 4 - 1))) = u32x4{v, v, v, v};
     }
     __syncthreads();
+    // u32 * 254 + 2^23 + 256 holds the cell in its low bits; shifted by 7 its exponent leaves 2^31, taken off with the lane's offset
+    const uint32_t cell_lane = (uint32_t)(lane & (kCellCopies - 1)) * 4u - (0x4b000000u << 7);
+    typedef __attribute__((address_space(3))) const uint32_t lds_cu32;
+    const uint32_t cells = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const char*)smem;
 
-    for (long long unit = (long long)blockIdx.x * 4 + wave; unit < p.units; unit += (long long)gridDim.x * 4) {
-        const int rb = (int)(unit / p.upr), uc = (int)(unit % p.upr);
+    // unit = row block x p.upr + unit of the row block; a stride of p.drb row blocks and p.duc units
+    const int first = (int)blockIdx.x * kQuantWaves + wave;
+    int rb = first / p.upr, uc = first % p.upr;
+    for (; rb < p.nb; rb += p.drb, uc += p.duc, rb += uc >= p.upr ? 1 : 0, uc -= uc >= p.upr ? p.upr : 0) {
         const long long row = 16ll * rb + i;
         const int col0 = uc * UC;
-        float w[NSTEP][8];
+        const long long e0 = row * p.K + col0 + 8 * o;
+        u32x4 raw[NSTEP][WF32 ? 2 : 1];
 #pragma unroll
         for (int t = 0; t < NSTEP; ++t) {
-            const long long e = row * p.K + col0 + 32 * t + 8 * o;
-            if constexpr (WF32) {
-                const float4* src = reinterpret_cast<const float4*>(static_cast<const float*>(p.W) + e);
-                const float4 a = src[0], b = src[1];
-                w[t][0] = a.x; w[t][1] = a.y; w[t][2] = a.z; w[t][3] = a.w;
-                w[t][4] = b.x; w[t][5] = b.y; w[t][6] = b.z; w[t][7] = b.w;
-            } else {
-                const u32x4 v = *reinterpret_cast<const u32x4*>(static_cast<const uint16_t*>(p.W) + e);
+            const char* src = static_cast<const char*>(p.W) + (e0 + 32 * t) * (WF32 ? 4 : 2);
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    w[t][2 * j] = widen16(v[j] & 0xffffu, bf16);
-                    w[t][2 * j + 1] = widen16(v[j] >> 16, bf16);
-                }
-            }
+            for (int k = 0; k < (WF32 ? 2 : 1); ++k) raw[t][k] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(src + 16 * k));
         }
+        auto weight = [&](int t, int j) -> float {
+            if constexpr (WF32) {
+                const uint32_t v = raw[t][j / 4][j % 4];
+                return __builtin_bit_cast(float, v);
+            } else return widen16((j & 1) ? raw[t][0][j / 2] >> 16 : raw[t][0][j / 2] & 0xffffu, WT == 2);
+        };
         // group maxima of |w| on the bit patterns (non-negative floats order like unsigned integers)
         uint32_t sbits[NG];
-        double s[NG];
+        float s[NG];
 #pragma unroll
         for (int g = 0; g < NG; ++g) {
             uint32_t m = 0;
+            if constexpr (WF32) {
 #pragma unroll
-            for (int t = g * SPG; t < (g + 1) * SPG; ++t)
+                for (int t = g * SPG; t < (g + 1) * SPG; ++t)
 #pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    const uint32_t a = __builtin_bit_cast(uint32_t, w[t][j]) & 0x7fffffffu;
-                    m = a > m ? a : m;
-                }
+                    for (int j = 0; j < 8; ++j) {
+                        const uint32_t v = raw[t][j / 4][j % 4] & 0x7fffffffu;
+                        m = v > m ? v : m;
+                    }
+            } else {
+                u16x2 m2 = u16x2{0, 0};
+#pragma unroll
+                for (int t = g * SPG; t < (g + 1) * SPG; ++t)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) m2 = __builtin_elementwise_max(m2, __builtin_bit_cast(u16x2, raw[t][0][j] & 0x7fff7fffu));
+                const uint16_t h = m2.x > m2.y ? m2.x : m2.y;
+                m = __builtin_bit_cast(uint32_t, widen16(h, WT == 2));
+            }
             const uint32_t m1 = (uint32_t)__shfl_xor((int)m, 16);
             m = m1 > m ? m1 : m;
             const uint32_t m2 = (uint32_t)__shfl_xor((int)m, 32);
             m = m2 > m ? m2 : m;
             sbits[g] = round16(__builtin_bit_cast(float, m), bf16);
-            s[g] = (double)widen16(sbits[g], bf16);
+            s[g] = widen16(sbits[g], bf16);
         }
         if (o == 0) {
             uint16_t* dst = p.scales + row * p.SG + (long long)uc * NG;
@@ -139,31 +206,50 @@ __global__ __launch_bounds__(256) void quantize_kernel(const QuantParams p) {
         uint32_t idx[NSTEP];                          // 8 indices of step t, 4 bits apart
 #pragma unroll
         for (int t = 0; t < NSTEP; ++t) {
-            const double sg = s[t / SPG];
-            uint32_t word = 0;
+            const float sg = s[t / SPG];
+            // a scale that is zero makes u = 0; one that is not an ordinary number (fp16 subnormals are up to half off the
+            // absmax) sends the group through the fp64 rule
+            const bool ordinary = sg >= (bf16 ? 0x1p-100f : 0x1p-14f) && sg <= 0x1p+100f;
+            const float inv = ordinary ? __builtin_amdgcn_rcpf(sg) : 0.f;
+            const float near = ordinary || sg == 0.f ? kNear : __builtin_inff();
+            const float to_cell = inv * kCellScale;
+            uint32_t word = 0, open = 0;              // open: bit 7 - j set where weight j is not decided
+            uint32_t ent[8];
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
-                const double u = sg == 0.0 ? 0.0 : (double)w[t][j] / sg;
-                uint32_t arg = 0;
-                if (sorted) {                               // (uniform over the launch)
-                    int lower = 0;                          // entries [0, lower) are <= u
+                const float cell = __builtin_fmaf(weight(t, j), to_cell, 0x1p+23f + 256.f);
+                ent[j] = *reinterpret_cast<lds_cu32*>((uintptr_t)((__builtin_bit_cast(uint32_t, cell) << 7) + cell_lane + cells));
+            }
 #pragma unroll
-                    for (int step = E / 2; step >= 1; step >>= 1)
-                        if (Ts[lower + step - 1] <= u) lower += step;
-                    if (Ts[lower] <= u) lower += 1;
-                    const int lo = lower > 0 ? lower - 1 : 0, hi = lower < E ? lower : E - 1;
-                    arg = __builtin_fabs(u - Ts[hi]) < __builtin_fabs(u - Ts[lo]) ? (uint32_t)hi : (uint32_t)lo;
-                } else {
-                    double best = __builtin_fabs(u - T[0]);
+            for (int j = 0; j < 8; ++j) {
+                const float d = weight(t, j) * inv - __builtin_bit_cast(float, ent[j]);
+                const uint32_t code = d > 0.f ? ent[j] >> 4 : ent[j];
+                word = __builtin_amdgcn_alignbit(code, word, 4);
+                open = 2u * open + (__builtin_fabsf(d) >= near ? 0u : 1u);
+            }
+            while (open) {                            // (a lane at a time in effect: rare)
+                const int j = __builtin_clz(open) - 24;
+                open &= ~(128u >> j);
+                float w;
+                if constexpr (WF32) {
+                    uint32_t v = raw[t][0].x;
 #pragma unroll
-                    for (int c = 1; c < E; ++c) {
-                        const double d = __builtin_fabs(u - T[c]);
-                        const bool less = d < best;
-                        best = less ? d : best;
-                        arg = less ? (uint32_t)c : arg;
+                    for (int k = 1; k < 8; ++k) {
+                        const uint32_t x = raw[t][k / 4][k % 4];
+                        v = j == k ? x : v;
                     }
+                    w = __builtin_bit_cast(float, v);
+                } else {
+                    uint32_t v = raw[t][0].x;
+#pragma unroll
+                    for (int k = 1; k < 4; ++k) {
+                        const uint32_t x = raw[t][0][k];
+                        v = (j >> 1) == k ? x : v;
+                    }
+                    w = widen16((j & 1) ? v >> 16 : v & 0xffffu, WT == 2);
                 }
-                word |= arg << (4 * j);
+                const double u = sg == 0.f ? 0.0 : (double)w / (double)sg;
+                word = (word & ~(15u << (4 * j))) | (nearest_entry<E>(u, Ts) << (4 * j));
             }
             idx[t] = word;
         }
@@ -223,8 +309,18 @@ namespace {
 
 template <int BITS, int GROUP>
 hipError_t launch_q(bool wf32, const QuantParams& p, int grid, hipStream_t stream) {
-    if (wf32) hipLaunchKernelGGL((quantize_kernel<BITS, GROUP, true>), dim3(grid), dim3(256), 0, stream, p);
-    else hipLaunchKernelGGL((quantize_kernel<BITS, GROUP, false>), dim3(grid), dim3(256), 0, stream, p);
+    auto kernel = wf32 ? quantize_kernel<BITS, GROUP, 0> : p.bf16 ? quantize_kernel<BITS, GROUP, 2> : quantize_kernel<BITS, GROUP, 1>;
+    constexpr int lds_bytes = kCells * kCellCopies * 4 + (1 << BITS) * 8;
+    // more than 64 KiB of dynamic LDS has to be enabled once per kernel
+    static const hipError_t attr = [] {
+        for (auto k : {quantize_kernel<BITS, GROUP, 0>, quantize_kernel<BITS, GROUP, 1>, quantize_kernel<BITS, GROUP, 2>}) {
+            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, kCells * kCellCopies * 4 + (1 << BITS) * 8);
+            if (e != hipSuccess) return e;
+        }
+        return hipSuccess;
+    }();
+    if (attr != hipSuccess) return attr;
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(64 * kQuantWaves), lds_bytes, stream, p);
     return hipGetLastError();
 }
 
@@ -272,10 +368,14 @@ extern "C" lutq_status lutq_quantize(const void* W, int w_is_f32, const void* lu
     p.SG = (int)(K / group_size);
     p.SB = lutq::layout::super_block(nb);
     p.upr = (int)(K / uc);
-    p.units = nb * (K / uc);
+    const int64_t units = nb * (K / uc);
+    p.nb = (int)nb;
     p.bf16 = dtype == LUTQ_BF16;
-    int64_t grid = (p.units + 3) / 4;
-    if (grid > 16384) grid = 16384;
+    // two workgroups (their tables fill the LDS) per compute unit of the 256; more would only build more tables
+    int64_t grid = (units + lutq::kQuantWaves - 1) / lutq::kQuantWaves;
+    if (grid > 512) grid = 512;
+    p.drb = (int)(grid * lutq::kQuantWaves / p.upr);
+    p.duc = (int)(grid * lutq::kQuantWaves % p.upr);
     const hipStream_t s = static_cast<hipStream_t>(stream);
     const hipError_t e = bits == 2 ? lutq::launch_qb<2>(group_size, w_is_f32 != 0, p, (int)grid, s)
                        : bits == 3 ? lutq::launch_qb<3>(group_size, w_is_f32 != 0, p, (int)grid, s)

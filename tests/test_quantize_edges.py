@@ -1,0 +1,91 @@
+"""lutq_quantize where its table of cells decides least: weights on and beside every decision threshold, tables that are
+not ascending, hold equal, nearly equal or very large entries, and scales that are zero, subnormal, near the ends of the type or infinite.
+Indices and scales equal the oracle's (fp64 division and scan) bit for bit."""
+import numpy as np
+import pytest
+
+import lutq_inputs as gen
+from gpu_util import to_bits, to_dev, torch_dtype
+from oracle import lutq_oracle as orc
+
+pytestmark = pytest.mark.gpu
+
+
+def tables(bits, dtype, rng):
+    E = 1 << bits
+    asc = np.sort(rng.standard_normal(E))
+    asc /= np.abs(asc).max()
+    yield "symmetric", np.linspace(-1, 1, E)                       # a threshold at exactly zero
+    yield "learned", asc
+    yield "descending", asc[::-1]
+    yield "shuffled", rng.permutation(asc)
+    yield "duplicates", np.sort(rng.choice(asc, E))
+    yield "crowded", np.sort(np.concatenate([[-1.0], 0.3 + rng.standard_normal(E - 2) * 1e-3, [1.0]]))   # many thresholds per cell
+    yield "beyond one", asc * 1.7                                  # thresholds at magnitudes above 1
+    yield "large", np.concatenate([asc[:-1], [30000.0]])           # distances whose rounding could reorder them
+    if dtype == "bf16":                                            # different entries that fp64 distances cannot tell apart
+        yield "nearly equal", np.concatenate([[1e-30, -1e-25, 3e-20], asc[3:]])
+
+
+@pytest.mark.parametrize("bits", (2, 3, 4))
+@pytest.mark.parametrize("dtype", ("f16", "bf16"))
+def test_quantize_thresholds_tables_and_scales(lutq, bits, dtype):
+    import torch
+    rng = np.random.default_rng(bits)
+    N, K = 64, 1024
+    for ti, (name, T64) in enumerate(tables(bits, dtype, rng)):
+        group = (32, 64, 128, 256)[ti % 4]
+        T = gen.encode16(np.asarray(T64), dtype)
+        t = np.unique(orc.to_f64(T, dtype))
+        W = (rng.standard_normal((N, K)) * 0.02).astype(np.float32)
+        # a scale of exactly 1, and weights at the thresholds, one fp32 step and some 1e-6 to 1e-4 beside them
+        mids = ((t[:-1] + t[1:]) / 2) if len(t) > 1 else np.zeros(1)
+        mids = mids[np.abs(mids) < 1]
+        if len(mids):
+            off = rng.choice([0, 0, 1e-7, -1e-7, 2e-6, -2e-6, 8e-6, -8e-6, 3e-5, -3e-5, 1e-4, -1e-4], (16, K))
+            W[:16] = np.clip(rng.choice(mids, (16, K)) + off, -1, 1).astype(np.float32)
+            W[1] = np.nextafter(W[1], np.float32(2))
+            W[:16, ::32] = 1.0
+        W[16] = 0.0
+        W[17] *= np.float32(2.0 ** -14)                             # fp16: subnormal scales, or zero ones
+        W[18] *= np.float32(2.0 ** -22)
+        W[19] *= np.float32(2.0 ** -126)                            # bf16: the smallest scales
+        W[20] *= np.float32(2.0 ** 20)                              # fp16: an infinite scale
+        W[21] *= np.float32(2.0 ** 120)                             # bf16: the largest ones
+        W[22] = (2.0 ** rng.integers(-30, 1, K) * rng.choice([-1.0, 1.0], K)).astype(np.float32)
+        for w16 in (False, True):
+            if w16:
+                with np.errstate(over="ignore"):
+                    Wb = gen.encode16(W, dtype)
+                W64 = orc.to_f64(Wb, dtype)
+                W64[~np.isfinite(W64)] = 0.0                        # (weights are finite)
+                Wd = to_dev(gen.encode16(W64, dtype), dtype)
+            else:
+                W64, Wd = W.astype(np.float64), torch.from_numpy(W).cuda()
+            with np.errstate(over="ignore"):
+                Q, S = orc.quantize(W64, T, group, dtype)
+            # a scale of zero makes u = 0 against every entry: the nearest to zero, the lowest of equal ones
+            S_out = torch.zeros((N, K // group), dtype=torch_dtype(dtype), device="cuda")
+            P_out = torch.zeros(lutq.lutq_packed_bytes(N, K, bits, group), dtype=torch.uint8, device="cuda")
+            lutq.lutq_quantize(Wd, to_dev(T, dtype), bits, group, S_out, P_out)
+            what = f"b{bits} {dtype} g{group} {name} w16={w16}"
+            assert np.array_equal(to_bits(S_out), S), what
+            got = lutq.lutq_unpack(P_out.cpu().numpy(), N, K, bits, group)
+            bad = np.argwhere(got != Q)
+            assert not len(bad), f"{what}: {len(bad)} indices differ, first at {bad[0]}"
+
+
+def test_quantize_more_units_than_wavefronts(lutq):
+    """Every wavefront walks several units, the last stride runs past the end: 4112 x 4096 and a single row block."""
+    import torch
+    rng = np.random.default_rng(9)
+    T = gen.encode16(gen.normal_float_table(4), "f16")
+    for N, K, group in ((4112, 4096, 256), (16, 128, 32), (16, 65536, 128)):
+        W = rng.standard_normal((N, K)).astype(np.float32)
+        S_out = torch.zeros((N, K // group), dtype=torch.float16, device="cuda")
+        P_out = torch.zeros(N * K // 2, dtype=torch.uint8, device="cuda")
+        lutq.lutq_quantize(torch.from_numpy(W).cuda(), to_dev(T, "f16"), 4, group, S_out, P_out)
+        got = lutq.lutq_unpack(P_out.cpu().numpy(), N, K, 4, group)
+        rows = np.unique(np.concatenate([np.arange(min(N, 16)), np.arange(N - 16, N), rng.choice(N, 32)]))
+        Q, S = orc.quantize(W[rows].astype(np.float64), T, group, "f16")
+        assert np.array_equal(got[rows], Q) and np.array_equal(to_bits(S_out)[rows], S), (N, K, group)
