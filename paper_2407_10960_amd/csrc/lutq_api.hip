@@ -84,12 +84,6 @@ DeviceInfo device_info() {
     return cache[dev];
 }
 
-// bytes of lutq_dequant's table (log2c copies); entries are 8 bytes for the 2-bit quad table and for the
-// widened bf16 pair tables, else 4
-int lut_bytes(int bits, bool bf16, int log2c) {
-    return ((bits == 3 ? 64 : 256) * ((bits == 2 || bf16) ? 8 : 4)) << log2c;
-}
-
 int ilog2(int v) {
     int l = 0;
     while ((1 << l) < v) ++l;
@@ -704,7 +698,7 @@ Decomp default_decomp(int bits, bool bf16, bool sch, int64_t M, int64_t N, int64
 }
 
 typedef hipError_t (*matmul_launcher)(int, int, int, int, bool, int, bool, int, const MatmulParams&, hipStream_t);
-typedef hipError_t (*dequant_launcher)(int, const DequantParams&, int, int, hipStream_t);
+typedef hipError_t (*dequant_launcher)(int, const DequantParams&, int, hipStream_t);
 
 matmul_launcher pick_matmul(int bits, lutq_dtype dt) {
     if (dt == LUTQ_F16) return bits == 2 ? launch_matmul_b2_F16 : bits == 3 ? launch_matmul_b3_F16 : launch_matmul_b4_F16;
@@ -1903,12 +1897,13 @@ extern "C" lutq_status lutq_dequant(const void* packed, const void* scales, cons
     p.KT = (int)(K / tile_k(bits));
     p.SG = (int)(K / group_size);
     p.SB = super_block(N / 16);
+    p.SBL = ilog2(p.SB);
     p.tiles = (N / 16) * (int64_t)p.KT;
-    p.log2c = 3;
-    int64_t grid = (p.tiles + 3) / 4;
-    const int64_t cap = (int64_t)di.cus * 8;
-    if (grid > cap) grid = cap;
-    hipError_t e = pick_dequant(bits, dtype)(group_size, p, (int)grid, lut_bytes(bits, dtype == LUTQ_BF16, p.log2c) + 2048,
-                                             static_cast<hipStream_t>(stream));
+    // one workgroup per compute unit; fewer wavefronts each where there are few tiles, so that all units get some
+    const int64_t per_unit = (p.tiles + di.cus - 1) / di.cus;
+    p.NW = (int)(per_unit < 4 ? 4 : per_unit > kDequantWaves ? kDequantWaves : per_unit);
+    int64_t grid = (p.tiles + p.NW - 1) / p.NW;
+    if (grid > di.cus) grid = di.cus;
+    const hipError_t e = pick_dequant(bits, dtype)(group_size, p, (int)grid, static_cast<hipStream_t>(stream));
     return e == hipSuccess ? LUTQ_OK : LUTQ_ERR_DEVICE;
 }

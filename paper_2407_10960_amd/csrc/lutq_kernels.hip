@@ -176,8 +176,13 @@ hipError_t launch_rows_group(int mb, int amax, bool rowlut, const RowsParams& p,
 }
 
 template <int GROUP>
-hipError_t launch_dq(const DequantParams& p, int grid, int lds_bytes, hipStream_t stream) {
-    hipLaunchKernelGGL((dequant_kernel<LUTQ_INST_BITS, GROUP, LUTQ_INST_DT>), dim3(grid), dim3(256), lds_bytes, stream, p);
+hipError_t launch_dq(const DequantParams& p, int grid, hipStream_t stream) {
+    auto kernel = dequant_kernel<LUTQ_INST_BITS, GROUP, LUTQ_INST_DT>;
+    const int lds_bytes = dequant_lds_bytes<LUTQ_INST_BITS>(p.NW);
+    static hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    if (attr != hipSuccess) return attr;
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(64 * p.NW), lds_bytes, stream, p);
     return hipGetLastError();
 }
 
@@ -229,12 +234,12 @@ hipError_t LUTQ_NAME(launch_rows_b, LUTQ_INST_BITS, LUTQ_INST_DT)(int group, int
 }
 
 hipError_t LUTQ_NAME(launch_dequant_b, LUTQ_INST_BITS, LUTQ_INST_DT)(int group, const DequantParams& p, int grid,
-                                                                     int lds_bytes, hipStream_t stream) {
+                                                                     hipStream_t stream) {
     switch (group) {
-        case 32: return launch_dq<32>(p, grid, lds_bytes, stream);
-        case 64: return launch_dq<64>(p, grid, lds_bytes, stream);
-        case 128: return launch_dq<128>(p, grid, lds_bytes, stream);
-        case 256: return launch_dq<256>(p, grid, lds_bytes, stream);
+        case 32: return launch_dq<32>(p, grid, stream);
+        case 64: return launch_dq<64>(p, grid, stream);
+        case 128: return launch_dq<128>(p, grid, stream);
+        case 256: return launch_dq<256>(p, grid, stream);
     }
     return hipErrorInvalidValue;
 }
