@@ -9,6 +9,7 @@ import numpy as np
 
 _PKG_DIR = os.path.dirname(os.path.abspath(__file__))
 _LIB = None
+_NATIVE = None       # _lutq_torch: plain calls on the current stream (see _native)
 
 EXPORTED_SYMBOLS = (
     "lutq_status_string", "lutq_packed_bytes", "lutq_pack", "lutq_unpack", "lutq_workspace_bytes",
@@ -131,8 +132,35 @@ def load_library():
     lib.lutq_calib_matmul_trace.restype = ci
     lib.lutq_calib_matmul_trace.argtypes = [vp, vp, vp, vp, ci, ci, i64, i64, i64, ci, vp, vp, sz, vp,
                                             ctypes.POINTER(_CPlan), vp, sz, ctypes.POINTER(ctypes.c_int)]
+    _load_native(lib)
     _LIB = lib
     return lib
+
+
+def _load_native(lib):
+    """Loads the binding's native part and hands it the library's functions."""
+    global _NATIVE
+    path = os.path.join(_PKG_DIR, "_lutq_torch.so")
+    if not os.path.exists(path):
+        raise RuntimeError(f"{path} is missing: build it with `python -m paper_2407_10960_amd.build`")
+    from . import _lutq_torch as native
+    native.bind(*(ctypes.cast(getattr(lib, f), ctypes.c_void_p).value for f in
+                  ("lutq_packed_bytes", "lutq_matmul", "lutq_matmul_static", "lutq_matmul_channel", "lutq_matmul_pairs",
+                   "lutq_matmul_quads", "lutq_quantize", "lutq_dequant")))
+    _NATIVE = native
+
+
+def _native():
+    if _NATIVE is None:
+        load_library()
+    return _NATIVE
+
+
+def _done(code: int, what: str) -> bool:
+    """Whether the native part took the call (-1: it was not a plain one); raises for an error status."""
+    if code > 0:
+        raise LutqError(code, what)
+    return code == 0
 
 
 def _status_string(code: int) -> str:
@@ -265,6 +293,9 @@ def lutq_matmul(X, packed, scales, lut, bits: int, group_size: int, Y, workspace
                 plan: Plan | None = None):
     """Y[M,N] = X[M,K] @ dequant(packed, scales, lut)^T on the GPU.  All tensors are caller-owned
     torch CUDA tensors (X/scales/lut/Y float16 or bfloat16, packed/workspace uint8)."""
+    if stream is None and plan is None and _done(
+            _native().mm(0, X, packed, scales, lut, bits, group_size, Y, workspace), "lutq_matmul"):
+        return Y
     lib = load_library()
     if not (X.is_cuda and packed.is_cuda and scales.is_cuda and lut.is_cuda and Y.is_cuda and workspace.is_cuda):
         raise ValueError("lutq_matmul needs CUDA (HIP) tensors")
@@ -295,6 +326,9 @@ STATIC_SCRATCH_BYTES = 64 * 1024 + 16 * 1024 * 1024
 
 def lutq_matmul_static(X, packed, scales, lut, bits: int, group_size: int, Y, stream=None, plan: Plan | None = None):
     """lutq_matmul on the library's built-in scratch: no workspace argument, nothing is allocated."""
+    if stream is None and plan is None and _done(
+            _native().mm(1, X, packed, scales, lut, bits, group_size, Y, None), "lutq_matmul_static"):
+        return Y
     lib = load_library()
     for t in (X, packed, scales, lut, Y):
         if not (t.is_cuda and t.is_contiguous()):
@@ -316,6 +350,9 @@ def lutq_matmul_static(X, packed, scales, lut, bits: int, group_size: int, Y, st
 
 
 def _matmul_codebook(name, dim, bits, X, packed, scales, codebook, group_size, Y, workspace, stream):
+    if stream is None and _done(
+            _native().mm(3 if dim == 2 else 4, X, packed, scales, codebook, bits, group_size, Y, workspace), name):
+        return Y
     lib = load_library()
     for t in (X, packed, scales, codebook, Y, workspace):
         if not (t.is_cuda and t.is_contiguous()):
@@ -347,6 +384,9 @@ def lutq_matmul_quads(X, packed, scales, codebook, group_size: int, Y, workspace
 
 def lutq_matmul_channel(X, packed, scales, luts, bits: int, group_size: int, Y, workspace, stream=None):
     """lutq_matmul with one table per output row: luts is [N, 2^bits]."""
+    if stream is None and _done(
+            _native().mm(2, X, packed, scales, luts, bits, group_size, Y, workspace), "lutq_matmul_channel"):
+        return Y
     lib = load_library()
     for t in (X, packed, scales, luts, Y, workspace):
         if not (t.is_cuda and t.is_contiguous()):
@@ -413,6 +453,8 @@ def lutq_tune(X, packed_ring, scales_ring, lut, bits: int, group_size: int, Y, w
 def lutq_quantize(W, lut, bits: int, group_size: int, scales_out, packed_out, stream=None):
     """Quantises the dense device matrix W[N,K] (float32, or the 16-bit dtype of lut) against the table:
     writes the group scales and the packed indices that lutq_matmul consumes."""
+    if stream is None and _done(_native().quantize(W, lut, bits, group_size, scales_out, packed_out), "lutq_quantize"):
+        return scales_out, packed_out
     import torch
     lib = load_library()
     for t in (W, lut, scales_out, packed_out):
@@ -436,6 +478,8 @@ def lutq_quantize(W, lut, bits: int, group_size: int, scales_out, packed_out, st
 
 def lutq_dequant(packed, scales, lut, bits: int, group_size: int, W_out, stream=None):
     """W_out[N,K] = round16(lut[Q] * scales) on the GPU (same lookup + scale routine as lutq_matmul)."""
+    if stream is None and _done(_native().dequant(packed, scales, lut, bits, group_size, W_out), "lutq_dequant"):
+        return W_out
     lib = load_library()
     code = _dtype_code(W_out)
     N, K = W_out.shape

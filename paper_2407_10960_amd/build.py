@@ -16,6 +16,7 @@ CSRC = os.path.join(PKG_DIR, "csrc")
 INCLUDE = os.path.join(os.path.dirname(PKG_DIR), "include")
 BUILD_DIR = os.path.join(PKG_DIR, "_build")
 LIB_PATH = os.path.join(PKG_DIR, "liblutq.so")
+TORCH_LIB_PATH = os.path.join(PKG_DIR, "_lutq_torch.so")     # the Python binding's native part
 
 HIP_FLAGS = [
     "-O3", "--offload-arch=gfx950", "-fPIC", "-std=c++17",
@@ -41,6 +42,20 @@ def _run(cmd):
     return out
 
 
+def _torch_binding() -> list:
+    """The command that compiles the binding's native part against the installed torch (host code only)."""
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+    lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    includes = [f"-isystem{d}" for d in (*cpp_extension.include_paths(device_type="cuda"), sysconfig.get_paths()["include"])]
+    return ["g++", "-O2", "-fPIC", "-shared", "-std=c++17", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", f"-I{INCLUDE}", *includes,
+            os.path.join(CSRC, "lutq_torch.cpp"), "-o", TORCH_LIB_PATH, f"-L{lib}", "-ltorch_python", "-ltorch", "-ltorch_cpu",
+            "-lc10", "-lc10_hip"]
+
+
 def build(verbose: bool = False, jobs: int | None = None) -> str:
     os.makedirs(BUILD_DIR, exist_ok=True)
     hipcc = _hipcc()
@@ -63,6 +78,7 @@ def build(verbose: bool = False, jobs: int | None = None) -> str:
     objs.append(obj)
     steps.append(["g++", "-O3", "-fPIC", "-std=c++17", "-fopenmp", f"-I{INCLUDE}",
                   "-c", os.path.join(CSRC, "lutq_pack.cpp"), "-o", obj])
+    steps.insert(0, _torch_binding())
     jobs = jobs or min(8, os.cpu_count() or 1)
     with concurrent.futures.ThreadPoolExecutor(max_workers=jobs) as ex:
         for out in ex.map(_run, steps):

@@ -1,0 +1,71 @@
+"""The binding's native part takes plain calls and leaves every other one to the Python code: same results on the current
+stream, same errors, nothing written where a call is refused."""
+import numpy as np
+import pytest
+
+import lutq_inputs as gen
+
+
+def test_native_part_answers_what_is_not_plain_with_minus_one(lutq):
+    import torch
+    nat = lutq.binding._native()
+    t = torch.zeros((1, 128), dtype=torch.float16)                      # not on the GPU
+    assert nat.mm(0, t, t, t, t, 4, 128, t, t) == -1
+    assert nat.mm(0, None, t, t, t, 4, 128, t, t) == -1
+    assert nat.mm(0, t, t, t, t, "4", 128, t, t) == -1
+    assert nat.mm(0, t, t) == -1
+    assert nat.quantize(t, t, 4, 128, t, t) == -1 and nat.dequant(t, t, t, 4, 128, t) == -1
+    with pytest.raises(TypeError):
+        nat.bind(1)
+    with pytest.raises(ValueError, match="CUDA"):
+        lutq.lutq_matmul(t, t, t, t, 4, 128, t, t)
+
+
+@pytest.mark.gpu
+def test_native_calls_match_the_python_path(lutq):
+    import torch
+    from gpu_util import DeviceCase, to_bits
+    side = torch.cuda.Stream()
+    for M in (1, 7, 40):
+        c = gen.make_case(M, M, 64, 1024, 4, 64, "f16", "nf")
+        d = DeviceCase(lutq, c)
+        want = None
+        for stream in (None, torch.cuda.current_stream(), side):        # a stream given goes through the Python code
+            Y = torch.full((M, c.N), float("nan"), dtype=d.X.dtype, device="cuda")
+            torch.cuda.synchronize()
+            lutq.lutq_matmul(d.X, d.packed, d.S, d.T, 4, 64, Y, d.ws, stream=stream)
+            torch.cuda.synchronize()
+            want = to_bits(Y) if want is None else want
+            assert np.array_equal(to_bits(Y), want)
+        # the current stream is the one that `with torch.cuda.stream` sets: the call waits for what is queued there
+        Y = torch.full((M, c.N), float("nan"), dtype=d.X.dtype, device="cuda")
+        X = torch.zeros_like(d.X)
+        side.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.stream(side):
+            torch.cuda._sleep(2000000)
+            X.copy_(d.X)
+            lutq.lutq_matmul(X, d.packed, d.S, d.T, 4, 64, Y, d.ws)
+        side.synchronize()
+        assert np.array_equal(to_bits(Y), want)
+
+
+@pytest.mark.gpu
+def test_refused_calls_are_refused_as_before(lutq):
+    import torch
+    from gpu_util import DeviceCase
+    c = gen.make_case(1, 3, 64, 1024, 4, 64, "f16", "nf")
+    d = DeviceCase(lutq, c)
+    Y = torch.full((3, 64), 7.0, dtype=torch.float16, device="cuda")
+    call = lambda X=d.X, packed=d.packed, S=d.S, T=d.T, bits=4, group=64, Y=Y, ws=d.ws: \
+        lutq.lutq_matmul(X, packed, S, T, bits, group, Y, ws)
+    for kw, err in (({"X": d.X.cpu()}, ValueError), ({"X": d.X.t()}, ValueError), ({"X": d.X.float()}, TypeError),
+                    ({"S": d.S.bfloat16()}, TypeError), ({"T": d.T[:8].contiguous()}, ValueError), ({"Y": Y[:2]}, ValueError),
+                    ({"packed": d.packed[1:]}, ValueError), ({"group": 32}, ValueError), ({"ws": d.ws[:64]}, lutq.LutqError),
+                    ({"X": d.X[0]}, ValueError), ({"ws": d.ws[1:]}, lutq.LutqError)):
+        with pytest.raises(err):
+            call(**kw)
+    torch.cuda.synchronize()
+    assert (Y == 7.0).all().item()
+    call(bits=np.int64(4))                                               # (an index type, not an int)
+    torch.cuda.synchronize()
+    assert not (Y == 7.0).all().item()
