@@ -1353,56 +1353,65 @@ int slice_rows(int bits, int group_size, int64_t M, int64_t N, int64_t K, bool b
 
 // Panel launch (panel_kernel): 33..128 activation rows in one pass over the weights.
 struct PanelDecomp {
-    int mb, rp, ks;           // blocks of 32 activation rows, panel height / 32, K slices
-    int64_t shares;           // workgroups side by side: 64 rp output channels each
+    int mb, rp, ks;           // blocks of 32 activation rows per workgroup, panel height / 32, K slices
+    int64_t shares;           // shares of the output channels: 64 rp each
+    int ms;                   // parts of M: mb x 32 rows each
 };
 
-// Every call of 33 rows or more without a plan: one pass over the weights measured faster than slices of 32 or 64 rows on
-// every shape tried (us, HBM-cold weights, MI355X, slices -> panel): 8B gate+up W4 fp16 M = 33 / 64 / 96 / 128 28.9 / 33.0 /
-// 54.3 / 65.0 -> 24.9 / 27.3 / 34.6 / 41.8, O 13.1 / 14.6 / 25.2 / 28.8 -> 11.8 / 12.3 / 15.9 / 19.1, down 29.0 / 33.9 / 51.0 /
-// 66.3 -> 19.8 / 21.0 / 27.9 / 31.9, 1024 x 4096 13.7 / 18.6 / 27.8 / 36.7 -> 9.7 / 9.8 / 12.2 / 14.2, 70B gate+up 90 / 104 / 163 /
-// 205 -> 89 / 97 / 124 / 153; W3 bf16 8B down 27.9 / 37.3 / 55.3 / 73.2 -> 20.4 / 21.1 / 27.3 / 32.7, 70B O 27.9 / 36.6 / 54.9 / 73.3 ->
-// 21.6 / 22.8 / 29.6 / 34.0.  (70B QKV W4 at M = 33 24.1 -> 24.6.)
-// The panel height (32 or 64 channels per wavefront) and the number of K slices are those of the least estimated time: a launch
-// costs a fixed part, a part per K tile that a wavefront works on (t0 + t1 per 32 activation rows; the taller panel takes less per
-// weight), more where the chip is full, and with K slices the exchange of partial sums.  The constants are fitted to 380
-// measurements (twelve shapes from 1024 x 4096 to 57344 x 8192, M = 33, 64, 96, 128; 4 bits, and 3 bits in bf16, whose wider tiles
-// count twice); the choice is within 1.3 % of the fastest plan on average, 10 % at worst.
+// Calls of 33 rows or more without a plan: one pass over the weights measured faster than slices of 32 or 64 rows, but for the
+// exceptions of panel_plan (us, HBM-cold weights, MI355X, slices -> panel): 8B gate+up W4 fp16 M = 64 / 96 / 128 33.0 / 54.3 / 65.0 ->
+// 27.8 / 36 / 42.8, O 14.6 / 25.2 / 28.8 -> 11.6 / 13.5 / 13.5, down 33.9 / 51.0 / 66.3 -> 21.7 / 27.7 / 30.5, 1024 x 4096 18.6 /
+// 27.8 / 36.7 -> 8.6 / 8.9 / 9.1, 70B gate+up 104 / 163 / 205 -> 97 / 124 / 153; W3 bf16 8B down 37.3 / 55.3 / 73.2 -> 21.5 / 27.3 /
+// 32.8, 70B O 36.6 / 54.9 / 73.3 -> 23.2 / 29.9 / 33.8.
+// The panel height (32 or 64 channels per wavefront), the number of K slices and the parts of M (a part is 32 mb rows; the weights
+// are read and dequantised once per part, side by side) are those of the least estimated time: a launch costs a fixed part, a
+// part per K tile that a wavefront works on (t0 + t1 per 32 activation rows; the taller panel takes less per weight), more where
+// the chip is full, and with K slices the exchange of partial sums.  Parts of M fill the chip where the matrix is small, without
+// that exchange (8B O M = 128: 4 K slices 18.5, 4 parts of M 13.5; 1024 x 4096 14.0 -> 9.1); a large one is faster in one.  The constants
+// are fitted per bit width to 1260 measurements in all (fourteen shapes from 1024 x 4096 to 28672 x 4096, M = 64, 96, 128); the
+// choice is within 0.6 % of the fastest plan measured on average, 7 % at worst.  (3 bits, 64 channels by 128 rows: no instance,
+// the registers spill.)
 // `room`: bytes of scratch for the slices' partial sums.
 bool panel_decomp(int bits, int64_t M, int64_t N, int64_t K, int cus, size_t room, PanelDecomp* out) {
     if (M <= 32 || M > 128 || M * K * 2 >= (int64_t)1 << 31) return false;
     const int64_t nb = N / 16, kt = K / tile_k(bits);
-    const int mb = (int)((M + 31) / 32);
-    struct Fit { double fixed, t0[2], t1[2], full, slices, exchange, share; };
-    static const Fit fits[2] = {{4.47, {0.24, 1.154}, {0.549, 0.474}, 0.177, 1.138, 1.234, 0.126},
-                                {3.573, {0.606, 1.532}, {0.496, 0.525}, 0.041, 1.113, 1.049, 0.236}};
-    const Fit& f = fits[bits == 4 ? 0 : 1];
+    const int blocks = (int)((M + 31) / 32);
+    struct Fit { double fixed, t0[2], t1[2], full, slices, exchange, share, per_slice; };
+    static const Fit fits[3] = {{4.150, {0.358, 0.625}, {0.406, 0.600}, 0.200, 0.940, 0.945, 0.122, 0.024},     // 2 bits
+                                {3.288, {0.778, 1.815}, {0.408, 0.444}, 0.050, 1.573, 1.092, 0.154, 0.056},     // 3 bits
+                                {3.865, {0.537, 1.092}, {0.453, 0.511}, 0.131, 1.244, 1.022, 0.103, 0.072}};    // 4 bits
+    const Fit& f = fits[bits - 2];
     double best = 0.;
     out->ks = 0;
-    for (int rp = 1; rp <= 2; ++rp) {
-        const int64_t shares = (nb + 4 * rp - 1) / (4 * rp);
-        for (int64_t ks = 1; ks <= 32; ++ks) {
-            // (one workgroup per compute unit where K is cut, and a K tile for every wavefront)
-            if (ks > 1 && (shares * ks > cus || ks * kPanelWK > kt || shares * 64 > (int64_t)kCounterBytes ||
-                           (size_t)(shares * ks) * panel_slot_bytes(mb, rp) > room))
-                break;
-            const int64_t grid = shares * ks, rounds = (grid + cus - 1) / cus;
-            const int64_t tiles = ((kt + ks - 1) / ks + kPanelWK - 1) / kPanelWK * (tile_k(bits) / 128);
-            const double filled = (double)grid / (double)(rounds * cus);
-            const double us = (double)rounds * (f.fixed * (1. + f.share * mb * rp) +
-                                                (double)tiles * (f.t0[rp - 1] + f.t1[rp - 1] * mb) * (1. + f.full * filled)) +
-                              (ks > 1 ? f.slices + f.exchange * rp * mb * filled : 0.);
-            if (out->ks == 0 || us < best) {
-                best = us;
-                *out = PanelDecomp{mb, rp, (int)ks, shares};
+    for (int mb = blocks; mb >= 1; --mb) {
+        const int ms = (blocks + mb - 1) / mb;
+        if (mb < blocks && (blocks + ms - 1) / ms != mb) continue;        // (as many parts do with fewer rows each)
+        for (int rp = 1; rp <= 2; ++rp) {
+            if (!panel_instance_exists(bits, mb, rp)) continue;
+            const int64_t shares = (nb + 4 * rp - 1) / (4 * rp) * ms;      // over all parts of M
+            for (int64_t ks = 1; ks <= 32; ++ks) {
+                // (one workgroup per compute unit where K is cut, and a K tile for every wavefront)
+                if (ks > 1 && (shares * ks > cus || ks * kPanelWK > kt || shares * 64 > (int64_t)kCounterBytes ||
+                               (size_t)(shares * ks) * panel_slot_bytes(mb, rp) > room))
+                    break;
+                const int64_t grid = shares * ks, rounds = (grid + cus - 1) / cus;
+                const int64_t tiles = ((kt + ks - 1) / ks + kPanelWK - 1) / kPanelWK * (tile_k(bits) / 128);
+                const double filled = (double)grid / (double)(rounds * cus);
+                const double us = (double)rounds * (f.fixed * (1. + f.share * mb * rp) +
+                                                    (double)tiles * (f.t0[rp - 1] + f.t1[rp - 1] * mb) * (1. + f.full * filled)) +
+                                  (ks > 1 ? f.slices + f.exchange * rp * mb * filled + f.per_slice * (double)ks * rp * mb : 0.);
+                if (out->ks == 0 || us < best) {
+                    best = us;
+                    *out = PanelDecomp{mb, rp, (int)ks, shares / ms, ms};
+                }
             }
         }
     }
     return true;
 }
 
-// Whether a call of M > 32 rows goes to the panel kernel: no plan from the caller, and none registered that its slices
-// of 32 rows would take.
+// Whether a call of M > 32 rows goes to the panel kernel: no plan from the caller, none registered that its slices of 32 rows
+// would take, and not one of the cases where the row-streaming kernel is faster.
 bool panel_plan(int bits, int group_size, int64_t M, int64_t N, int64_t K, lutq_dtype dtype, const lutq_plan* user_plan, int cus,
                 size_t workspace_bytes, PanelDecomp* out) {
     if (user_plan && (user_plan->scheduling || user_plan->row_blocks_per_wave || user_plan->grid || user_plan->waves_per_workgroup ||
@@ -1410,6 +1419,16 @@ bool panel_plan(int bits, int group_size, int64_t M, int64_t N, int64_t K, lutq_
         return false;
     lutq_plan registered;
     if (!user_plan && plan_table_find(bits, group_size, 32, N, K, dtype, &registered)) return false;
+    // Where one row-streaming launch (4 bits, up to 64 rows, blocks of sixteen) stays the faster: up to 48 rows, three such blocks,
+    // in bf16 with more than one row block per compute unit and K up to 8192 (us, row streaming against panel, M = 40: 8B QKV
+    // 14.5 / 15.6, 70B QKV 24.1 / 27.1, 70B O 21.8 / 22.3, 8B gate+up 29.1 / 29.6, 70B gate+up 89 / 103; a longer K, 70B down, 59.7 /
+    // 52.5), in fp16 with eight row blocks per compute unit (70B gate+up 86 / 89) or two to three (70B QKV 23.6 / 24.2; elsewhere 5
+    // to 20 % slower); up to 64 rows in bf16 with eight or more (70B gate+up 103 / 107).
+    const int64_t nb = N / 16;
+    const bool bf16 = dtype == LUTQ_BF16;
+    if (bits == 4 && (M <= 48 ? (bf16 ? nb > cus && K <= 8192 : nb >= 8 * (int64_t)cus || (nb > 2 * (int64_t)cus && nb <= 3 * (int64_t)cus))
+                              : M <= 64 && bf16 && nb >= 8 * (int64_t)cus))
+        return false;
     return panel_decomp(bits, M, N, K, cus, workspace_bytes > kCounterBytes ? workspace_bytes - kCounterBytes : 0, out);
 }
 
@@ -1432,7 +1451,7 @@ lutq_status launch_panel(const void* X, const void* packed, const void* scales, 
     const uint32_t tile_bytes = bits == 3 ? 1536u : 1024u;
     q.tile_stride = tile_bytes << q.SBL;
     q.sblock_bytes = (uint32_t)kt * q.tile_stride;
-    q.G = (int)(d.shares * d.ks); q.KS = d.ks; q.TS = (int)(kt / d.ks); q.KSB = (int)(kt % d.ks);
+    q.G = (int)(d.shares * d.ks * d.ms); q.shares = (int)d.shares; q.KS = d.ks; q.TS = (int)(kt / d.ks); q.KSB = (int)(kt % d.ks);
     const int threads = 64 * kPanelWaves;
     q.lut_ltpe = (bits == 2 ? lut_log2_threads_per_row<2>(threads) : bits == 3 ? lut_log2_threads_per_row<3>(threads)
                                                                                : lut_log2_threads_per_row<4>(threads)) |
@@ -1441,7 +1460,7 @@ lutq_status launch_panel(const void* X, const void* packed, const void* scales, 
     q.slots = reinterpret_cast<float*>(static_cast<char*>(workspace) + kCounterBytes);
     q.slot_bytes = d.ks > 1 ? (uint32_t)((size_t)q.G * panel_slot_bytes(d.mb, d.rp)) : 0u;
     if (env_switches().verbose)
-        std::fprintf(stderr, "lutq_matmul: panels of %d rows, %d x 32 activation rows, grid=%d (%d K slices)\n", 32 * d.rp, d.mb, q.G, d.ks);
+        std::fprintf(stderr, "lutq_matmul: panels of %d rows, %d x 32 activation rows in %d parts, grid=%d (%d K slices)\n", 32 * d.rp, d.mb, d.ms, q.G, d.ks);
     const hipError_t e = pick_panel(bits, dtype)(group_size, d.mb, d.rp, q, static_cast<hipStream_t>(stream));
     return e == hipSuccess ? LUTQ_OK : LUTQ_ERR_DEVICE;
 }

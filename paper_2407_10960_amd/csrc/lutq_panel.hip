@@ -26,16 +26,19 @@ hipError_t launch_panel_sch(const PanelParams& p, hipStream_t stream) {
 
 template <int GROUP, int MB, int RP>
 hipError_t launch_panel_one(const PanelParams& p, hipStream_t stream) {
-    return p.SG2 % 16 == 0 ? launch_panel_sch<GROUP, MB, RP, true>(p, stream) : launch_panel_sch<GROUP, MB, RP, false>(p, stream);
+    if constexpr (!panel_instance_exists(LUTQ_INST_BITS, MB, RP)) return hipErrorInvalidValue;
+    else return p.SG2 % 16 == 0 ? launch_panel_sch<GROUP, MB, RP, true>(p, stream) : launch_panel_sch<GROUP, MB, RP, false>(p, stream);
 }
 
 template <int GROUP>
 hipError_t launch_panel_group(int mb, int rp, const PanelParams& p, hipStream_t stream) {
     if (rp == 1) {
+        if (mb == 1) return launch_panel_one<GROUP, 1, 1>(p, stream);
         if (mb == 2) return launch_panel_one<GROUP, 2, 1>(p, stream);
         if (mb == 3) return launch_panel_one<GROUP, 3, 1>(p, stream);
         if (mb == 4) return launch_panel_one<GROUP, 4, 1>(p, stream);
     } else if (rp == 2) {
+        if (mb == 1) return launch_panel_one<GROUP, 1, 2>(p, stream);
         if (mb == 2) return launch_panel_one<GROUP, 2, 2>(p, stream);
         if (mb == 3) return launch_panel_one<GROUP, 3, 2>(p, stream);
         if (mb == 4) return launch_panel_one<GROUP, 4, 2>(p, stream);

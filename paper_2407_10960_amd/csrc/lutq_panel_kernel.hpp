@@ -4,8 +4,8 @@
 // take longer than the weight stream (8B gate+up at M = 128: 30 GFLOP, 12 us at 2.5 PFLOP/s, against 58.7 MB of weights),
 // so this kernel is laid out like a matrix product whose A operand is dequantised on the way in:
 //
-//   * A wavefront owns a panel of 32 RP output channels x all M activation rows (accumulators 32 RP x 32 MB) and dequantises
-//     every weight of it exactly once; the workgroup is two panels side by side (WN) times four parts of K (WK).
+//   * A wavefront owns a panel of 32 RP output channels x 32 MB activation rows (all of them, or where the matrix is small a part
+//     of M per workgroup) and dequantises every weight of it exactly once; the workgroup is two panels side by side (WN) times four parts of K (WK).
 //   * Matrix instruction 32x32x16.  The packed tile is in the operand order of the 16x16x32 one (lane 16 o + i = row i, K
 //     octet o), so two row blocks' words are exchanged once per tile: v_permlane16_swap turns (block 0, block 1) into octets
 //     {0, 2} of both blocks and octets {1, 3} of both blocks, which are A operands of two 32x32x16 instructions (K inside
@@ -72,13 +72,14 @@ struct PanelParams {
     int SBL;                  // log2 of the row blocks per super-block of the packed layout
     uint32_t tile_stride;     // packed bytes from K tile kt to kt + 1 of one row block
     uint32_t sblock_bytes;    // packed bytes of one super-block
-    int G;                    // workgroups = shares x KS
-    int KS;                   // K slices: workgroup b works on slice b % KS of share b / KS
+    int G;                    // workgroups = parts of M (32 MB rows each) x shares x KS
+    int shares;               // shares of the output channels, 64 RP each
+    int KS;                   // K slices: workgroup b works on slice b % KS of share (b / KS) % shares of M part b / KS / shares
     int TS, KSB;              // K tiles per slice; the first KSB slices have one more
     int lut_ltpe;
     float* slots;             // KS > 1: partial sums, one slot of RP x MB x 8 KiB per workgroup
     uint32_t slot_bytes;      // ... of all workgroups
-    uint32_t* counters;       // KS > 1: arrivals, eight per share (one 64-byte line); zero between launches
+    uint32_t* counters;       // KS > 1: arrivals, eight per share and M part (one 64-byte line); zero between launches
 };
 
 constexpr int kAuxDevice = 16;   // sc1: past the compute unit's and the die's own caches, what agent-scope atomic accesses use
@@ -90,6 +91,8 @@ __host__ __device__ constexpr int panel_kc(int mb) { return mb <= 2 ? 64 : 32; }
 __host__ __device__ constexpr int panel_depth(int mb, int rp) { return mb == 4 && rp == 2 ? 1 : 2; }
 // K tiles of weights in flight
 __host__ __device__ constexpr int panel_stages(int bits, int mb, int rp) { return bits == 4 && (rp == 1 || mb == 2) ? 4 : 2; }
+// (3 bits, two bit-slices per tile: 64 channels x 128 rows do not fit the registers)
+__host__ __device__ constexpr bool panel_instance_exists(int bits, int mb, int rp) { return !(bits == 3 && mb == 4 && rp == 2); }
 __host__ __device__ constexpr int panel_xbuf_bytes(int mb) { return 32 * mb * panel_kc(mb) * 2; }
 // [table, 256-byte entry stride][per K part: two activation buffers], of which the final reduction takes four tiles' sums; then
 // [per wavefront: 64 rows' eight scales, 1 KiB][per wavefront: two progress words]
@@ -123,7 +126,7 @@ __global__ __launch_bounds__(64 * kPanelWaves) void panel_kernel(const PanelPara
 
     asm volatile("" ::"s"(p.X), "s"(p.packed), "s"(p.scales), "s"(p.lut), "s"(p.Y), "s"(p.packed_bytes), "s"(p.scale_bytes),
                  "s"(p.x_bytes), "s"(p.M), "s"(p.N), "s"(p.K), "s"(p.NB), "s"(p.SG2), "s"(p.SBL), "s"(p.tile_stride),
-                 "s"(p.sblock_bytes), "s"(p.KS), "s"(p.TS), "s"(p.KSB), "s"(p.lut_ltpe));
+                 "s"(p.sblock_bytes), "s"(p.shares), "s"(p.KS), "s"(p.TS), "s"(p.KSB), "s"(p.lut_ltpe));
 
     extern __shared__ __align__(16) char smem[];
     const int tid = threadIdx.x;
@@ -139,9 +142,12 @@ __global__ __launch_bounds__(64 * kPanelWaves) void panel_kernel(const PanelPara
     const LutAddr la = make_lut_addr<BITS, TT>(lut, LOG2C, lane);
     const rsrc_t rW = make_rsrc(p.packed, p.packed_bytes);
     const rsrc_t rS = make_rsrc(p.scales, p.scale_bytes);
-    const rsrc_t rX = make_rsrc(p.X, p.x_bytes);
 
-    const int share = (int)blockIdx.x / p.KS, slice = (int)blockIdx.x - share * p.KS;
+    // workgroup = (part of M, share of the rows, K slice); a part is 32 MB activation rows
+    const int gshare = (int)blockIdx.x / p.KS, slice = (int)blockIdx.x - gshare * p.KS;
+    const int mpart = gshare / p.shares, share = gshare - mpart * p.shares;
+    const int m0 = mpart * 32 * MB;
+    const rsrc_t rX = make_rsrc(p.X + (size_t)m0 * p.K, p.x_bytes - (uint32_t)m0 * (uint32_t)p.K * 2u);
     const int rbw = (share * kPanelWN + wn) * 2 * RP;                   // first row block of the wavefront's panel
     // the slice's tiles over the four K parts
     const int st_n = p.TS + (slice < p.KSB ? 1 : 0);
@@ -253,11 +259,6 @@ __global__ __launch_bounds__(64 * kPanelWaves) void panel_kernel(const PanelPara
         load_x(xr[(1 + d) % D], (1 + d) / CH, (1 + d) % CH);
         __builtin_amdgcn_sched_barrier(0);
     }
-#pragma unroll
-    for (int q = 1; q < P - 1; ++q) {
-        load_stage(st[q], q);
-        __builtin_amdgcn_sched_barrier(0);
-    }
     {
         LutSeed seed = lut_seed;
         asm volatile("" : "+v"(seed.w[0]), "+v"(seed.w[1]), "+v"(seed.w[2]), "+v"(seed.w[3]));
@@ -278,6 +279,11 @@ __global__ __launch_bounds__(64 * kPanelWaves) void panel_kernel(const PanelPara
     uint32_t* other = flags + 2 * (wave ^ 1);
     __syncthreads();
     __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int q = 1; q < P - 1; ++q) {                  // (before the barrier the first activations would queue behind them)
+        load_stage(st[q], q);
+        __builtin_amdgcn_sched_barrier(0);
+    }
     auto publish = [&](int word, int v) {
         asm volatile("" ::: "memory");
         if (lane == 0) __hip_atomic_store(own + word, (uint32_t)v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -441,7 +447,7 @@ seen = __builtin_bit_cast(u32x2, __hip_atomic_load(reinterpret_cast<uint64_t*>(o
     auto emit = [&](int task, f32x4 lo, f32x4 hi) {
         const int j = task >> 2, pn = (task >> 1) & 1, half = task & 1;
         const int rp = j / MB, mb = j % MB;
-        const int m = 32 * mb + 16 * half + om, n = nrow0 + (pn * RP + rp) * 32 + 8 * ok;
+        const int m = m0 + 32 * mb + 16 * half + om, n = nrow0 + (pn * RP + rp) * 32 + 8 * ok;
         if (m < p.M && n < p.N) {
             const u32x2 a = pack4<DT>(lo), c = pack4<DT>(hi);
             *reinterpret_cast<u32x4*>(p.Y + (size_t)m * p.N + n) = u32x4{a.x, a.y, c.x, c.y};
@@ -487,7 +493,7 @@ seen = __builtin_bit_cast(u32x2, __hip_atomic_load(reinterpret_cast<uint64_t*>(o
         // their slots in slice order, its own included, and writes Y (it is the only one whose loads follow all arrivals)
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
         __builtin_amdgcn_s_waitcnt(0);
-        uint32_t* counter = p.counters + (size_t)share * 16 + wave;
+        uint32_t* counter = p.counters + (size_t)gshare * 16 + wave;
         uint32_t old = 0;
         if (lane == 0) old = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         old = __builtin_amdgcn_readfirstlane(old);
@@ -497,7 +503,7 @@ seen = __builtin_bit_cast(u32x2, __hip_atomic_load(reinterpret_cast<uint64_t*>(o
         // all of the wavefront's tasks, SB slices at a time in flight together (a slice beyond the last is not loaded -- its
         // offset is out of range -- and not added)
         constexpr int PT = (TILES * 4 + kPanelWaves - 1) / kPanelWaves, SB = PT > 2 ? 4 : 8;
-        const uint32_t base = (uint32_t)(share * p.KS) * (uint32_t)panel_slot_bytes(MB, RP) + 16u * (uint32_t)lane;
+        const uint32_t base = (uint32_t)(gshare * p.KS) * (uint32_t)panel_slot_bytes(MB, RP) + 16u * (uint32_t)lane;
         f32x4 lo[PT], hi[PT];
 #pragma unroll
         for (int i = 0; i < PT; ++i) lo[i] = hi[i] = f32x4{0.f, 0.f, 0.f, 0.f};

@@ -17,7 +17,9 @@ pytestmark = pytest.mark.gpu
 # of super-blocks of one
 EDGES = [(33, 1, 1, 32), (64, 3, 2, 128), (65, 4, 3, 64), (96, 5, 4, 32), (97, 13, 5, 128), (128, 21, 8, 64),
          (128, 8, 9, 32), (50, 257, 4, 64), (128, 300, 8, 128), (100, 64, 33, 32), (80, 128, 16, 256), (34, 640, 6, 64),
-         (128, 1024, 4, 128)]
+         (128, 1024, 4, 128),
+         # parts of M: small matrices, the last part of one row, of 32, or (M = 65 above) all but empty
+         (65, 16, 32, 128), (97, 40, 8, 32), (128, 64, 4, 64), (72, 256, 2, 256), (128, 256, 8, 128)]
 
 
 @pytest.mark.parametrize("bits", (4, 3, 2))
