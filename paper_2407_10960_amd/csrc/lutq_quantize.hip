@@ -23,8 +23,8 @@
 //
 // What bounds it: the memory traffic, with the vector unit close behind (twelve instructions a weight).  The table is built
 // per workgroup, so workgroups are few (two per compute unit) and large (eight wavefronts), each walking many units.
-// 8192 x 28672 bf16 to 4 bits, group 64: 138 us, 4.3 TB/s (658 us with an fp64 division and a scan of the sixteen entries per
-// weight); 28672 x 4096 fp32 to 4 bits fp16 189 -> 119 us, fp16 200 -> 68; 1024 x 4096 bf16 17.7 -> 8.8.
+// 8192 x 28672 bf16 to 4 bits, group 64: 129 us, 4.6 TB/s (658 us with an fp64 division and a scan of the sixteen entries per
+// weight); 28672 x 4096 fp32 to 4 bits fp16 189 -> 117 us, fp16 200 -> 62; 1024 x 4096 bf16 17.7 -> 8.8.
 //
 // Work unit: 16 rows x UC columns, UC = max(K tile, group), one wavefront per unit.  Lane l = 16 o + i
 // holds, for every 32-column step t of the unit, the 8 weights W[16 rb + i][col0 + 32 t + 8 o + j] --
@@ -155,11 +155,12 @@ __global__ __launch_bounds__(64 * kQuantWaves) void quantize_kernel(const QuantP
         const int col0 = uc * UC;
         const long long e0 = row * p.K + col0 + 8 * o;
         u32x4 raw[NSTEP][WF32 ? 2 : 1];
+        // (plain loads: a row's 128-byte lines are read by two instructions, and with non-temporal ones 138 us instead of 129)
 #pragma unroll
         for (int t = 0; t < NSTEP; ++t) {
             const char* src = static_cast<const char*>(p.W) + (e0 + 32 * t) * (WF32 ? 4 : 2);
 #pragma unroll
-            for (int k = 0; k < (WF32 ? 2 : 1); ++k) raw[t][k] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(src + 16 * k));
+            for (int k = 0; k < (WF32 ? 2 : 1); ++k) raw[t][k] = *reinterpret_cast<const u32x4*>(src + 16 * k);
         }
         auto weight = [&](int t, int j) -> float {
             if constexpr (WF32) {
