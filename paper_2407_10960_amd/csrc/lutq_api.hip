@@ -1360,8 +1360,8 @@ struct PanelDecomp {
 
 // Calls of 33 rows or more without a plan: one pass over the weights measured faster than slices of 32 or 64 rows, but for the
 // exceptions of panel_plan (us, HBM-cold weights, MI355X, slices -> panel): 8B gate+up W4 fp16 M = 64 / 96 / 128 33.0 / 54.3 / 65.0 ->
-// 27.8 / 36 / 42.8, O 14.6 / 25.2 / 28.8 -> 11.6 / 13.5 / 13.5, down 33.9 / 51.0 / 66.3 -> 21.7 / 27.7 / 30.5, 1024 x 4096 18.6 /
-// 27.8 / 36.7 -> 8.6 / 8.9 / 9.1, 70B gate+up 104 / 163 / 205 -> 97 / 124 / 153; W3 bf16 8B down 37.3 / 55.3 / 73.2 -> 21.5 / 27.3 /
+// 25.2 / 36 / 40.2, O 14.6 / 25.2 / 28.8 -> 11.8 / 13.5 / 13.5, down 33.9 / 51.0 / 66.3 -> 19.9 / 27.7 / 27.9, 1024 x 4096 18.6 /
+// 27.8 / 36.7 -> 8.8 / 8.9 / 8.9, 70B gate+up 104 / 163 / 205 -> 93 / 124 / 148; W3 bf16 8B down 37.3 / 55.3 / 73.2 -> 21.5 / 27.3 /
 // 32.8, 70B O 36.6 / 54.9 / 73.3 -> 23.2 / 29.9 / 33.8.
 // The panel height (32 or 64 channels per wavefront), the number of K slices and the parts of M (a part is 32 mb rows; the weights
 // are read and dequantised once per part, side by side) are those of the least estimated time: a launch costs a fixed part, a

@@ -11,13 +11,13 @@
 //     {0, 2} of both blocks and octets {1, 3} of both blocks, which are A operands of two 32x32x16 instructions (K inside
 //     an instruction may be permuted as long as B agrees).  One instruction per word, and every B operand read from LDS then
 //     feeds twice the multiplications of a 16x16x32.
-//   * Activations go through LDS, in chunks of KC columns per K part, double buffered, shared by the two panels; one
-//     barrier per chunk.  A lane fetches 16 bytes of one row; its place inside the row's 2 KC bytes is permuted by the row
+//   * Activations go through LDS, in chunks of KC columns per K part, double buffered, shared by the two panels, whose
+//     wavefronts keep in step through two words in LDS (no barrier in the K loop).  A lane fetches 16 bytes of one row; its place inside the row's 2 KC bytes is permuted by the row
 //     number (swz), so that global reads are whole 64- or 128-byte pieces of rows, the LDS writes are contiguous and the
 //     operand reads (32 rows, one octet each) hit all banks evenly.
 //   * The tables hold 16-bit pairs at every type: bf16 pairs are widened in registers, since LDS (operands, lookups) and not
 //     the vector unit is what the matrix instructions wait for here.
-//   * What bounds it: no unit is full.  8B gate+up, M = 128, W4 fp16, 41.8 us (two slices of 64 rows on the row-streaming kernel
+//   * What bounds it: no unit is full.  8B gate+up, M = 128, W4 fp16, 40-42 us (two slices of 64 rows on the row-streaming kernel
 //     took 65.0; the dense fp16 product of the same shape 56): matrix units busy 40 % of a compute unit's time, LDS 40 %, vector
 //     unit 28 %; alone the matrix instructions and the reduction take 27.5 us, with the lookups and operand reads 28.9, the
 //     staging of the activations adds 8-11 us, the pairs' handshake 2, the weight loads 3.  Deeper activation prefetch, K ranges
@@ -87,10 +87,11 @@ constexpr int kPanelQuarter = 1088;   // LDS bytes from one parked quarter tile 
 constexpr int kPanelWN = 2, kPanelWK = 4, kPanelWaves = kPanelWN * kPanelWK;
 // columns of K per activation chunk
 __host__ __device__ constexpr int panel_kc(int mb) { return mb <= 2 ? 64 : 32; }
-// chunks of activations held in registers on their way to LDS, ahead of the one being written
-__host__ __device__ constexpr int panel_depth(int mb, int rp) { return mb == 4 && rp == 2 ? 1 : 2; }
-// K tiles of weights in flight
-__host__ __device__ constexpr int panel_stages(int bits, int mb, int rp) { return bits == 4 && (rp == 1 || mb == 2) ? 4 : 2; }
+// chunks of activations held in registers on their way to LDS, ahead of the one being written, and K tiles of weights in flight.
+// (4 bits, 33..64 rows: one and two measured faster than two and four, 8B gate+up M = 64 29.2 -> 27.6 us, 70B down 52.7 -> 50.9; 128 rows
+// by 64 channels leave registers for one chunk and two tiles only; with 32 rows four tiles are 2 % faster than two.)
+__host__ __device__ constexpr int panel_depth(int bits, int mb, int rp) { return (mb == 4 && rp == 2) || (bits == 4 && mb == 2) ? 1 : 2; }
+__host__ __device__ constexpr int panel_stages(int bits, int mb, int rp) { return bits == 4 && rp == 1 && mb != 2 ? 4 : 2; }
 // (3 bits, two bit-slices per tile: 64 channels x 128 rows do not fit the registers)
 __host__ __device__ constexpr bool panel_instance_exists(int bits, int mb, int rp) { return !(bits == 3 && mb == 4 && rp == 2); }
 __host__ __device__ constexpr int panel_xbuf_bytes(int mb) { return 32 * mb * panel_kc(mb) * 2; }
@@ -118,7 +119,7 @@ __global__ __launch_bounds__(64 * kPanelWaves) void panel_kernel(const PanelPara
     constexpr int LOG2C = perm_log2_copies<BITS, TT>();
     constexpr int LUT_BYTES = lut_row_table_bytes<BITS>();
     constexpr int KC = panel_kc(MB), SPC = KC / 32, CH = TK / KC;      // chunk, its steps, chunks per tile
-    constexpr int D = panel_depth(MB, RP), P = panel_stages(BITS, MB, RP);
+    constexpr int D = panel_depth(BITS, MB, RP), P = panel_stages(BITS, MB, RP);
     constexpr int SL = KC / 8;                         // 16-byte slots of one row of a chunk
     constexpr int XL = MB * SL / 4;                    // activation loads per wavefront and chunk
     constexpr int XB = panel_xbuf_bytes(MB);
