@@ -33,6 +33,7 @@ from .binding import (  # noqa: F401
     calib_stream_read,
     calib_copy,
     calib_matmul_trace,
+    calib_route,
     TRACE_STAMPS,
     EXPORTED_SYMBOLS,
 )

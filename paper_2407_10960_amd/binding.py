@@ -14,7 +14,7 @@ _NATIVE = None       # _lutq_torch: plain calls on the current stream (see _nati
 EXPORTED_SYMBOLS = (
     "lutq_status_string", "lutq_packed_bytes", "lutq_pack", "lutq_unpack", "lutq_workspace_bytes",
     "lutq_plan_default", "lutq_plan_default_for", "lutq_plan_check", "lutq_pack_layout", "lutq_plan_table_set", "lutq_plan_table_lookup", "lutq_matmul", "lutq_matmul_plan", "lutq_matmul_static", "lutq_matmul_channel", "lutq_matmul_pairs", "lutq_matmul_quads", "lutq_tune", "lutq_tune_candidates", "lutq_quantize", "lutq_dequant",
-    "lutq_calib_stream_read", "lutq_calib_copy", "lutq_calib_matmul_trace",
+    "lutq_calib_stream_read", "lutq_calib_copy", "lutq_calib_matmul_trace", "lutq_calib_route",
 )
 
 LUTQ_F16, LUTQ_BF16 = 0, 1
@@ -132,6 +132,8 @@ def load_library():
     lib.lutq_calib_matmul_trace.restype = ci
     lib.lutq_calib_matmul_trace.argtypes = [vp, vp, vp, vp, ci, ci, i64, i64, i64, ci, vp, vp, sz, vp,
                                             ctypes.POINTER(_CPlan), vp, sz, ctypes.POINTER(ctypes.c_int)]
+    lib.lutq_calib_route.restype = ci
+    lib.lutq_calib_route.argtypes = [ci, ci, i64, i64, i64, ci, ci, sz, ctypes.POINTER(ctypes.c_int)]
     _load_native(lib)
     _LIB = lib
     return lib
@@ -508,6 +510,18 @@ def calib_stream_read(src, grid: int, sink, stream=None):
 def calib_copy(src, dst, grid: int, stream=None):
     _check(load_library().lutq_calib_copy(src.data_ptr(), dst.data_ptr(), src.numel() * src.element_size(), grid,
                                           _stream_ptr(stream)), "lutq_calib_copy")
+
+
+def calib_route(bits: int, group_size: int, M: int, N: int, K: int, dtype_code: int = LUTQ_F16, compute_units: int = 256,
+                workspace_bytes: int | None = None) -> tuple:
+    """How lutq_matmul serves 33..128 rows without a plan: (0, blocks of 32 rows and panel height / 32 per workgroup, K
+    slices, parts of M) for the one launch, else (rows per slice, 0, 0, 0, 0).  Host logic, no device needed."""
+    if workspace_bytes is None:
+        workspace_bytes = lutq_workspace_bytes(N, K, bits, group_size)
+    r = (ctypes.c_int * 5)()
+    _check(load_library().lutq_calib_route(bits, group_size, M, N, K, dtype_code, compute_units, workspace_bytes, r),
+           "lutq_calib_route")
+    return tuple(r)
 
 
 TRACE_STAMPS = ("start", "arguments arrived", "first loads issued", "table built", "first tile multiplied",

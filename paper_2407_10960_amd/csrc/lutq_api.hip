@@ -1651,6 +1651,21 @@ extern "C" lutq_status lutq_matmul(const void* X, const void* packed, const void
                             workspace_bytes, stream, nullptr);
 }
 
+extern "C" int lutq_calib_route(int bits, int group_size, int64_t M, int64_t N, int64_t K, int dtype, int compute_units,
+                                size_t workspace_bytes, int* route) {
+    if (!route) return LUTQ_ERR_NULL;
+    lutq_status st = check_problem(bits, group_size, N, K);
+    if (st != LUTQ_OK) return st;
+    if (M <= 32 || M > kMaxRows || compute_units < 1 || compute_units > 4096) return LUTQ_ERR_SHAPE;
+    if (dtype != LUTQ_F16 && dtype != LUTQ_BF16) return LUTQ_ERR_DTYPE;
+    PanelDecomp d;
+    const bool one = panel_plan(bits, group_size, M, N, K, (lutq_dtype)dtype, nullptr, compute_units, workspace_bytes, &d);
+    const int slice = one ? 0 : slice_rows(bits, group_size, M, N, K, dtype == LUTQ_BF16, nullptr, false, compute_units, &st);
+    const int out[5] = {slice, one ? d.mb : 0, one ? d.rp : 0, one ? d.ks : 0, one ? d.ms : 0};
+    std::copy(out, out + 5, route);
+    return st;
+}
+
 extern "C" int lutq_calib_matmul_trace(const void* X, const void* packed, const void* scales, const void* lut,
                                        int bits, int group_size, int64_t M, int64_t N, int64_t K, int dtype,
                                        void* Y, void* workspace, size_t workspace_bytes, void* stream,

@@ -9,12 +9,9 @@ from gpu_util import DeviceCase, to_bits, to_dev
 from oracle import lutq_oracle as orc
 from test_gpu_parity import check_y, tk
 
-pytestmark = pytest.mark.gpu
-
 # (M, row blocks, K tiles, group): one K tile for four parts and a lone row block; panels cut by the last row block; scale rows
 # that are not whole 16-byte units (the scales go tile by tile) and ones that are (eight at a time); uneven K slices; two
-# super-block sizes (257..512 row blocks); the taller panel with and without slices (from its fitted choice); an odd number
-# of super-blocks of one
+# super-block sizes (257..512 row blocks); an odd number of super-blocks of one (34 rows: at 4 bits a row-streaming launch)
 EDGES = [(33, 1, 1, 32), (64, 3, 2, 128), (65, 4, 3, 64), (96, 5, 4, 32), (97, 13, 5, 128), (128, 21, 8, 64),
          (128, 8, 9, 32), (50, 257, 4, 64), (128, 300, 8, 128), (100, 64, 33, 32), (80, 128, 16, 256), (34, 640, 6, 64),
          (128, 1024, 4, 128),
@@ -22,6 +19,79 @@ EDGES = [(33, 1, 1, 32), (64, 3, 2, 128), (65, 4, 3, 64), (96, 5, 4, 32), (97, 1
          (65, 16, 32, 128), (97, 40, 8, 32), (128, 64, 4, 64), (72, 256, 2, 256), (128, 256, 8, 128)]
 
 
+# One case per instance of the kernel that the choice reaches, each with and without K slices and with scales eight at a time and
+# tile by tile (a class: blocks of 32 rows, panel height / 32, slices, scales eight at a time); (M, row blocks, K tiles, group)
+CLASSES = {
+    4: [(33, 1, 1, 32), (33, 1, 2, 32), (50, 1, 12, 256), (33, 1, 12, 32), (65, 600, 1, 64), (66, 600, 2, 32), (96, 200, 33, 32),
+        (90, 200, 48, 64), (97, 257, 1, 32), (120, 257, 2, 32), (97, 96, 33, 128), (128, 96, 40, 32), (100, 600, 1, 128),
+        (97, 600, 2, 32), (97, 257, 33, 64), (128, 257, 40, 128), (65, 768, 1, 32), (80, 768, 2, 32), (65, 200, 40, 256),
+        (96, 200, 40, 128), (65, 1280, 1, 32), (96, 1280, 2, 32), (70, 384, 64, 128), (97, 1280, 1, 64), (128, 1280, 2, 32),
+        (100, 257, 112, 256)],
+    3: [(33, 1, 1, 256), (64, 1, 1, 32), (40, 1, 9, 128), (33, 1, 8, 32), (65, 128, 20, 256), (96, 128, 20, 64), (97, 257, 1, 128),
+        (128, 257, 1, 32), (97, 96, 12, 256), (100, 96, 12, 32), (33, 1280, 1, 64), (64, 1280, 1, 32), (50, 384, 33, 256),
+        (33, 384, 33, 32), (65, 600, 1, 256), (90, 600, 1, 32), (65, 160, 20, 256), (96, 160, 20, 128), (65, 1280, 1, 128),
+        (96, 1280, 1, 32), (65, 384, 33, 64), (80, 384, 33, 32), (97, 600, 1, 256), (128, 600, 1, 32), (128, 200, 33, 256),
+        (97, 257, 24, 128)],
+    2: [(33, 1, 1, 256), (64, 1, 1, 32), (40, 1, 9, 128), (33, 1, 8, 32), (65, 600, 1, 64), (96, 600, 1, 32), (65, 128, 20, 256),
+        (90, 128, 20, 64), (97, 257, 1, 128), (128, 257, 1, 32), (97, 96, 20, 256), (100, 96, 20, 32), (97, 600, 1, 128),
+        (128, 600, 1, 32), (97, 200, 33, 256), (97, 257, 24, 32), (65, 768, 1, 256), (96, 768, 1, 32), (65, 256, 33, 64),
+        (80, 96, 64, 128), (65, 1280, 1, 256), (96, 1280, 1, 32), (70, 384, 33, 64), (65, 384, 33, 32), (97, 1280, 1, 64),
+        (128, 1280, 1, 32), (100, 600, 33, 256), (97, 600, 24, 32)],
+}
+
+
+def route_class(lutq, bits, dtype, M, nb, kt, group):
+    """The class of a call's launch, None where it is served in slices."""
+    K = kt * tk(bits)
+    r = lutq.calib_route(bits, group, M, 16 * nb, K, 0 if dtype == "f16" else 1)
+    return None if r[0] else (r[1], r[2], r[3] > 1, K // group * 2 % 16 == 0)
+
+
+@pytest.mark.parametrize("bits", (4, 3, 2))
+@pytest.mark.parametrize("dtype", ("f16", "bf16"))
+def test_cases_reach_every_instance_the_choice_reaches(lutq, bits, dtype):
+    """CLASSES names every class that shapes up to 3584 row blocks, 128 K tiles and 128 rows lead to, and EDGES is served by
+    one launch (host logic, 256 compute units)."""
+    reached = set()
+    for M in (33, 64, 65, 96, 97, 128):
+        for nb in (1, 2, 3, 5, 8, 13, 16, 24, 32, 48, 64, 96, 128, 160, 200, 256, 257, 300, 384, 448, 512, 600, 640, 768, 1024, 1280,
+                   1792, 2048, 2560, 3584):
+            for kt in (1, 2, 3, 4, 8, 9, 12, 16, 20, 24, 32, 33, 40, 48, 64, 80, 112, 128):
+                for group in (32, 64, 256):
+                    if kt * tk(bits) % group == 0 and 16 * nb * kt * tk(bits) * bits < 1 << 34:
+                        reached.add(route_class(lutq, bits, dtype, M, nb, kt, group))
+    covered = [route_class(lutq, bits, dtype, *case) for case in CLASSES[bits]]
+    assert None not in covered and len(set(covered)) == len(covered)
+    assert reached - {None} == set(covered)
+    for M, nb, kt, group in EDGES:
+        K = kt * tk(bits)
+        kt = (K + K % group) // tk(bits)
+        assert (bits == 4 and M == 34) or route_class(lutq, bits, dtype, M, nb, kt, group) is not None, (M, nb, kt, group)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("bits", (4, 3, 2))
+@pytest.mark.parametrize("dtype", ("f16", "bf16"))
+def test_every_instance_matches_oracle(lutq, bits, dtype):
+    """All rows of 160 sampled weight rows, first and last row blocks included, of every class."""
+    workspace, rng = None, np.random.default_rng(bits)
+    for i, (M, nb, kt, group) in enumerate(CLASSES[bits]):
+        N = 16 * nb
+        c = gen.make_case(700 + i, M, N, kt * tk(bits), bits, group, dtype, "random_index")
+        d = DeviceCase(lutq, c)
+        workspace = d.ws if workspace is None else workspace
+        d.ws = workspace
+        what = f"b{bits} {dtype} M{M} N{N} K{c.K} g{group}"
+        print(what, flush=True)
+        Y = to_bits(d.matmul(lutq))
+        rows = np.arange(N) if N <= 160 else np.unique(np.concatenate([np.arange(16), np.arange(N - 16, N), rng.choice(N, 128, replace=False)]))
+        check_y(Y[:, rows], gen.Case(M, len(rows), c.K, bits, group, dtype, c.X, c.Q[rows], c.S[rows], c.T), what)
+        assert np.isfinite(orc.to_f64(Y, dtype)).all(), what
+        assert np.array_equal(Y, to_bits(d.matmul(lutq))), f"{what}: not reproducible"
+        assert not workspace[:65536].any().item(), what
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("bits", (4, 3, 2))
 @pytest.mark.parametrize("dtype", ("f16", "bf16"))
 def test_panel_matches_oracle(lutq, bits, dtype):
@@ -40,6 +110,7 @@ def test_panel_matches_oracle(lutq, bits, dtype):
         assert not workspace[:65536].any().item(), what
 
 
+@pytest.mark.gpu
 @pytest.mark.parametrize("op,bits,dim", (("lutq_matmul_pairs", 4, 2), ("lutq_matmul_quads", 2, 4)))
 def test_panel_codebooks_and_static_scratch(lutq, op, bits, dim):
     """A codebook made of the scalar table, and the built-in scratch, give the call's own bits."""
@@ -59,6 +130,7 @@ def test_panel_codebooks_and_static_scratch(lutq, op, bits, dim):
             assert np.array_equal(to_bits(Y), want)
 
 
+@pytest.mark.gpu
 def test_panel_rows_do_not_touch_each_other(lutq):
     """An infinity in the last activation row reaches that row alone, and rows beyond M are not written."""
     import torch
@@ -73,6 +145,7 @@ def test_panel_rows_do_not_touch_each_other(lutq):
     assert not torch.isfinite(Y[40]).any().item() and (Y[41:] == 7.0).all().item()
 
 
+@pytest.mark.gpu
 def test_panel_graph_replays_match_eager(lutq):
     """Captured with K slices (counters and partial sums in the workspace), replayed with eager calls between."""
     import torch
@@ -93,6 +166,7 @@ def test_panel_graph_replays_match_eager(lutq):
             assert np.array_equal(to_bits(d.matmul(lutq)), want)
 
 
+@pytest.mark.gpu
 def test_registered_and_given_plans_keep_the_slices(lutq):
     """A plan given, or registered for slices of 32 rows, is what runs: the bits are those of the slices."""
     c = gen.make_case(3, 96, 16 * 24, 2048, 4, 64, "f16", "nf")
