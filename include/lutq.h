@@ -213,9 +213,11 @@ lutq_status lutq_plan_check(int bits, int group_size, int64_t M, int64_t N, int6
 /* Plans chosen by measurement (lutq_tune; Section 4.1 picks the kernel configuration per shape offline and
  * dispatches on it): a process-wide table that lutq_matmul and lutq_matmul_static consult, when no plan
  * is passed, before their own choice.  An entry applies to calls with its bits, group_size, dtype, N,
- * K and m_min <= M <= m_max (for M > 32 the M of each slice of up to 32 rows counts; slices of 33..64
- * rows have a single decomposition and do not consult the table); the first match wins; an
- * entry whose plan the kernels cannot run for a call is skipped (the library's own choice is used). */
+ * K and m_min <= M <= m_max; the first match wins; an entry whose plan the kernels cannot run for a call,
+ * or whose plan is all zero, is skipped (the library's own choice is used).  A call of M > 32 goes in slices of
+ * 32 rows for the sake of the table where the first match for 32 rows is such that they can run it, and the library's own
+ * slices on that shape are not of 64 rows (those have a single decomposition and do not consult the table); the M of each
+ * slice counts then. */
 typedef struct {
     int bits, group_size;
     lutq_dtype dtype;

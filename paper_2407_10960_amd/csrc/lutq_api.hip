@@ -872,7 +872,9 @@ lutq_status prepare_rows(const void* X, const void* packed, const void* scales, 
     const int amax = d.rs + (extra ? 1 : 0);
     if (ks > 1) {
         if (rowlut || mb > 2 || ks > kt || amax > d.r || (int64_t)shares * 64 > (int64_t)kCounterBytes) return LUTQ_ERR_PLAN;
-        if (!dry && (!scratch || (size_t)d.grid * d.r * mb * 1024 > scratch_room)) return scratch ? LUTQ_ERR_SCRATCH : LUTQ_ERR_PLAN;
+        // (a dry run with a room of zero does not ask)
+        if (!dry && !scratch) return LUTQ_ERR_PLAN;
+        if ((!dry || scratch_room) && (size_t)d.grid * d.r * mb * 1024 > scratch_room) return LUTQ_ERR_SCRATCH;
     }
     const int64_t ts = kt / ks;                               // K tiles per slice (the first kt % ks slices: one more)
     // the scales of a pass's row blocks are staged in LDS in 16-byte units: row by row with 16 bytes of padding, or, where a
@@ -1137,7 +1139,7 @@ lutq_status prepare_matmul(const void* X, const void* packed, const void* scales
             if (ks > 1) {
                 const lutq_status rs = prepare_rows(X, packed, scales, lut, bits, group_size, M, N, K, bf16, Y, q, out, false,
                                                     dry ? nullptr : static_cast<char*>(workspace) + kCounterBytes,
-                                                    dry ? 0 : workspace_bytes - kCounterBytes, dry);
+                                                    dry && !fitted_workspace ? 0 : workspace_bytes - kCounterBytes, dry);
                 return rs;
             }
             return prepare_rows(X, packed, scales, lut, bits, group_size, M, N, K, bf16, Y, q, out);
@@ -1410,15 +1412,28 @@ bool panel_decomp(int bits, int64_t M, int64_t N, int64_t K, int cus, size_t roo
     return true;
 }
 
-// Whether a call of M > 32 rows goes to the panel kernel: no plan from the caller, none registered that its slices of 32 rows
-// would take, and not one of the cases where the row-streaming kernel is faster.
+bool plan_is_zero(const lutq_plan& p) {
+    return !(p.scheduling || p.row_blocks_per_wave || p.grid || p.waves_per_workgroup || p.tiles_in_flight || p.row_groups_per_workgroup ||
+             p.tiles_per_item);
+}
+
+// Whether a call of M > 32 rows without a plan is one that a registered plan serves: it goes in slices of 32 rows (those of 64 have
+// one decomposition and take no plan from the table) and the entry for 32 rows asks for something that can run in this scratch.
+bool registered_plan_runs(int bits, int group_size, int64_t M, int64_t N, int64_t K, lutq_dtype dtype, int cus, size_t workspace_bytes) {
+    lutq_plan registered;
+    if (!plan_table_find(bits, group_size, 32, N, K, dtype, &registered) || plan_is_zero(registered)) return false;
+    lutq_status st;
+    if (slice_rows(bits, group_size, M, N, K, dtype == LUTQ_BF16, nullptr, false, cus, &st) != 32) return false;
+    Prepared q{};
+    return prepare_matmul(nullptr, nullptr, nullptr, nullptr, bits, group_size, 32, N, K, dtype, nullptr, nullptr, workspace_bytes,
+                          &registered, false, cus, &q, true) == LUTQ_OK;
+}
+
+// Whether a call of M > 32 rows goes to the panel kernel: no plan from the caller, none registered that serves it, and not one of
+// the cases where the row-streaming kernel is faster.
 bool panel_plan(int bits, int group_size, int64_t M, int64_t N, int64_t K, lutq_dtype dtype, const lutq_plan* user_plan, int cus,
                 size_t workspace_bytes, PanelDecomp* out) {
-    if (user_plan && (user_plan->scheduling || user_plan->row_blocks_per_wave || user_plan->grid || user_plan->waves_per_workgroup ||
-                      user_plan->tiles_in_flight || user_plan->row_groups_per_workgroup || user_plan->tiles_per_item))
-        return false;
-    lutq_plan registered;
-    if (!user_plan && plan_table_find(bits, group_size, 32, N, K, dtype, &registered)) return false;
+    if (user_plan ? !plan_is_zero(*user_plan) : registered_plan_runs(bits, group_size, M, N, K, dtype, cus, workspace_bytes)) return false;
     // Where one row-streaming launch (4 bits, up to 64 rows, blocks of sixteen) stays the faster: up to 48 rows, three such blocks,
     // in bf16 with more than one row block per compute unit and K up to 8192 (us, row streaming against panel, M = 40: 8B QKV
     // 14.5 / 15.6, 70B QKV 24.1 / 27.1, 70B O 21.8 / 22.3, 8B gate+up 29.1 / 29.6, 70B gate+up 89 / 103; a longer K, 70B down, 59.7 /

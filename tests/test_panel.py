@@ -182,3 +182,38 @@ def test_registered_and_given_plans_keep_the_slices(lutq):
     finally:
         lutq.lutq_plan_table_set([])
     check_y(to_bits(d.matmul(lutq)), c, "one launch")
+
+
+def test_only_a_registered_plan_that_can_run_keeps_the_slices(lutq):
+    """Routes of calls of 33..128 rows with plans registered for up to 32 rows (host logic, 256 compute units)."""
+    def route(plan, bits, N, K, M=96, m_max=32, ws=None):
+        try:
+            lutq.lutq_plan_table_set([(bits, 128, 0, 1, m_max, N, K, plan)])
+            return lutq.calib_route(bits, 128, M, N, K, 0, 256, ws)[0]
+        finally:
+            lutq.lutq_plan_table_set([])
+    decode = lutq.Plan(1, 256, 12, 2, 7, 2, 4)
+    team = lutq.Plan(1, 128, 8, 2, 1)
+    assert route(team, 4, 2048, 4096) == 32 and route(team, 3, 28672, 4096) == 32        # slices of 32 rows that run it
+    assert route(team, 4, 28672, 4096, 128) == 0                # its slices are of 64 rows, which take no plan from the table
+    assert route(decode, 4, 2048, 4096) == 0                    # a work queue is for up to four rows
+    assert route(lutq.Plan(1, 0, 8, 2, 3), 4, 2048, 4096) == 0                           # eight waves are not three teams
+    assert route(team, 4, 2048, 4096, m_max=16) == 0 and route(lutq.Plan(), 4, 2048, 4096) == 0
+    # 64 MiB of partial sums fit a workspace and not the built-in scratch; so do a row-streaming plan's slices
+    for plan in (lutq.Plan(4, 4095, 4, 2, 1), lutq.Plan(8, 4096, 0, 2, 8, 3, 1)):
+        assert lutq.lutq_plan_check(4, 128, 32, 2048, 32768, 0, 256, plan) == 0
+        assert route(plan, 4, 2048, 32768) == 32 and route(plan, 4, 2048, 32768, ws=lutq.STATIC_SCRATCH_BYTES) == 0
+
+
+@pytest.mark.gpu
+def test_registered_plans_that_do_not_serve_a_call_leave_its_bits(lutq):
+    for N, plan in ((4096, lutq.Plan(1, 128, 8, 2, 1)), (384, lutq.Plan(1, 0, 8, 2, 3))):
+        c = gen.make_case(5, 100, N, 1024, 4, 64, "f16", "nf")
+        d = DeviceCase(lutq, c)
+        want = to_bits(d.matmul(lutq))
+        try:
+            lutq.lutq_plan_table_set([(4, 64, 0, 1, 32, c.N, c.K, plan)])
+            assert np.array_equal(to_bits(d.matmul(lutq)), want)
+        finally:
+            lutq.lutq_plan_table_set([])
+        check_y(want, c, f"N{N}")
