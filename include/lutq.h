@@ -346,7 +346,9 @@ lutq_status lutq_tune(const void* X, const void* const* packed, const void* cons
                       lutq_dtype dtype, void* Y, void* workspace, size_t workspace_bytes, void* stream,
                       int reps, lutq_plan* best, float* best_us);
 
-/* The plans lutq_tune tries for this problem on the current device, the default plan first.
+/* The plans lutq_tune tries for this problem on the current device, the default plan first.  For M > 32
+ * that is the all-zero plan, which asks for what a call without a plan takes (a registered all-zero plan
+ * is the library's choice, too); lutq_plan_default's plan of the slices comes second.
  * Writes min(*count, capacity) of them to plans (host) and their number to *count; plans may be
  * NULL when capacity is 0.  Some of them have no kernel instance: lutq_matmul_plan answers those
  * with LUTQ_ERR_PLAN, and lutq_tune skips them. */

@@ -1715,8 +1715,8 @@ extern "C" int lutq_calib_matmul_trace(const void* X, const void* packed, const 
 
 namespace {
 
-// Candidate work decompositions of lutq_tune: the default plan first, then every combination of row
-// blocks per wave, teams, waves per team, grid (one workgroup per set of row groups, or 1/2, 1, 2, 4
+// Candidate work decompositions of lutq_tune: the default plan first (beyond 32 rows the empty plan, which is what a call
+// without one takes, then that of its slices), then every combination of row blocks per wave, teams, waves per team, grid (one workgroup per set of row groups, or 1/2, 1, 2, 4
 // workgroups per compute unit with the K range cut where they do not divide the tiles) and pipeline
 // depth that passes the ranges of lutq_plan.  Combinations without a kernel instance are rejected by
 // lutq_matmul_plan when they are tried.
@@ -1732,8 +1732,10 @@ std::vector<lutq_plan> tune_candidates(int bits, int group_size, int64_t M, int6
                 return;
         out.push_back(c);
     };
+    // (beyond 32 rows what a call without a plan takes is no plan of its own but the empty one)
+    if (M > 32) out.push_back(lutq_plan{});
     lutq_plan def;
-    if (lutq_plan_default(bits, group_size, M, N, K, dtype, &def) == LUTQ_OK) out.push_back(def);
+    if (lutq_plan_default(bits, group_size, M, N, K, dtype, &def) == LUTQ_OK) push_unique(def);
     const int64_t nb = N / 16, kt = K / tile_k(bits);
     if (M <= 4 && (K / group_size) % 8 == 0) {
         // work-queue plans with uneven shares: one workgroup per compute unit (or per two), R = 1
@@ -1842,6 +1844,7 @@ extern "C" lutq_status lutq_tune(const void* X, const void* const* packed, const
     lutq_plan def;
     lutq_status st = lutq_plan_default(bits, group_size, M, N, K, dtype, &def);
     if (st != LUTQ_OK) return st;
+    if (M > 32) def = lutq_plan{};
     hipStream_t s = static_cast<hipStream_t>(stream);
     // the default plan validates every other argument; its launches also bring the clocks up
     int next = 0;
