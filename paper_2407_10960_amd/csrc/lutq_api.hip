@@ -239,6 +239,9 @@ bool wide_rows_decomp(int bits, bool bf16, int64_t M, int64_t N, int64_t K, int 
     return true;
 }
 
+// Bytes of the operand-order copy of the activations that a row-streaming launch of more than 32 rows makes in the scratch.
+size_t xop_bytes(int64_t M, int64_t K) { return M > 32 ? (size_t)(K / 32) * ((M + 15) / 16) * 1024 : 0; }
+
 // LDS bytes of a work-queue launch
 int queue_lds_bytes(int bits, int nw, int items, int r) {
     return bits == 2 ? decode_lds_bytes<2>(nw, items, r) : bits == 3 ? decode_lds_bytes<3>(nw, items, r) : decode_lds_bytes<4>(nw, items, r);
@@ -860,8 +863,8 @@ lutq_status prepare_rows(const void* X, const void* packed, const void* scales, 
     const int mb = M > 32 ? (int)((M + 15) / 16) : M > 16 ? 2 : 1;
     const int ks = d.ks > 1 ? d.ks : 1;
     // beyond 32 rows the kernel reads the activations from their operand-order copy in the scratch
-    const size_t xop_bytes = mb > 2 ? (size_t)(K / 32) * mb * 1024 : 0;
-    if (mb > 2 && (rowlut || (!dry && (!scratch || xop_bytes > scratch_room)))) return LUTQ_ERR_PLAN;
+    const size_t xop = xop_bytes(M, K);
+    if (mb > 2 && (rowlut || (!dry && (!scratch || xop > scratch_room)))) return LUTQ_ERR_PLAN;
     const int max_waves = rows_instance_waves(bits, bf16, mb, d.r);
     if (max_waves == 0 || d.nw < 4 || d.nw > max_waves || d.stages != 2) return LUTQ_ERR_PLAN;
     // K slices: grid = shares x ks workgroups; a share's row blocks in one pass; partial sums and counters in the scratch
@@ -905,7 +908,7 @@ lutq_status prepare_rows(const void* X, const void* packed, const void* scales, 
     if (mb > 2) {
         out->xp = XopParams{static_cast<const uint16_t*>(X), static_cast<uint16_t*>(scratch), (int)M, (int)K, mb, tile_k(bits) / 32};
         q.X = static_cast<const uint16_t*>(scratch);
-        q.x_bytes = (uint32_t)xop_bytes;
+        q.x_bytes = (uint32_t)xop;
     }
     q.M = (int)M; q.N = (int)N; q.K = (int)K; q.KT = (int)kt;
     q.SG2 = (int)(K / group_size) * 2;
@@ -1439,12 +1442,18 @@ bool panel_plan(int bits, int group_size, int64_t M, int64_t N, int64_t K, lutq_
     // 14.5 / 15.6, 70B QKV 24.1 / 27.1, 70B O 21.8 / 22.3, 8B gate+up 29.1 / 29.6, 70B gate+up 89 / 103; a longer K, 70B down, 59.7 /
     // 52.5), in fp16 with eight row blocks per compute unit (70B gate+up 86 / 89) or two to three (70B QKV 23.6 / 24.2; elsewhere 5
     // to 20 % slower); up to 64 rows in bf16 with eight or more (70B gate+up 103 / 107).
+    // (only where that launch exists and its copy of the activations fits the scratch: with scale rows too long for LDS the call would
+    // go in slices of 32 rows instead, 10240 x 28672 group 32 fp16 M = 40 102 us against 59)
     const int64_t nb = N / 16;
     const bool bf16 = dtype == LUTQ_BF16;
-    if (bits == 4 && (M <= 48 ? (bf16 ? nb > cus && K <= 8192 : nb >= 8 * (int64_t)cus || (nb > 2 * (int64_t)cus && nb <= 3 * (int64_t)cus))
-                              : M <= 64 && bf16 && nb >= 8 * (int64_t)cus))
+    const size_t room = workspace_bytes > kCounterBytes ? workspace_bytes - kCounterBytes : 0;
+    Decomp rows;
+    bool take = false;
+    if (bits == 4 && M <= 64 && wide_rows_decomp(bits, bf16, M, N, K, group_size, cus, &rows, &take) && take && xop_bytes(M, K) <= room &&
+        (M <= 48 ? (bf16 ? nb > cus && K <= 8192 : nb >= 8 * (int64_t)cus || (nb > 2 * (int64_t)cus && nb <= 3 * (int64_t)cus))
+                 : bf16 && nb >= 8 * (int64_t)cus))
         return false;
-    return panel_decomp(bits, M, N, K, cus, workspace_bytes > kCounterBytes ? workspace_bytes - kCounterBytes : 0, out);
+    return panel_decomp(bits, M, N, K, cus, room, out);
 }
 
 lutq_status launch_panel(const void* X, const void* packed, const void* scales, const void* lut, int bits, int group_size,

@@ -239,3 +239,14 @@ def test_tuner_times_the_single_launch(lutq):
         assert np.array_equal(to_bits(d.matmul(lutq)), want)
     finally:
         lutq.lutq_plan_table_set([])
+
+
+def test_row_streaming_keeps_a_call_only_where_its_launch_exists(lutq):
+    """4 bits, up to 64 rows: scale rows too long for the LDS of that launch, or a copy of the activations that does not fit the
+    scratch, leave the call to the panel kernel (slices of 32 rows, or none at all, would be what is left)."""
+    for M, N, K, group in ((40, 10240, 28672, 32), (33, 12288, 24576, 32), (48, 12288, 32768, 32)):
+        assert lutq.lutq_plan_default_for(4, group, M, N, K, 0, 256).scheduling != 3
+        assert lutq.calib_route(4, group, M, N, K, 0)[0] == 0
+    for M in (33, 48):
+        K = 180224                                   # 16.5 MiB and more of activations
+        assert lutq.calib_route(4, 64, M, 10240, K, 0, 256, lutq.STATIC_SCRATCH_BYTES)[0] == 0
