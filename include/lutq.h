@@ -22,7 +22,8 @@
  *
  * Supported domain: bits in {2,3,4}; group_size in {32,64,128,256}; 1 <= M <= 128
  * (one launch on the caller's stream, the weights streamed once.  Beyond 32 rows that is a kernel of its
- * own with no plan to choose; a call with a plan, with a registered plan that fits slices of 32 rows, or
+ * own with no plan to choose, or at 4 bits up to 64 rows, where that is the faster, a slice of 64 rows; a call with
+ * a plan, with a registered plan that slices of 32 rows can run, or
  * with one table per output row is served in slices instead, one launch each: 32 rows, or, at 4 bits where the plan
  * asks for LUTQ_SCHED_ROWS, 64 rows, each such launch preceded by a small one that copies the slice's
  * activations into the workspace in the order the matrix instruction reads them);

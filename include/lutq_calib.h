@@ -43,7 +43,7 @@ int lutq_calib_matmul_trace(const void* X, const void* packed, const void* scale
 /* How lutq_matmul serves a call of 33..128 rows without a plan on a device with `compute_units` compute
  * units (1..4096) and a workspace of `workspace_bytes`; host logic only, no device is touched (the plan
  * table counts).  route[0] = 0: one launch for all rows, each workgroup on 32 route[1] activation rows by
- * 128 route[2] output channels, with K cut into route[3] slices and M into route[4] parts; else
+ * 64 route[2] output channels, with K cut into route[3] slices and M into route[4] parts; else
  * route[0] = the rows per launch of the slices it is served in (32 or 64) and the others are 0.
  * Return values: 0, or the status lutq_matmul would give the problem (SHAPE also for M <= 32). */
 int lutq_calib_route(int bits, int group_size, int64_t M, int64_t N, int64_t K, int dtype, int compute_units,

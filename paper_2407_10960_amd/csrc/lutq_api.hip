@@ -1363,8 +1363,8 @@ struct PanelDecomp {
     int ms;                   // parts of M: mb x 32 rows each
 };
 
-// Calls of 33 rows or more without a plan: one pass over the weights measured faster than slices of 32 or 64 rows, but for the
-// exceptions of panel_plan (us, HBM-cold weights, MI355X, slices -> panel): 8B gate+up W4 fp16 M = 64 / 96 / 128 33.0 / 54.3 / 65.0 ->
+// Calls of 33 rows or more without a plan: one pass over the weights measured faster than slices of 32 or 64 rows, but for one
+// row-streaming launch of up to 64 rows (panel_plan) (us, HBM-cold weights, MI355X, slices -> panel): 8B gate+up W4 fp16 M = 64 / 96 / 128 33.0 / 54.3 / 65.0 ->
 // 25.2 / 36 / 40.2, O 14.6 / 25.2 / 28.8 -> 11.8 / 13.5 / 13.5, down 33.9 / 51.0 / 66.3 -> 19.9 / 27.7 / 27.9, 1024 x 4096 18.6 /
 // 27.8 / 36.7 -> 8.8 / 8.9 / 8.9, 70B gate+up 104 / 163 / 205 -> 93 / 124 / 148; W3 bf16 8B down 37.3 / 55.3 / 73.2 -> 21.5 / 27.3 /
 // 32.8, 70B O 36.6 / 54.9 / 73.3 -> 23.2 / 29.9 / 33.8.
@@ -1374,8 +1374,9 @@ struct PanelDecomp {
 // the chip is full, and with K slices the exchange of partial sums.  Parts of M fill the chip where the matrix is small, without
 // that exchange (8B O M = 128: 4 K slices 18.5, 4 parts of M 13.5; 1024 x 4096 14.0 -> 9.1); a large one is faster in one.  The constants
 // are fitted per bit width to 1260 measurements in all (fourteen shapes from 1024 x 4096 to 28672 x 4096, M = 64, 96, 128); the
-// choice is within 0.6 % of the fastest plan measured on average, 7 % at worst.  (3 bits, 64 channels by 128 rows: no instance,
-// the registers spill.)
+// choice was within 0.6 % of the fastest plan measured on average, 7 % at worst.  With the shorter prefetch that 33..64 rows at 4 bits
+// have since (panel_depth), eighteen shapes at M = 64: within 0.7 % and 2.5 % in fp16, 0.8 % and 7.7 % (8B QKV) in bf16.  (3 bits, 64
+// channels by 128 rows: no instance, the registers spill.)
 // `room`: bytes of scratch for the slices' partial sums.
 bool panel_decomp(int bits, int64_t M, int64_t N, int64_t K, int cus, size_t room, PanelDecomp* out) {
     if (M <= 32 || M > 128 || M * K * 2 >= (int64_t)1 << 31) return false;
@@ -1415,6 +1416,40 @@ bool panel_decomp(int bits, int64_t M, int64_t N, int64_t K, int cus, size_t roo
     return true;
 }
 
+// Estimated us of the two launches that a call of 33..64 rows at 4 bits can take: each a sum of a fixed part, parts per K tile
+// and per row block or panel of the busiest compute unit, and one per megabyte of weights, fitted per type (and to 48 or 64 rows, or to
+// the panel launch's shape) to 1352 pairs of measurements: 340 shapes from 4096 to 57344 channels and K = 1024 to 28672, groups of 32 to 256.
+// The estimates are 2.4 % (row streaming) and 4.3 % off, the choice costs 0.2 % against the better launch on average, 8 % at worst
+// (fitted to the first 782 pairs and tried on the others: 0.4 %, 9 %).
+// Both, us, row streaming / panel: fp16 M = 40 8B gate+up 29.2 / 24.6, 70B QKV 24.1 / 24.2, 12288 x 4096 15.9 / 17.1, 32768 x 8192 52.4 /
+// 46.9, 40960 x 5120 48.9 / 53.8, M = 64 57.2 / 57.5; bf16 M = 40 5120 x 5120 16.3 / 14.0, 8B QKV 14.5 / 15.6, 70B down 60.3 / 50.9,
+// 12288 x 12288 34.5 / 42.2 (M = 64 40.0 / 42.7), 8B gate+up 29.7 / 29.0, 70B gate+up 91.8 / 105 (M = 64 106 / 109), 40960 x 5120 49.9 /
+// 65.1 (a panel launch's last round leaves most of the chip idle there).
+double wide_rows_us(bool bf16, int64_t M, int64_t N, int64_t K, int cus) {
+    // fixed; per K tile, per K tile and pass of four row blocks, per K tile and row block; per MB; per pass, per row block
+    static const double fits[2][2][7] = {{{4.214, 0.0170, 0.1426, 0.0224, 0.0613, 2.035, 0.543},        // fp16, 48 rows
+                                          {4.095, 0.0331, 0.1698, 0.0204, 0.0859, 2.638, 0.483}},
+                                         {{4.040, 0.0157, 0.1433, 0.0203, 0.0733, 2.188, 0.613},        // bf16
+                                          {4.384, 0.0246, 0.1865, 0.0173, 0.0846, 1.866, 0.790}}};
+    const double* f = fits[bf16][M > 48];
+    const double kt = (double)(K / 128), blocks = (double)((N / 16 + cus - 1) / cus), passes = (double)((N / 16 + 4 * (int64_t)cus - 1) / (4 * (int64_t)cus));
+    return f[0] + kt * (f[1] + f[2] * passes + f[3] * blocks) + f[4] * (double)N * (double)K * 5e-7 + f[5] * passes + f[6] * blocks;
+}
+double panel_us_w4(bool bf16, int64_t N, int64_t K, int cus, const PanelDecomp& d) {
+    // per round; per round and K tile of a wavefront; K slices: fixed, times the filled part of the chip, per slice; per MB
+    static const double fits[2][3][6] = {{{4.318, 0.999, 0.000, 0.000, 1.141, 0.1078},                  // fp16: 32 rows, 64 channels
+                                          {4.642, 1.097, 2.125, 0.000, 0.198, 0.1385},                  // 64 rows
+                                          {4.970, 1.655, 0.000, 4.003, 0.459, 0.1107}},                 // 64 rows, 128 channels
+                                         {{4.608, 1.089, 0.000, 0.000, 0.825, 0.1603},
+                                          {4.441, 1.201, 1.673, 0.329, 0.385, 0.1583},
+                                          {4.917, 2.102, 0.000, 4.059, 0.318, 0.1116}}};
+    const double* f = fits[bf16][d.rp == 2 ? 2 : d.mb == 1 ? 0 : 1];
+    const int64_t grid = d.shares * d.ks * d.ms, rounds = (grid + cus - 1) / cus;
+    const int64_t tiles = ((K / 128 + d.ks - 1) / d.ks + kPanelWK - 1) / kPanelWK;
+    return (double)rounds * (f[0] + f[1] * (double)tiles) + f[5] * (double)N * (double)K * 5e-7 +
+           (d.ks > 1 ? f[2] + f[3] * (double)grid / (double)(rounds * cus) + f[4] * d.ks : 0.);
+}
+
 bool plan_is_zero(const lutq_plan& p) {
     return !(p.scheduling || p.row_blocks_per_wave || p.grid || p.waves_per_workgroup || p.tiles_in_flight || p.row_groups_per_workgroup ||
              p.tiles_per_item);
@@ -1432,28 +1467,21 @@ bool registered_plan_runs(int bits, int group_size, int64_t M, int64_t N, int64_
                           &registered, false, cus, &q, true) == LUTQ_OK;
 }
 
-// Whether a call of M > 32 rows goes to the panel kernel: no plan from the caller, none registered that serves it, and not one of
-// the cases where the row-streaming kernel is faster.
+// Whether a call of M > 32 rows goes to the panel kernel: no plan from the caller, none registered that serves it, and no
+// row-streaming launch that is the faster.
 bool panel_plan(int bits, int group_size, int64_t M, int64_t N, int64_t K, lutq_dtype dtype, const lutq_plan* user_plan, int cus,
                 size_t workspace_bytes, PanelDecomp* out) {
     if (user_plan ? !plan_is_zero(*user_plan) : registered_plan_runs(bits, group_size, M, N, K, dtype, cus, workspace_bytes)) return false;
-    // Where one row-streaming launch (4 bits, up to 64 rows, blocks of sixteen) stays the faster: up to 48 rows, three such blocks,
-    // in bf16 with more than one row block per compute unit and K up to 8192 (us, row streaming against panel, M = 40: 8B QKV
-    // 14.5 / 15.6, 70B QKV 24.1 / 27.1, 70B O 21.8 / 22.3, 8B gate+up 29.1 / 29.6, 70B gate+up 89 / 103; a longer K, 70B down, 59.7 /
-    // 52.5), in fp16 with eight row blocks per compute unit (70B gate+up 86 / 89) or two to three (70B QKV 23.6 / 24.2; elsewhere 5
-    // to 20 % slower); up to 64 rows in bf16 with eight or more (70B gate+up 103 / 107).
-    // (only where that launch exists and its copy of the activations fits the scratch: with scale rows too long for LDS the call would
-    // go in slices of 32 rows instead, 10240 x 28672 group 32 fp16 M = 40 102 us against 59)
-    const int64_t nb = N / 16;
-    const bool bf16 = dtype == LUTQ_BF16;
     const size_t room = workspace_bytes > kCounterBytes ? workspace_bytes - kCounterBytes : 0;
+    if (!panel_decomp(bits, M, N, K, cus, room, out)) return false;
+    // 4 bits, up to 64 rows: one row-streaming launch is the alternative, where it exists and its copy of the activations fits the
+    // scratch (with scale rows too long for its LDS the call would go in slices of 32 rows instead, 10240 x 28672 group 32 fp16
+    // M = 40 102 us against 59); by estimate the faster of the two.
+    const bool bf16 = dtype == LUTQ_BF16;
     Decomp rows;
     bool take = false;
-    if (bits == 4 && M <= 64 && wide_rows_decomp(bits, bf16, M, N, K, group_size, cus, &rows, &take) && take && xop_bytes(M, K) <= room &&
-        (M <= 48 ? (bf16 ? nb > cus && K <= 8192 : nb >= 8 * (int64_t)cus || (nb > 2 * (int64_t)cus && nb <= 3 * (int64_t)cus))
-                 : bf16 && nb >= 8 * (int64_t)cus))
-        return false;
-    return panel_decomp(bits, M, N, K, cus, room, out);
+    return !(bits == 4 && M <= 64 && wide_rows_decomp(bits, bf16, M, N, K, group_size, cus, &rows, &take) && take &&
+             xop_bytes(M, K) <= room && wide_rows_us(bf16, M, N, K, cus) <= panel_us_w4(bf16, N, K, cus, *out));
 }
 
 lutq_status launch_panel(const void* X, const void* packed, const void* scales, const void* lut, int bits, int group_size,

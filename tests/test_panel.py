@@ -250,3 +250,22 @@ def test_row_streaming_keeps_a_call_only_where_its_launch_exists(lutq):
     for M in (33, 48):
         K = 180224                                   # 16.5 MiB and more of activations
         assert lutq.calib_route(4, 64, M, 10240, K, 0, 256, lutq.STATIC_SCRATCH_BYTES)[0] == 0
+
+
+# (type, M, N, K, row streaming us, panel us), group 128, HBM-cold weights: pairs that differ by 8 % and more
+MEASURED_W4 = [
+    ("f16", 40, 4096, 4096, 13.0, 11.7), ("f16", 48, 5120, 5120, 16.3, 13.4), ("f16", 33, 6144, 4096, 14.6, 13.5),
+    ("f16", 64, 8192, 8192, 25.7, 21.6), ("f16", 64, 10240, 8192, 28.7, 25.2), ("f16", 40, 10240, 16384, 41.9, 37.4),
+    ("f16", 48, 12288, 4096, 16.0, 17.5), ("f16", 64, 20480, 8192, 47.5, 41.5), ("f16", 48, 27648, 5120, 35.4, 30.4),
+    ("f16", 40, 28672, 4096, 29.2, 24.6), ("f16", 33, 32768, 8192, 52.8, 47.9), ("f16", 48, 40960, 5120, 49.6, 55.7),
+    ("f16", 64, 57344, 8192, 104.9, 94.2), ("bf16", 64, 4096, 4096, 15.5, 12.8), ("bf16", 33, 5120, 5120, 16.2, 13.9),
+    ("bf16", 64, 6144, 4096, 17.6, 15.8), ("bf16", 48, 8192, 28672, 60.6, 53.2), ("bf16", 48, 10240, 8192, 24.8, 27.1),
+    ("bf16", 40, 12288, 4096, 16.1, 18.8), ("bf16", 33, 12288, 12288, 34.6, 42.2), ("bf16", 48, 12288, 12288, 34.5, 42.5),
+    ("bf16", 48, 16384, 6144, 24.7, 27.3), ("bf16", 40, 20480, 8192, 42.0, 48.9), ("bf16", 64, 28672, 4096, 34.8, 30.0),
+    ("bf16", 33, 40960, 5120, 49.2, 63.5), ("bf16", 64, 40960, 5120, 58.3, 67.7), ("bf16", 40, 57344, 8192, 91.8, 105.2)]
+
+
+def test_33_to_64_rows_at_4_bits_take_the_faster_launch(lutq):
+    for dtype, M, N, K, rows_us, panel_us in MEASURED_W4:
+        r = lutq.calib_route(4, 128, M, N, K, 0 if dtype == "f16" else 1)
+        assert (r[0] == 0) == (panel_us < rows_us), (dtype, M, N, K, r)
