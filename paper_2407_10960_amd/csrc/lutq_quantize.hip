@@ -34,6 +34,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <type_traits>
 
 #include "lutq.h"
 #include "lutq_layout.hpp"
@@ -203,22 +204,21 @@ __global__ __launch_bounds__(64 * kQuantWaves) void quantize_kernel(const QuantP
 #pragma unroll
             for (int g = 0; g < NG; ++g) dst[g] = (uint16_t)sbits[g];
         }
-        // indices of this lane, step by step, packed as they are found
-        uint32_t idx[NSTEP];                          // 8 indices of step t, 4 bits apart
-#pragma unroll
-        for (int t = 0; t < NSTEP; ++t) {
+        // the 8 indices of step t of this lane, 4 bits apart; `limited`: cells outside the table, and NaN, become one inside it
+        auto step_indices = [&](int t, auto limited) -> uint32_t {
             const float sg = s[t / SPG];
             // a scale that is zero makes u = 0; one that is not an ordinary number (fp16 subnormals are up to half off the
             // absmax) sends the group through the fp64 rule
-            const bool ordinary = sg >= (bf16 ? 0x1p-100f : 0x1p-14f) && sg <= 0x1p+100f;
+            const bool ordinary = decltype(limited)::value ? sg >= (bf16 ? 0x1p-100f : 0x1p-14f) && sg <= 0x1p+100f : sg != 0.f;
             const float inv = ordinary ? __builtin_amdgcn_rcpf(sg) : 0.f;
-            const float near = ordinary || sg == 0.f ? kNear : __builtin_inff();
+            const float near = !decltype(limited)::value || ordinary || sg == 0.f ? kNear : __builtin_inff();
             const float to_cell = inv * kCellScale;
             uint32_t word = 0, open = 0;              // open: bit 7 - j set where weight j is not decided
             uint32_t ent[8];
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
-                const float cell = __builtin_fmaf(weight(t, j), to_cell, 0x1p+23f + 256.f);
+                float cell = __builtin_fmaf(weight(t, j), to_cell, 0x1p+23f + 256.f);
+                if constexpr (decltype(limited)::value) cell = __builtin_amdgcn_fmed3f(cell, 0x1p+23f, 0x1p+23f + (kCells - 1));
                 ent[j] = *reinterpret_cast<lds_cu32*>((uintptr_t)((__builtin_bit_cast(uint32_t, cell) << 7) + cell_lane + cells));
             }
 #pragma unroll
@@ -252,7 +252,25 @@ __global__ __launch_bounds__(64 * kQuantWaves) void quantize_kernel(const QuantP
                 const double u = sg == 0.f ? 0.0 : (double)w / (double)sg;
                 word = (word & ~(15u << (4 * j))) | (nearest_entry<E>(u, Ts) << (4 * j));
             }
-            idx[t] = word;
+            return word;
+        };
+        // The cell of a weight is an LDS address, and only a group whose scale is zero or an ordinary number is sure to keep it inside
+        // the table (a weight that is not finite makes its group's scale one that is not, or a zero with a sign): any other takes the
+        // limits, in a copy of the code, since they cost 1 to 3 % of a call.
+        uint32_t most = 0, least = 0xffffffffu;       // (of the scales' patterns; a zero counts as the largest for the least)
+#pragma unroll
+        for (int g = 0; g < NG; ++g) {
+            most = sbits[g] > most ? sbits[g] : most;
+            least = sbits[g] - 1u < least ? sbits[g] - 1u : least;
+        }
+        const bool odd = most > (bf16 ? 0x7180u : 0x7bffu) || least < (bf16 ? 0x0d80u : 0x0400u) - 1u;
+        uint32_t idx[NSTEP];
+        if (__ballot(odd) == 0) {
+#pragma unroll
+            for (int t = 0; t < NSTEP; ++t) idx[t] = step_indices(t, std::false_type{});
+        } else {
+#pragma unroll
+            for (int t = 0; t < NSTEP; ++t) idx[t] = step_indices(t, std::true_type{});
         }
         // packed tiles of the unit
 #pragma unroll

@@ -89,3 +89,35 @@ def test_quantize_more_units_than_wavefronts(lutq):
         rows = np.unique(np.concatenate([np.arange(min(N, 16)), np.arange(N - 16, N), rng.choice(N, 32)]))
         Q, S = orc.quantize(W[rows].astype(np.float64), T, group, "f16")
         assert np.array_equal(got[rows], Q) and np.array_equal(to_bits(S_out)[rows], S), (N, K, group)
+
+
+@pytest.mark.parametrize("bits", (2, 3, 4))
+@pytest.mark.parametrize("dtype", ("f16", "bf16"))
+@pytest.mark.parametrize("w16", (False, True))
+def test_quantize_weights_that_are_not_finite(lutq, bits, dtype, w16):
+    """Weights are to be finite; one that is not spoils its own group and nothing else, and looks nothing up outside the table of
+    cells (whose addresses are formed from the weights)."""
+    import torch
+    rng = np.random.default_rng(20 + bits)
+    N, K, group = 48, 2048, 32 if w16 else 64
+    T = gen.encode16(gen.normal_float_table(bits), dtype)
+    W = (rng.standard_normal((N, K)) * 0.02).astype(np.float32)
+    clean = np.ones((N, K // group), dtype=bool)
+    for r, v in ((0, np.inf), (1, -np.inf), (2, np.nan), (17, np.inf), (18, -np.nan), (40, np.nan)):
+        c = rng.integers(0, K, 5)
+        W[r, c] = v
+        clean[r, c // group] = False
+    if not w16:
+        W[3, 100:102] = np.array([0x7fffffff, 0xffffffff], dtype=np.uint32).view(np.float32)      # rounds past the last NaN to a zero
+        clean[3, 100 // group] = False
+    Wt = torch.from_numpy(W).cuda()
+    Wd = Wt.to(torch_dtype(dtype)) if w16 else Wt
+    W64 = np.where(np.isfinite(W), Wd.double().cpu().numpy(), 0.0)
+    Q, S = orc.quantize(W64, T, group, dtype)
+    S_out = torch.zeros((N, K // group), dtype=torch_dtype(dtype), device="cuda")
+    P_out = torch.zeros(lutq.lutq_packed_bytes(N, K, bits, group), dtype=torch.uint8, device="cuda")
+    lutq.lutq_quantize(Wd, to_dev(T, dtype), bits, group, S_out, P_out)
+    got = lutq.lutq_unpack(P_out.cpu().numpy(), N, K, bits, group)
+    full = np.repeat(clean, group, axis=1)
+    assert np.array_equal(to_bits(S_out)[clean], S[clean])
+    assert np.array_equal(got[full], Q[full])
