@@ -14,17 +14,22 @@
 // value; a cell without one has a threshold that no u reaches).  A weight takes u32 = w * rcp(scale) in fp32, one table read and
 // one comparison.  u32, the threshold (whose low eight mantissa bits hold the two indices: off by at most 2^-17 below 1) and
 // their difference are off by less than kNear together, so a weight whose u32 is kNear or further from its cell's threshold is
-// decided as the fp64 rule decides it.  The others -- about one in eight thousand with a NormalFloat table of 16 entries --, cells
-// with more than one threshold, and groups whose scale is not a normal number of ordinary size go through the fp64 rule itself, lane by lane.
+// decided as the fp64 rule decides it.  The others -- about one in eight thousand with a NormalFloat table of 16 entries -- and cells
+// with more than one threshold go through the fp64 rule itself, lane by lane.  With subnormal fp16 scales |u| is up to 1.5, which the
+// first and the last cell take in; groups with a bf16 scale beyond 2^-100 or 2^100 go through the fp64 rule.
 // That the decision away from thresholds is the nearest entry by value, and the lowest of equal entries, needs that rounding
-// never reorders the smallest distances: with one entry of magnitude up to 1000 the smallest distance is below 1002, an entry
-// beyond 2100 in magnitude is never nearest, the others' distances are below 2^12 and round by less than 2^-41, and different ones
-// among them have to be 2^-40 or more apart; any other table has no thresholds and every weight goes through the fp64 rule.
+// never reorders the distances there.  fp16 entries: distances are below 2^17 and round by less than 2^-36, and two of them that differ by
+// as little are those of a weight within 2^-36 of a threshold.  bf16: with one entry of magnitude up to 1000 the smallest distance is below
+// 1002, an entry beyond 2100 in magnitude is never nearest, the others' distances are below 2^12 and round by less than 2^-41, and different
+// ones among them have to be 2^-40 or more apart; any other table has no thresholds and every weight goes through the fp64 rule.
 //
 // What bounds it: the memory traffic, with the vector unit close behind (twelve instructions a weight).  The table is built
 // per workgroup, so workgroups are few (two per compute unit) and large (eight wavefronts), each walking many units.
 // 8192 x 28672 bf16 to 4 bits, group 64: 129 us, 4.6 TB/s (658 us with an fp64 division and a scan of the sixteen entries per
-// weight); 28672 x 4096 fp32 to 4 bits fp16 189 -> 117 us, fp16 200 -> 62; 1024 x 4096 bf16 17.7 -> 8.8.
+// weight); 28672 x 4096 fp32 to 4 bits fp16 189 -> 112 us, fp16 200 -> 61; 1024 x 4096 bf16 17.7 -> 9.1.
+// Where the cells decide less (8192 x 8192 fp32 to 4 bits, us, with the fp64 division and -- sorted fp16 tables -- a binary search -> now):
+// subnormal or infinite fp16 scales 113 -> 64, an fp16 table with all but two entries within some 1e-3 of zero 113 -> 80, bf16 scales below 2^-100
+// 193 -> 222, a bf16 table without an entry below 1000 or with entries closer than 2^-40 193 -> 218 (2 bits 87 -> 88).
 //
 // Work unit: 16 rows x UC columns, UC = max(K tile, group), one wavefront per unit.  Lane l = 16 o + i
 // holds, for every 32-column step t of the unit, the 8 weights W[16 rb + i][col0 + 32 t + 8 o + j] --
@@ -98,7 +103,9 @@ template <int E>
 __device__ __forceinline__ uint32_t cell_entry(int cell, const double* T) {
     // (the margin covers how far u is from the value the cell was chosen with)
     const double centre = (double)(cell - 256) / (double)kCellScale, half = 0.5 / (double)kCellScale + 2e-5;
-    const uint32_t below = nearest_entry<E>(centre - half, T), above = nearest_entry<E>(centre + half, T);
+    // (the first and the last cell are also those of the weights beyond the cells: |u| is up to 1.5 with the smallest fp16 scales)
+    const uint32_t below = nearest_entry<E>(cell == 0 ? -2.0 : centre - half, T);
+    const uint32_t above = nearest_entry<E>(cell == kCells - 1 ? 2.0 : centre + half, T);
     const uint32_t code = below | (above << 4);
     if (below == above) return 0x7f000000u | code;
     const double mid = 0.5 * (T[below] + T[above]);
@@ -135,7 +142,7 @@ __global__ __launch_bounds__(64 * kQuantWaves) void quantize_kernel(const QuantP
         small = __builtin_fabs(a) <= 1000.0;
         close = __builtin_fabs(a) <= 2100.0 && __builtin_fabs(b) <= 2100.0 && a != b && __builtin_fabs(a - b) < 0x1p-40;
     }
-    const bool thresholds = __syncthreads_or(close) == 0 && __syncthreads_or(small) != 0;
+    const bool thresholds = __syncthreads_or(close) == 0 && (__syncthreads_or(small) != 0 || !bf16);
     for (int cell = threadIdx.x; cell < kCells; cell += 64 * kQuantWaves) {
         const uint32_t v = thresholds ? cell_entry<E>(cell, Ts) : 0x7fc00000u;
 #pragma unroll 1
@@ -204,14 +211,35 @@ __global__ __launch_bounds__(64 * kQuantWaves) void quantize_kernel(const QuantP
 #pragma unroll
             for (int g = 0; g < NG; ++g) dst[g] = (uint16_t)sbits[g];
         }
+        double T[E];                                  // the table in scalar registers (odd units only)
+        // the 8 indices of step t of this lane, 4 bits apart, by the fp64 rule alone
+        auto step_by_rule = [&](int t) -> uint32_t {
+            const float sg = s[t / SPG];
+            uint32_t word = 0;
+#pragma unroll 1
+            for (int half = 0; half < 2; ++half) {
+                uint32_t part = 0;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const float w = half ? weight(t, 4 + j) : weight(t, j);
+                    const double u = sg == 0.f ? 0.0 : (double)w / (double)sg;
+                    part |= nearest_entry<E>(u, T) << (4 * j);
+                }
+                word |= part << (16 * half);
+            }
+            return word;
+        };
         // the 8 indices of step t of this lane, 4 bits apart; `limited`: cells outside the table, and NaN, become one inside it
         auto step_indices = [&](int t, auto limited) -> uint32_t {
             const float sg = s[t / SPG];
-            // a scale that is zero makes u = 0; one that is not an ordinary number (fp16 subnormals are up to half off the
-            // absmax) sends the group through the fp64 rule
-            const bool ordinary = decltype(limited)::value ? sg >= (bf16 ? 0x1p-100f : 0x1p-14f) && sg <= 0x1p+100f : sg != 0.f;
+            // a scale that is zero or infinite makes u = 0 (of a finite weight)
+            const bool ordinary = decltype(limited)::value ? sg >= (bf16 ? 0x1p-100f : 0x1p-24f) && sg <= 0x1p+100f : sg != 0.f;
             const float inv = ordinary ? __builtin_amdgcn_rcpf(sg) : 0.f;
-            const float near = !decltype(limited)::value || ordinary || sg == 0.f ? kNear : __builtin_inff();
+            float near = kNear;
+            if constexpr (decltype(limited)::value) {
+                if (!ordinary && sg != 0.f && sg != __builtin_inff()) near = __builtin_inff();
+                if (!thresholds || __ballot(near != kNear) != 0) return step_by_rule(t);
+            }
             const float to_cell = inv * kCellScale;
             uint32_t word = 0, open = 0;              // open: bit 7 - j set where weight j is not decided
             uint32_t ent[8];
@@ -250,7 +278,10 @@ __global__ __launch_bounds__(64 * kQuantWaves) void quantize_kernel(const QuantP
                     w = widen16((j & 1) ? v >> 16 : v & 0xffffu, WT == 2);
                 }
                 const double u = sg == 0.f ? 0.0 : (double)w / (double)sg;
-                word = (word & ~(15u << (4 * j))) | (nearest_entry<E>(u, Ts) << (4 * j));
+                uint32_t at;
+                if constexpr (decltype(limited)::value) at = nearest_entry<E>(u, T);
+                else at = nearest_entry<E>(u, Ts);
+                word = (word & ~(15u << (4 * j))) | (at << (4 * j));
             }
             return word;
         };
@@ -263,12 +294,17 @@ __global__ __launch_bounds__(64 * kQuantWaves) void quantize_kernel(const QuantP
             most = sbits[g] > most ? sbits[g] : most;
             least = sbits[g] - 1u < least ? sbits[g] - 1u : least;
         }
-        const bool odd = most > (bf16 ? 0x7180u : 0x7bffu) || least < (bf16 ? 0x0d80u : 0x0400u) - 1u;
+        const bool odd = !thresholds || most > (bf16 ? 0x7180u : 0x7bffu) || least < (bf16 ? 0x0d80u : 0x0400u) - 1u;
         uint32_t idx[NSTEP];
         if (__ballot(odd) == 0) {
 #pragma unroll
             for (int t = 0; t < NSTEP; ++t) idx[t] = step_indices(t, std::false_type{});
         } else {
+#pragma unroll
+    for (int c = 0; c < E; ++c) {
+        const u32x2 v = *reinterpret_cast<const u32x2*>(Ts + c);
+        T[c] = __builtin_bit_cast(double, u32x2{(uint32_t)__builtin_amdgcn_readfirstlane((int)v.x), (uint32_t)__builtin_amdgcn_readfirstlane((int)v.y)});
+    }
 #pragma unroll
             for (int t = 0; t < NSTEP; ++t) idx[t] = step_indices(t, std::true_type{});
         }

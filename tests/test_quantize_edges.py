@@ -121,3 +121,38 @@ def test_quantize_weights_that_are_not_finite(lutq, bits, dtype, w16):
     full = np.repeat(clean, group, axis=1)
     assert np.array_equal(to_bits(S_out)[clean], S[clean])
     assert np.array_equal(got[full], Q[full])
+
+
+@pytest.mark.parametrize("bits", (2, 3, 4))
+@pytest.mark.parametrize("dtype", ("f16", "bf16"))
+def test_quantize_beyond_the_cells(lutq, bits, dtype):
+    """Whole matrices of the smallest scales, where |u| is up to 1.5 (fp16), of infinite ones and of those beyond 2^-100 and 2^100
+    (bf16), and a mixture; tables without an entry below 1000, with entries that cancel, and with thresholds above 1."""
+    import torch
+    rng = np.random.default_rng(40 + bits)
+    N, K, group, E = 32, 1024, 64, 1 << bits
+    asc = np.sort(rng.standard_normal(E))
+    tables = {"nf": gen.normal_float_table(bits), "far": np.linspace(1100, 2000, E), "opposite": np.linspace(-60000, 60000, E),
+              "far shuffled": rng.permutation(np.linspace(-9000, 30000, E)), "wide": asc / np.abs(asc).max() * 1.9, "near": asc * 1e-3}
+    tiny = 2.0 ** -24
+    matrices = {"least": rng.uniform(-1.49, 1.49, (N, K)) * tiny, "two": rng.uniform(-2.49, 2.49, (N, K)) * tiny,
+                "subnormal": rng.standard_normal((N, K)) * 1e-5, "infinite": rng.standard_normal((N, K)) * 1e6,
+                "small": rng.standard_normal((N, K)) * 2.0 ** -106, "large": rng.standard_normal((N, K)) * 2.0 ** 106}
+    mixed = rng.standard_normal((N, K)) * 0.02
+    for i, m in enumerate(matrices.values()):
+        mixed[3 * i] = m[0]
+        mixed[3 * i + 1, group:2 * group] = m[1, :group]
+    matrices["mixed"] = mixed
+    for tname, T64 in tables.items():
+        T = gen.encode16(np.asarray(T64), dtype)
+        for mname, W64 in matrices.items():
+            W = W64.astype(np.float32)
+            with np.errstate(over="ignore"):
+                Q, S = orc.quantize(W.astype(np.float64), T, group, dtype)
+            S_out = torch.zeros((N, K // group), dtype=torch_dtype(dtype), device="cuda")
+            P_out = torch.zeros(lutq.lutq_packed_bytes(N, K, bits, group), dtype=torch.uint8, device="cuda")
+            lutq.lutq_quantize(torch.from_numpy(W).cuda(), to_dev(T, dtype), bits, group, S_out, P_out)
+            what = f"b{bits} {dtype} {tname} {mname}"
+            assert np.array_equal(to_bits(S_out), S), what
+            got = lutq.lutq_unpack(P_out.cpu().numpy(), N, K, bits, group)
+            assert np.array_equal(got, Q), f"{what}: {np.count_nonzero(got != Q)} indices differ"
