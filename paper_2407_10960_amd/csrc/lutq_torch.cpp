@@ -72,10 +72,21 @@ bool shape_is(const at::Tensor& t, int64_t a, int64_t b) { return t.dim() == 2 &
 
 void* current_stream() { return static_cast<void*>(c10::hip::getCurrentHIPStream().stream()); }
 
+// A torch call that throws (a nested tensor asked for an irregular size, storage that may not be read, no device) makes the call one
+// that is not plain: no exception leaves through the C entry, and the binding's own code meets the same refusal and raises it.
+template <typename F> PyObject* answer(F f) {
+    try { return f(); } catch (...) { return PyLong_FromLong(-1); }
+}
+
+struct WithoutGil {
+    PyThreadState* state = PyEval_SaveThread();
+    ~WithoutGil() { PyEval_RestoreThread(state); }
+};
+
 enum Kind { kMatmul = 0, kStatic = 1, kChannel = 2, kPairs = 3, kQuads = 4 };
 
 // (kind, X, packed, scales, lut, bits, group_size, Y, workspace or None) -> status, or -1
-PyObject* mm(PyObject*, PyObject* const* args, Py_ssize_t n) {
+PyObject* mm(PyObject*, PyObject* const* args, Py_ssize_t n) { return answer([&]() -> PyObject* {
     int kind, bits, group;
     if (!matmul || n != 9 || !small_int(args[0], 0, 4, &kind) || !small_int(args[5], 2, 4, &bits) || !small_int(args[6], 1, 1 << 16, &group))
         return PyLong_FromLong(-1);
@@ -97,20 +108,21 @@ PyObject* mm(PyObject*, PyObject* const* args, Py_ssize_t n) {
     const size_t wb = ws ? (size_t)ws->numel() * ws->element_size() : 0;
     const lutq_dtype dt = (lutq_dtype)code;
     lutq_status st = LUTQ_OK;
-    Py_BEGIN_ALLOW_THREADS
-    switch (kind) {
-        case kMatmul: st = matmul(x, p, s, l, bits, group, M, N, K, dt, y, w, wb, stream); break;
-        case kStatic: st = matmul_static(x, p, s, l, bits, group, M, N, K, dt, y, stream, nullptr); break;
-        case kChannel: st = matmul_channel(x, p, s, l, bits, group, M, N, K, dt, y, w, wb, stream); break;
-        case kPairs: st = matmul_pairs(x, p, s, l, group, M, N, K, dt, y, w, wb, stream); break;
-        case kQuads: st = matmul_quads(x, p, s, l, group, M, N, K, dt, y, w, wb, stream); break;
+    {
+        WithoutGil released;
+        switch (kind) {
+            case kMatmul: st = matmul(x, p, s, l, bits, group, M, N, K, dt, y, w, wb, stream); break;
+            case kStatic: st = matmul_static(x, p, s, l, bits, group, M, N, K, dt, y, stream, nullptr); break;
+            case kChannel: st = matmul_channel(x, p, s, l, bits, group, M, N, K, dt, y, w, wb, stream); break;
+            case kPairs: st = matmul_pairs(x, p, s, l, group, M, N, K, dt, y, w, wb, stream); break;
+            case kQuads: st = matmul_quads(x, p, s, l, group, M, N, K, dt, y, w, wb, stream); break;
+        }
     }
-    Py_END_ALLOW_THREADS
     return PyLong_FromLong((long)st);
-}
+}); }
 
 // (W, lut, bits, group_size, scales_out, packed_out) -> status, or -1
-PyObject* quant(PyObject*, PyObject* const* args, Py_ssize_t n) {
+PyObject* quant(PyObject*, PyObject* const* args, Py_ssize_t n) { return answer([&]() -> PyObject* {
     int bits, group;
     if (!quantize || n != 6 || !small_int(args[2], 2, 4, &bits) || !small_int(args[3], 1, 1 << 16, &group)) return PyLong_FromLong(-1);
     const at::Tensor *W = plain(args[0]), *lut = plain(args[1]), *scales = plain(args[4]), *packed = plain(args[5]);
@@ -125,14 +137,15 @@ PyObject* quant(PyObject*, PyObject* const* args, Py_ssize_t n) {
     const void *w = W->data_ptr(), *l = lut->data_ptr();
     void *s = scales->data_ptr(), *p = packed->data_ptr(), *stream = current_stream();
     lutq_status st;
-    Py_BEGIN_ALLOW_THREADS
-    st = quantize(w, f32 ? 1 : 0, l, bits, group, N, K, (lutq_dtype)code, s, p, stream);
-    Py_END_ALLOW_THREADS
+    {
+        WithoutGil released;
+        st = quantize(w, f32 ? 1 : 0, l, bits, group, N, K, (lutq_dtype)code, s, p, stream);
+    }
     return PyLong_FromLong((long)st);
-}
+}); }
 
 // (packed, scales, lut, bits, group_size, W_out) -> status, or -1
-PyObject* dequantise(PyObject*, PyObject* const* args, Py_ssize_t n) {
+PyObject* dequantise(PyObject*, PyObject* const* args, Py_ssize_t n) { return answer([&]() -> PyObject* {
     int bits, group;
     if (!dequant || n != 6 || !small_int(args[3], 2, 4, &bits) || !small_int(args[4], 1, 1 << 16, &group)) return PyLong_FromLong(-1);
     const at::Tensor *packed = plain(args[0]), *scales = plain(args[1]), *lut = plain(args[2]), *W = plain(args[5]);
@@ -146,11 +159,12 @@ PyObject* dequantise(PyObject*, PyObject* const* args, Py_ssize_t n) {
     const void *p = packed->data_ptr(), *s = scales->data_ptr(), *l = lut->data_ptr();
     void *w = W->data_ptr(), *stream = current_stream();
     lutq_status st;
-    Py_BEGIN_ALLOW_THREADS
-    st = dequant(p, s, l, bits, group, N, K, (lutq_dtype)code, w, stream);
-    Py_END_ALLOW_THREADS
+    {
+        WithoutGil released;
+        st = dequant(p, s, l, bits, group, N, K, (lutq_dtype)code, w, stream);
+    }
     return PyLong_FromLong((long)st);
-}
+}); }
 
 PyMethodDef methods[] = {
     {"bind", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(bind)), METH_FASTCALL, nullptr},

@@ -69,3 +69,30 @@ def test_refused_calls_are_refused_as_before(lutq):
     call(bits=np.int64(4))                                               # (an index type, not an int)
     torch.cuda.synchronize()
     assert not (Y == 7.0).all().item()
+
+
+@pytest.mark.gpu
+def test_torch_errors_become_python_errors(lutq):
+    """Sizes of a nested tensor throw inside torch: the call raises as the Python code does, and the process lives on."""
+    import torch
+    from gpu_util import DeviceCase, to_bits
+    c = gen.make_case(1, 2, 64, 1024, 4, 64, "f16", "nf")
+    d = DeviceCase(lutq, c)
+    want = to_bits(d.matmul(lutq))
+    nested = torch.nested.nested_tensor([torch.zeros(1024), torch.zeros(512)], dtype=torch.float16, device="cuda")
+    Y = torch.full((2, 64), 7.0, dtype=torch.float16, device="cuda")
+    W = torch.zeros((64, 1024), dtype=torch.float16, device="cuda")
+    S = torch.zeros_like(d.S)
+    for call in (lambda: lutq.lutq_matmul(nested, d.packed, d.S, d.T, 4, 64, Y, d.ws),
+                 lambda: lutq.lutq_matmul(d.X, d.packed, nested, d.T, 4, 64, Y, d.ws),
+                 lambda: lutq.lutq_matmul(d.X, d.packed, d.S, d.T, 4, 64, nested, d.ws),
+                 lambda: lutq.lutq_matmul_static(nested, d.packed, d.S, d.T, 4, 64, Y),
+                 lambda: lutq.lutq_quantize(nested, d.T, 4, 64, S, torch.zeros_like(d.packed)),
+                 lambda: lutq.lutq_quantize(W, d.T, 4, 64, nested, torch.zeros_like(d.packed)),
+                 lambda: lutq.lutq_dequant(d.packed, nested, d.T, 4, 64, W),
+                 lambda: lutq.lutq_dequant(d.packed, d.S, d.T, 4, 64, nested)):
+        with pytest.raises(RuntimeError):
+            call()
+    torch.cuda.synchronize()
+    assert (Y == 7.0).all().item() and not W.any().item() and not S.any().item()
+    assert np.array_equal(to_bits(d.matmul(lutq)), want)
