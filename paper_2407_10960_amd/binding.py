@@ -3,6 +3,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import warnings
 from dataclasses import dataclass
 
 import numpy as np
@@ -134,28 +135,36 @@ def load_library():
                                             ctypes.POINTER(_CPlan), vp, sz, ctypes.POINTER(ctypes.c_int)]
     lib.lutq_calib_route.restype = ci
     lib.lutq_calib_route.argtypes = [ci, ci, i64, i64, i64, ci, ci, sz, ctypes.POINTER(ctypes.c_int)]
-    _load_native(lib)
     _LIB = lib
     return lib
 
 
-def _load_native(lib):
-    """Loads the binding's native part and hands it the library's functions."""
-    global _NATIVE
-    path = os.path.join(_PKG_DIR, "_lutq_torch.so")
-    if not os.path.exists(path):
-        raise RuntimeError(f"{path} is missing: build it with `python -m paper_2407_10960_amd.build`")
-    from . import _lutq_torch as native
-    native.bind(*(ctypes.cast(getattr(lib, f), ctypes.c_void_p).value for f in
-                  ("lutq_packed_bytes", "lutq_matmul", "lutq_matmul_static", "lutq_matmul_channel", "lutq_matmul_pairs",
-                   "lutq_matmul_quads", "lutq_quantize", "lutq_dequant")))
-    _NATIVE = native
+class _NoNative:
+    """In place of the native part where it cannot be loaded: takes no call."""
+    mm = quantize = dequant = staticmethod(lambda *args: -1)
 
 
 def _native():
-    if _NATIVE is None:
-        load_library()
-    return _NATIVE
+    """The binding's native part with the library's functions in its hands.  It only saves host time: without it (not built,
+    or built for another torch) every call goes through the Python code below, to the same library."""
+    global _NATIVE
+    if _NATIVE is not None:
+        return _NATIVE
+    lib = load_library()
+    import torch
+    try:
+        from . import _lutq_torch as native
+        if native.built_for != torch.__version__:
+            raise ImportError(f"built for torch {native.built_for}, this is {torch.__version__}")
+        native.bind(*(ctypes.cast(getattr(lib, f), ctypes.c_void_p).value for f in
+                      ("lutq_packed_bytes", "lutq_matmul", "lutq_matmul_static", "lutq_matmul_channel", "lutq_matmul_pairs",
+                       "lutq_matmul_quads", "lutq_quantize", "lutq_dequant")))
+    except ImportError as e:
+        warnings.warn(f"calls take about 6 us more host time each: the binding's native part is not loaded ({e}); "
+                      "`python -m paper_2407_10960_amd.build` builds it", RuntimeWarning, stacklevel=3)
+        native = _NoNative
+    _NATIVE = native
+    return native
 
 
 def _done(code: int, what: str) -> bool:

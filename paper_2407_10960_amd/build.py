@@ -42,16 +42,22 @@ def _run(cmd):
     return out
 
 
-def _torch_binding() -> list:
-    """The command that compiles the binding's native part against the installed torch (host code only)."""
+def _torch_binding() -> list | None:
+    """The command that compiles the binding's native part against the installed torch (host code only); None where the
+    headers of Python or torch are not there (the binding does without it)."""
     import sysconfig
 
     import torch
     from torch.utils import cpp_extension
     lib = os.path.join(os.path.dirname(torch.__file__), "lib")
-    includes = [f"-isystem{d}" for d in (*cpp_extension.include_paths(device_type="cuda"), sysconfig.get_paths()["include"])]
+    dirs = [*cpp_extension.include_paths(device_type="cuda"), sysconfig.get_paths()["include"]]
+    for header in ("Python.h", "ATen/core/Tensor.h", "c10/hip/HIPStream.h"):
+        if not any(os.path.exists(os.path.join(d, header)) for d in dirs):
+            print(f"{header} not found: the binding's native part is not built")
+            return None
     return ["g++", "-O2", "-fPIC", "-shared", "-std=c++17", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
-            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", f"-I{INCLUDE}", *includes,
+            f'-DLUTQ_TORCH_VERSION="{torch.__version__}"',
+            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", f"-I{INCLUDE}", *(f"-isystem{d}" for d in dirs),
             os.path.join(CSRC, "lutq_torch.cpp"), "-o", TORCH_LIB_PATH, f"-L{lib}", "-ltorch_python", "-ltorch", "-ltorch_cpu",
             "-lc10", "-lc10_hip"]
 
@@ -78,7 +84,11 @@ def build(verbose: bool = False, jobs: int | None = None) -> str:
     objs.append(obj)
     steps.append(["g++", "-O3", "-fPIC", "-std=c++17", "-fopenmp", f"-I{INCLUDE}",
                   "-c", os.path.join(CSRC, "lutq_pack.cpp"), "-o", obj])
-    steps.insert(0, _torch_binding())
+    torch_binding = _torch_binding()
+    if torch_binding:
+        steps.insert(0, torch_binding)
+    elif os.path.exists(TORCH_LIB_PATH):
+        os.remove(TORCH_LIB_PATH)                      # (never an older one beside a new library)
     jobs = jobs or min(8, os.cpu_count() or 1)
     with concurrent.futures.ThreadPoolExecutor(max_workers=jobs) as ex:
         for out in ex.map(_run, steps):

@@ -177,4 +177,8 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_lutq_torch", nullptr, -1, methods
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__lutq_torch() { return PyModule_Create(&module); }
+PyMODINIT_FUNC PyInit__lutq_torch() {
+    PyObject* m = PyModule_Create(&module);
+    if (m && PyModule_AddStringConstant(m, "built_for", LUTQ_TORCH_VERSION) != 0) { Py_DECREF(m); return nullptr; }
+    return m;
+}

@@ -21,6 +21,44 @@ def test_native_part_answers_what_is_not_plain_with_minus_one(lutq):
         lutq.lutq_matmul(t, t, t, t, 4, 128, t, t)
 
 
+def test_everything_but_host_time_does_without_the_native_part(lutq, monkeypatch):
+    """Missing, or built for another torch: the library loads, host functions work without a word, and the first call that
+    would have used it warns and goes through the Python code."""
+    import sys
+    import torch
+    from paper_2407_10960_amd import binding
+    t = torch.zeros((1, 128), dtype=torch.float16)
+    built = binding._native()
+    for missing in (True, False):
+        monkeypatch.setattr(binding, "_LIB", None)
+        monkeypatch.setattr(binding, "_NATIVE", None)
+        if missing:
+            monkeypatch.delattr(lutq, "_lutq_torch", raising=False)
+            monkeypatch.setitem(sys.modules, "paper_2407_10960_amd._lutq_torch", None)
+        else:
+            monkeypatch.setitem(sys.modules, "paper_2407_10960_amd._lutq_torch", built)
+            monkeypatch.setattr(lutq, "_lutq_torch", built, raising=False)
+            monkeypatch.setattr(built, "built_for", "0.4.1")
+        Q = np.arange(16 * 256, dtype=np.uint8).reshape(16, 256) % 16
+        assert np.array_equal(lutq.lutq_unpack(lutq.lutq_pack(Q, 4, 64), 16, 256, 4, 64), Q)
+        assert lutq.lutq_plan_default_for(4, 128, 1, 4096, 4096).grid > 0 and binding._NATIVE is None
+        with pytest.warns(RuntimeWarning, match="native part"), pytest.raises(ValueError, match="CUDA"):
+            lutq.lutq_matmul(t, t, t, t, 4, 128, t, t)
+        assert binding._native() is binding._NoNative
+
+
+@pytest.mark.gpu
+def test_calls_without_the_native_part_give_the_same_bits(lutq, monkeypatch):
+    from gpu_util import DeviceCase, to_bits
+    from paper_2407_10960_amd import binding
+    assert binding._native() is not binding._NoNative
+    c = gen.make_case(2, 5, 64, 1024, 4, 64, "f16", "nf")
+    d = DeviceCase(lutq, c)
+    want = to_bits(d.matmul(lutq))
+    monkeypatch.setattr(binding, "_NATIVE", binding._NoNative)
+    assert np.array_equal(to_bits(d.matmul(lutq)), want)
+
+
 @pytest.mark.gpu
 def test_native_calls_match_the_python_path(lutq):
     import torch
