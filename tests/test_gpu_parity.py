@@ -262,29 +262,38 @@ def test_64_row_slices_over_seeded_random_shapes(lutq):
 
 
 WIDE_FULL_SIZE = [
-    # (name, N, K, group, dtype, M): shapes with two or more row blocks per compute unit, default launch configuration
+    # (name, N, K, group, dtype, M): shapes with more than one row block per compute unit; the names describe the 64-row slices
     ("8B gate_up W4 g128 M64 (shares of seven row blocks: passes of four and three)", 28672, 4096, 128, "f16", 64),
     ("8B gate_up W4 g128 bf16 M40", 28672, 4096, 128, "bf16", 40),
     ("70B down W4 g64 bf16 M64 (two row blocks per workgroup, K = 28672)", 8192, 28672, 64, "bf16", 64),
     ("70B qkv W4 g64 M100 (a 64-row slice and 36 rows; shares of 2 and 3)", 10240, 8192, 64, "f16", 100),
     ("70B gate_up W4 g64 bf16 M128 (fourteen row blocks per workgroup)", 57344, 8192, 64, "bf16", 128),
+    ("70B gate_up W4 g64 bf16 M40 (fourteen row blocks per workgroup)", 57344, 8192, 64, "bf16", 40),
+    ("5120x13824 W4 g128 bf16 M48 (scale rows of 216 bytes)", 5120, 13824, 128, "bf16", 48),
+    ("12288x12288 W4 g128 bf16 M64 (three row blocks per workgroup)", 12288, 12288, 128, "bf16", 64),
 ]
 
 
 @pytest.mark.parametrize("name,N,K,group,dtype,M", WIDE_FULL_SIZE)
 def test_64_row_slices_full_size(lutq, name, N, K, group, dtype, M):
-    """Full layer sizes beyond 32 rows in the default launch configuration (64-row slices); the oracle recomputes
-    all M rows of 176 sampled weight rows, first and last row blocks included."""
-    assert lutq.lutq_plan_default(4, group, M, N, K, 0 if dtype == "f16" else 1).scheduling == 3
+    """Full layer sizes beyond 32 rows, in 64-row slices (which the plan asks for) and as a call without a plan takes them (one
+    launch, which up to 64 rows may be such a slice); the oracle recomputes all M rows of 176 sampled weight rows, first and
+    last row blocks included."""
+    dt = 0 if dtype == "f16" else 1
+    assert lutq.lutq_plan_default(4, group, M, N, K, dt).scheduling == 3
     c = gen.make_case(31, M, N, K, 4, group, dtype, "random_index")
     d = DeviceCase(lutq, c)
-    Y = to_bits(d.matmul(lutq))
-    assert not d.ws[:65536].any().item()
     rng = np.random.default_rng(2)
     rows = np.unique(np.concatenate([np.arange(16), np.arange(N - 16, N), rng.choice(N, 144, replace=False)]))
     sub = gen.Case(M, len(rows), K, 4, group, dtype, c.X, c.Q[rows], c.S[rows], c.T)
-    check_y(Y[:, rows], sub, name)
-    assert np.isfinite(orc.to_f64(Y, dtype)).all()
+    slices = to_bits(d.matmul(lutq, plan=lutq.Plan(scheduling=3)))
+    plain = to_bits(d.matmul(lutq))
+    assert not d.ws[:65536].any().item()
+    for Y, what in ((slices, "slices"), (plain, "no plan")):
+        check_y(Y[:, rows], sub, f"{name}: {what}")
+        assert np.isfinite(orc.to_f64(Y, dtype)).all()
+    if lutq.calib_route(4, group, M, N, K, dt)[0] == 64:
+        assert np.array_equal(slices, plain)
 
 
 @pytest.mark.parametrize("bits", BITS)
@@ -626,7 +635,7 @@ def test_vector_codebook_matches_oracle(lutq, dtype, d):
     """lutq_matmul_pairs / lutq_matmul_quads (Section 5: vector codebooks; 256 vectors of two or four adjacent
     weights, one byte of the 4- or 2-bit layout = one index): one-hot activations read the dequantised vectors
     back bit for bit, products match the oracle on every kernel the default plans reach (work queue, teams, row
-    streaming, K slices, slices of 32 and 64 rows), a codebook made of a scalar table gives lutq_matmul's bits,
+    streaming, K slices, one launch of 48 and 100 rows), a codebook made of a scalar table gives lutq_matmul's bits,
     and a misaligned codebook is refused."""
     import torch
     b = 8 // d
@@ -761,7 +770,7 @@ FULL_SIZE = [
     ("4096x8192 W2 g64 M20 (row streaming, four K slices of eight tiles)", 4096, 8192, 2, 64, "f16", 20),
     ("4096x11008 W4 g128 M24 (row streaming, K slices of 22, 22, 21, 21 tiles, scale rows of 172 bytes)", 4096, 11008, 4, 128, "f16", 24),
     ("5120x13824 W3 g128 M32 (row streaming, 80 shares x 3 K slices on 240 units)", 5120, 13824, 3, 128, "f16", 32),
-    ("5120x13824 W4 g128 bf16 M48 (64-row slice, scale rows of 216 bytes)", 5120, 13824, 4, 128, "bf16", 48),
+    ("5120x13824 W4 g128 bf16 M48 (one launch, scale rows of 216 bytes)", 5120, 13824, 4, 128, "bf16", 48),
     ("8B down W4 g128 M17 (row streaming, 64 shares x 4 K slices)", 4096, 14336, 4, 128, "f16", 17),
     ("8B down W4 g32 bf16 M32 (row streaming, K slices, group 32)", 4096, 14336, 4, 32, "bf16", 32),
     ("8B down W3 g128 bf16 M32 (row streaming, K slices, 3 bits)", 4096, 14336, 3, 128, "bf16", 32),

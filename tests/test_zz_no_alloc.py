@@ -35,7 +35,8 @@ def test_static_scratch_matches_workspace_call(lutq):
              (32, 128, 1024, 2, "f16", lutq.Plan(1, 3, 8, 2, 8)),
              (1, 4096, 4096, 4, "f16", None),
              (40, 208, 2048, 4, "bf16", lutq.Plan(1, 5, 8, 2, 1)),
-             # 64-row slices: the operand-order copy of the activations lives in the same array
+             # 64-row slices: the operand-order copy of the activations lives in the same array; and the one launch of a call without a plan
+             (64, 4800, 1024, 4, "f16", lutq.Plan(scheduling=3)),
              (64, 4800, 1024, 4, "f16", None),
              (100, 208, 2048, 4, "bf16", lutq.Plan(scheduling=3)),
              # K slices on the row-streaming kernel: the slices' sums and the arrival counters live there too
