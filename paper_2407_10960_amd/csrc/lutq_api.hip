@@ -734,6 +734,11 @@ dequant_launcher pick_dequant(int bits, lutq_dtype dt) {
 
 }  // namespace
 
+int lutq::compute_units() {
+    const DeviceInfo di = device_info();
+    return di.ok ? di.cus : 0;
+}
+
 extern "C" const char* lutq_status_string(lutq_status s) {
     switch (s) {
         case LUTQ_OK: return "ok";

@@ -24,4 +24,8 @@ inline int super_block(int64_t nb) { return (nb % 4 == 0 && (nb <= 256 || nb > 5
 inline int64_t tile_index(int64_t rb, int64_t kt, int64_t KT, int SB) { return ((rb / SB) * KT + kt) * SB + rb % SB; }
 
 }  // namespace layout
+
+// Compute units of the current device, 0 if it cannot be asked (lutq_api.hip).
+int compute_units();
+
 }  // namespace lutq

@@ -293,7 +293,8 @@ __global__ __launch_bounds__(64 * kPanelWaves) void panel_kernel(const PanelPara
     // the partner's words are asked for a unit ahead of their use; only if it is late are they asked for again
     u32x2 seen;
     auto ask = [&] {
-seen = __builtin_bit_cast(u32x2, __hip_atomic_load(reinterpret_cast<uint64_t*>(other), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)); };
+        seen = __builtin_bit_cast(u32x2, __hip_atomic_load(reinterpret_cast<uint64_t*>(other), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
+    };
     auto wait_for = [&](int word, int v) {
         while ((int)__builtin_amdgcn_readfirstlane(word ? seen.y : seen.x) < v) ask();
         asm volatile("" ::: "memory");

@@ -426,9 +426,11 @@ extern "C" lutq_status lutq_quantize(const void* W, int w_is_f32, const void* lu
     const int64_t units = nb * (K / uc);
     p.nb = (int)nb;
     p.bf16 = dtype == LUTQ_BF16;
-    // two workgroups (their tables fill the LDS) per compute unit of the 256; more would only build more tables
+    // two workgroups (their tables fill the LDS) per compute unit; more would only build more tables
+    const int cus = lutq::compute_units();
+    if (cus < 1) return LUTQ_ERR_DEVICE;
     int64_t grid = (units + lutq::kQuantWaves - 1) / lutq::kQuantWaves;
-    if (grid > 512) grid = 512;
+    if (grid > 2 * (int64_t)cus) grid = 2 * (int64_t)cus;
     p.drb = (int)(grid * lutq::kQuantWaves / p.upr);
     p.duc = (int)(grid * lutq::kQuantWaves % p.upr);
     const hipStream_t s = static_cast<hipStream_t>(stream);
