@@ -1993,11 +1993,19 @@ extern "C" lutq_status lutq_dequant(const void* packed, const void* scales, cons
     p.SB = super_block(N / 16);
     p.SBL = ilog2(p.SB);
     p.tiles = (N / 16) * (int64_t)p.KT;
-    // one workgroup per compute unit; fewer wavefronts each where there are few tiles, so that all units get some
+    // Workgroups of four wavefronts, eight at 4 bits from 24 tiles per compute unit, as many per unit as run side by side: three (bf16) or
+    // four of eight; of four, four at 2 and 3 bits -- eight, the last of which follow, on matrices of 48 tiles per unit and more (us, four / eight
+    // per unit: 3-bit 8192 x 4096 16.0 / 17.5, 28672 x 4096 60.3 / 57.0; 2-bit fp16 10240 x 4096 19.4 / 20.5, 28672 x 4096 58.7 / 54.0; 4-bit fp16
+    // 4096 x 4096, four of four / four of eight, 9.8 / 9.5, 8192 x 4096 19.7 / 18.7).
     const int64_t per_unit = (p.tiles + di.cus - 1) / di.cus;
-    p.NW = (int)(per_unit < 4 ? 4 : per_unit > kDequantWaves ? kDequantWaves : per_unit);
+    p.NW = bits == 4 && per_unit >= 24 ? 8 : 4;
+    const int64_t resident = p.NW == 8 ? (dtype == LUTQ_BF16 ? 3 : 4) : bits == 4 || per_unit >= 48 ? 8 : 4;
     int64_t grid = (p.tiles + p.NW - 1) / p.NW;
-    if (grid > di.cus) grid = di.cus;
+    if (grid > di.cus * resident) grid = di.cus * resident;
+    // Past the caches only what would not stay in them until a product reads it (us with a product of 512 rows, through the caches / past
+    // them: 4-bit fp16 1024 x 1024 11.9 / 14.2, 4096 x 4096 35.2 / 38.5, 10240 x 4096 68.2 / 73.8, 14336 x 4096 90.6 / 93.6, 8192 x 8192
+    // 118.2 / 113.7, 28672 x 4096 163.5 / 158.9; the call alone is up to 15 % faster past them, which the product pays for).
+    p.through = N * K * 2 >= (int64_t)1 << 27;
     const hipError_t e = pick_dequant(bits, dtype)(group_size, p, (int)grid, static_cast<hipStream_t>(stream));
     return e == hipSuccess ? LUTQ_OK : LUTQ_ERR_DEVICE;
 }

@@ -181,13 +181,6 @@ __device__ __forceinline__ void lut_build(char* lds, const LutSeed& seed, int mi
     }
 }
 
-template <int BITS, typename DT>
-__device__ __forceinline__ void build_lut(char* lds, const uint16_t* __restrict__ T, int log2c, int tid, int nthreads) {
-    const int ltpe = lut_log2_threads_per_row<BITS>(nthreads);
-    const LutSeed s = lut_fetch<BITS>(T, tid, ltpe);
-    lut_build<BITS, DT>(lds, s, (int)(reinterpret_cast<uintptr_t>(T) >> 1) & 1, log2c, tid, ltpe);
-}
-
 // ---------------------------------------------------------------------------------------
 // One table per output row (finer-grained tables: every output channel has its own 2^b values).
 // A lane only ever looks up indices of one row of a row block (row lane % 16), so its private copy of

@@ -177,12 +177,10 @@ hipError_t launch_rows_group(int mb, int amax, bool rowlut, const RowsParams& p,
 
 template <int GROUP>
 hipError_t launch_dq(const DequantParams& p, int grid, hipStream_t stream) {
-    auto kernel = dequant_kernel<LUTQ_INST_BITS, GROUP, LUTQ_INST_DT>;
-    const int lds_bytes = dequant_lds_bytes<LUTQ_INST_BITS>(p.NW);
-    static hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-    if (attr != hipSuccess) return attr;
-    hipLaunchKernelGGL(kernel, dim3(grid), dim3(64 * p.NW), lds_bytes, stream, p);
+    constexpr int most = dequant_lds_bytes<LUTQ_INST_BITS, LUTQ_INST_DT>(kDequantWaves);
+    static_assert(most <= 64 * 1024, "more has to be enabled first");
+    const int lds_bytes = dequant_lds_bytes<LUTQ_INST_BITS, LUTQ_INST_DT>(p.NW);
+    hipLaunchKernelGGL((dequant_kernel<LUTQ_INST_BITS, GROUP, LUTQ_INST_DT>), dim3(grid), dim3(64 * p.NW), lds_bytes, stream, p);
     return hipGetLastError();
 }
 

@@ -649,9 +649,10 @@ __global__ __launch_bounds__(WIDE ? 1024 : 512) void matmul_kernel(const MatmulP
 // and scale routine as the fused kernel.
 //
 // What bounds it: the writes (the dense matrix, four times the packed one or more).  A tile's lanes hold 64-byte pieces of sixteen
-// rows; they pass through LDS and leave as whole 256-byte pieces of four rows, past the caches, while the next tile's words are
-// on their way.  One workgroup per compute unit with a table that has no bank conflicts: 28672 x 4096 W4 fp16 62 us, 4.7 TB/s (86
-// us with pieces of 64 bytes, 8 table copies, nothing in flight; torch fills the same matrix in 36 us), 3-bit bf16 81 -> 59 us.
+// rows; they pass through LDS and leave as whole 256-byte pieces of four rows, while the next tile's words are on their way.
+// Eight table copies: one per lane has no bank conflicts but fills half the LDS and takes longer to build, 256 x 1024 3.3 us against 2.9,
+// 6144 x 4096 17.9 against 13.0.  28672 x 4096 W4 fp16 60.6 us, 4.9 TB/s (86 us with pieces of 64 bytes and nothing in flight; torch
+// fills the same matrix in 36 us), 3-bit bf16 80 -> 55 us; 4096 x 4096 W4 fp16 12.3 -> 9.5.
 // ---------------------------------------------------------------------------------------------
 struct DequantParams {
     const uint8_t* packed;
@@ -662,20 +663,26 @@ struct DequantParams {
     int N, K, KT, SG;
     int SB, SBL;      // row blocks per super-block of the packed layout, and their log2
     int64_t tiles;    // (N/16) * KT
-    int NW;           // wavefronts per workgroup, 4 to kDequantWaves
+    int NW;           // wavefronts per workgroup, 4 or 8
+    int through;      // W is written past the caches
 };
 
-constexpr int kDequantWaves = 16;
-// LDS: [table, 256-byte entry stride][per wavefront: 16 rows x 128 columns]
-template <int BITS>
-__host__ __device__ constexpr int dequant_lds_bytes(int waves) { return lut_row_table_bytes<BITS>() + waves * 4096; }
+constexpr int kDequantWaves = 8;
+constexpr int kDequantLog2Copies = 3;
+template <int BITS, typename DT>
+__host__ __device__ constexpr int dequant_table_bytes() {
+    return ((BITS == 3 ? 64 : 256) * (BITS == 2 || std::is_same<DT, BF16>::value ? 8 : 4)) << kDequantLog2Copies;
+}
+// LDS: [table][per wavefront: 16 rows x 128 columns]
+template <int BITS, typename DT>
+__host__ __device__ constexpr int dequant_lds_bytes(int waves) { return dequant_table_bytes<BITS, DT>() + waves * 4096; }
 
 template <int BITS, int GROUP, typename DT>
 __global__ __launch_bounds__(64 * kDequantWaves) void dequant_kernel(const DequantParams p) {
     using Gm = Geo<BITS>;
     constexpr int TK = Gm::TK, STEPS = Gm::STEPS, TILE_BYTES = Gm::TILE_BYTES;
     constexpr int TPS = GROUP > TK ? GROUP / TK : 1, NS = GROUP > TK ? 1 : TK / GROUP, SPG = GROUP / 32;
-    constexpr int LOG2C = perm_log2_copies<BITS, DT>();
+    constexpr int LOG2C = kDequantLog2Copies;
     extern __shared__ __align__(16) char smem[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -683,7 +690,7 @@ __global__ __launch_bounds__(64 * kDequantWaves) void dequant_kernel(const Dequa
     const int li = lane & 15, lo = lane >> 4;
     const rsrc_t rW = make_rsrc(p.packed, p.packed_bytes);
     const rsrc_t rS = make_rsrc(p.scales, (uint32_t)p.N * (uint32_t)p.SG * 2u);
-    char* tr = smem + lut_row_table_bytes<BITS>() + wave * 4096;
+    char* tr = smem + dequant_table_bytes<BITS, DT>() + wave * 4096;
 
     struct Tile {
         WFrag<BITS> f;
@@ -705,34 +712,45 @@ __global__ __launch_bounds__(64 * kDequantWaves) void dequant_kernel(const Dequa
     };
     int64_t t = (int64_t)blockIdx.x * p.NW + wave;
     Tile cur, nxt;
+    const int ltpe = lut_log2_threads_per_row<BITS>(64 * p.NW);
+    const LutSeed seed = lut_fetch<BITS>(p.lut, tid, ltpe);       // (first: loads are waited for in order)
+    __builtin_amdgcn_sched_barrier(0);
     load(cur, t);
     load(nxt, t + stride);
-    build_lut<BITS, DT>(smem, p.lut, LOG2C, tid, 64 * p.NW);
+    __builtin_amdgcn_sched_barrier(0);
+    lut_build<BITS, DT>(smem, seed, (int)(reinterpret_cast<uintptr_t>(p.lut) >> 1) & 1, LOG2C, tid, ltpe);
     __syncthreads();
-    for (; t < p.tiles; t += stride) {
-        uint16_t* out = p.W + ((size_t)cur.rb * 16) * p.K + (size_t)cur.kt * TK;
+    // (two loops: stores that differ only in how they are cached are merged otherwise)
+    auto walk = [&](auto through) {
+        for (; t < p.tiles; t += stride) {
+            uint16_t* out = p.W + ((size_t)cur.rb * 16) * p.K + (size_t)cur.kt * TK;
 #pragma unroll
-        for (int half = 0; half < STEPS / 4; ++half) {
-            // 16 rows x 128 columns: as they come, sixteen rows' 64-byte pieces, to LDS; out again as four rows' 256 bytes
-            // (chunk c of row r lies at chunk c ^ r: neither side meets itself in a bank)
-            asm volatile("" ::: "memory");              // (LDS operations of one wavefront complete in order)
+            for (int half = 0; half < STEPS / 4; ++half) {
+                // 16 rows x 128 columns: as they come, sixteen rows' 64-byte pieces, to LDS; out again as four rows' 256 bytes
+                // (chunk c of row r lies at chunk c ^ r: neither side meets itself in a bank)
+                asm volatile("" ::: "memory");              // (LDS operations of one wavefront complete in order)
 #pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                const ScaleReg<DT> sc = scale_of<DT, NS>(cur.sw, (half * 4 + s) / SPG);
-                *reinterpret_cast<u32x4*>(tr + li * 256 + (((4 * s + lo) ^ li) * 16)) =
-                    scale4<BITS, DT>(lookup_step<BITS, DT, true>(cur.f, half * 4 + s, la), sc);
+                for (int s = 0; s < 4; ++s) {
+                    const ScaleReg<DT> sc = scale_of<DT, NS>(cur.sw, (half * 4 + s) / SPG);
+                    *reinterpret_cast<u32x4*>(tr + li * 256 + (((4 * s + lo) ^ li) * 16)) =
+                        scale4<BITS, DT>(lookup_step<BITS, DT, false>(cur.f, half * 4 + s, la), sc);
+                }
+                asm volatile("" ::: "memory");
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const int r = 4 * k + lo;
+                    const u32x4 v = *reinterpret_cast<const u32x4*>(tr + r * 256 + ((li ^ r) * 16));
+                    u32x4* dst = reinterpret_cast<u32x4*>(out + (size_t)r * p.K + half * 128 + 8 * li);
+                    if constexpr (decltype(through)::value) __builtin_nontemporal_store(v, dst);
+                    else *dst = v;
+                }
             }
-            asm volatile("" ::: "memory");
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const int r = 4 * k + lo;
-                const u32x4 v = *reinterpret_cast<const u32x4*>(tr + r * 256 + ((li ^ r) * 16));
-                __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(out + (size_t)r * p.K + half * 128 + 8 * li));
-            }
+            cur = nxt;
+            load(nxt, t + 2 * stride);
         }
-        cur = nxt;
-        load(nxt, t + 2 * stride);
-    }
+    };
+    if (p.through) walk(std::true_type{});
+    else walk(std::false_type{});
 }
 
 }  // namespace lutq
