@@ -17,11 +17,13 @@
 //     operand reads (32 rows, one octet each) hit all banks evenly.
 //   * The tables hold 16-bit pairs at every type: bf16 pairs are widened in registers, since LDS (operands, lookups) and not
 //     the vector unit is what the matrix instructions wait for here.
-//   * What bounds it: no unit is full.  8B gate+up, M = 128, W4 fp16, 40-42 us (two slices of 64 rows on the row-streaming kernel
-//     took 65.0; the dense fp16 product of the same shape 56): matrix units busy 40 % of a compute unit's time, LDS 40 %, vector
-//     unit 28 %; alone the matrix instructions and the reduction take 27.5 us, with the lookups and operand reads 28.9, the
-//     staging of the activations adds 8-11 us, the pairs' handshake 2, the weight loads 3.  Deeper activation prefetch, K ranges
-//     walked from a different start per workgroup, and issue priority for the wavefront that is behind changed nothing.
+//   * What bounds it: no unit is full.  8B gate+up, M = 128, W4 fp16, 42 us (two slices of 64 rows on the row-streaming kernel took
+//     65.0; the dense fp16 product of the same shape 56): matrix units busy 42 % of a compute unit's time, LDS 42 %, vector units
+//     27 %; a wavefront issues 31 % of its time, waits at s_waitcnt 37 % and to issue 32 %.  Builds with parts left out: the matrix
+//     instructions and the reduction alone take 27.5 us, with the lookups and operand reads 28.9; the staging of the activations adds
+//     8-11 us, the pairs' handshake 2, the weight loads 3.  Deeper activation prefetch, K ranges walked from a different start per
+//     workgroup, and issue priority for the wavefront that is behind changed nothing.  8B down, M = 64: 19 / 39 / 23 %, at
+//     s_waitcnt 49 %; 70B o, W3 bf16, M = 100: 23 / 40 / 50 %.
 //   * K parts are added in order through LDS at the end.  Where panels are too few to fill the chip, K is also cut into KS
 //     slices across workgroups: partial sums go to global slots, one arrival counter per (share, wavefront), and whichever
 //     slice's wavefront arrives last adds the slots in slice order (the protocol of matmul_kernel's fix-up: nobody waits).
