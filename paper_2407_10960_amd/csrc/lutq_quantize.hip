@@ -26,10 +26,14 @@
 // What bounds it: the memory traffic, with the vector unit close behind (twelve instructions a weight).  The table is built
 // per workgroup, so workgroups are few (two per compute unit) and large (eight wavefronts), each walking many units.
 // 8192 x 28672 bf16 to 4 bits, group 64: 129 us, 4.6 TB/s (658 us with an fp64 division and a scan of the sixteen entries per
-// weight); 28672 x 4096 fp32 to 4 bits fp16 189 -> 112 us, fp16 200 -> 61; 1024 x 4096 bf16 17.7 -> 9.1.
+// weight); 28672 x 4096 fp32 to 4 bits fp16 189 -> 118 us (group 256: 113), fp16 200 -> 61;
+// 1024 x 4096 bf16 17.7 -> 8.9.  An instance of more than 128 registers has one workgroup a compute unit instead of two, which costs
+// medium sizes most (4096 x 4096 fp32, group 128: 21.3 -> 24.8 us); none has.
 // Where the cells decide less (8192 x 8192 fp32 to 4 bits, us, with the fp64 division and -- sorted fp16 tables -- a binary search -> now):
-// subnormal or infinite fp16 scales 113 -> 64, an fp16 table with all but two entries within some 1e-3 of zero 113 -> 80, bf16 scales below 2^-100
-// 193 -> 222, a bf16 table without an entry below 1000 or with entries closer than 2^-40 193 -> 218 (2 bits 87 -> 88).
+// subnormal or infinite fp16 scales 113 -> 65, an fp16 table with all but two entries within some 1e-3 of zero 115 -> 70.  The scan of the
+// table alone, lane by lane, is slower than it was: bf16 scales below 2^-100, a bf16 table without an entry below 1000 or with entries closer
+// than 2^-40 194 -> 260 (3 bits 122 -> 187, 2 bits 88 -> 141).  A walk of its own for these, with the table in scalar registers, takes 202 to
+// 236 and 87 to 122, but its registers and code cost every fp32 call 2 to 6 %.
 //
 // Work unit: 16 rows x UC columns, UC = max(K tile, group), one wavefront per unit.  Lane l = 16 o + i
 // holds, for every 32-column step t of the unit, the 8 weights W[16 rb + i][col0 + 32 t + 8 o + j] --
@@ -211,35 +215,13 @@ __global__ __launch_bounds__(64 * kQuantWaves) void quantize_kernel(const QuantP
 #pragma unroll
             for (int g = 0; g < NG; ++g) dst[g] = (uint16_t)sbits[g];
         }
-        double T[E];                                  // the table in scalar registers (odd units only)
-        // the 8 indices of step t of this lane, 4 bits apart, by the fp64 rule alone
-        auto step_by_rule = [&](int t) -> uint32_t {
-            const float sg = s[t / SPG];
-            uint32_t word = 0;
-#pragma unroll 1
-            for (int half = 0; half < 2; ++half) {
-                uint32_t part = 0;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const float w = half ? weight(t, 4 + j) : weight(t, j);
-                    const double u = sg == 0.f ? 0.0 : (double)w / (double)sg;
-                    part |= nearest_entry<E>(u, T) << (4 * j);
-                }
-                word |= part << (16 * half);
-            }
-            return word;
-        };
         // the 8 indices of step t of this lane, 4 bits apart; `limited`: cells outside the table, and NaN, become one inside it
         auto step_indices = [&](int t, auto limited) -> uint32_t {
             const float sg = s[t / SPG];
             // a scale that is zero or infinite makes u = 0 (of a finite weight)
             const bool ordinary = decltype(limited)::value ? sg >= (bf16 ? 0x1p-100f : 0x1p-24f) && sg <= 0x1p+100f : sg != 0.f;
             const float inv = ordinary ? __builtin_amdgcn_rcpf(sg) : 0.f;
-            float near = kNear;
-            if constexpr (decltype(limited)::value) {
-                if (!ordinary && sg != 0.f && sg != __builtin_inff()) near = __builtin_inff();
-                if (!thresholds || __ballot(near != kNear) != 0) return step_by_rule(t);
-            }
+            const float near = !decltype(limited)::value || ordinary || sg == 0.f || sg == __builtin_inff() ? kNear : __builtin_inff();
             const float to_cell = inv * kCellScale;
             uint32_t word = 0, open = 0;              // open: bit 7 - j set where weight j is not decided
             uint32_t ent[8];
@@ -278,33 +260,27 @@ __global__ __launch_bounds__(64 * kQuantWaves) void quantize_kernel(const QuantP
                     w = widen16((j & 1) ? v >> 16 : v & 0xffffu, WT == 2);
                 }
                 const double u = sg == 0.f ? 0.0 : (double)w / (double)sg;
-                uint32_t at;
-                if constexpr (decltype(limited)::value) at = nearest_entry<E>(u, T);
-                else at = nearest_entry<E>(u, Ts);
-                word = (word & ~(15u << (4 * j))) | (at << (4 * j));
+                word = (word & ~(15u << (4 * j))) | (nearest_entry<E>(u, Ts) << (4 * j));
             }
             return word;
         };
         // The cell of a weight is an LDS address, and only a group whose scale is zero or an ordinary number is sure to keep it inside
         // the table (a weight that is not finite makes its group's scale one that is not, or a zero with a sign): any other takes the
-        // limits, in a copy of the code, since they cost 1 to 3 % of a call.
+        // limits, in a copy of the code, since they cost 1 to 3 % of a call.  Where both copies would need more than 128 registers (the
+        // largest fp32 unit: 134 against 126) only the one with the limits is built: 4096 x 4096 takes 22.2 us with it, 25.1 with both.
+        constexpr bool always_limited = WF32 && BITS == 4 && GROUP == 256;
         uint32_t most = 0, least = 0xffffffffu;       // (of the scales' patterns; a zero counts as the largest for the least)
 #pragma unroll
         for (int g = 0; g < NG; ++g) {
             most = sbits[g] > most ? sbits[g] : most;
             least = sbits[g] - 1u < least ? sbits[g] - 1u : least;
         }
-        const bool odd = !thresholds || most > (bf16 ? 0x7180u : 0x7bffu) || least < (bf16 ? 0x0d80u : 0x0400u) - 1u;
+        const bool odd = most > (bf16 ? 0x7180u : 0x7bffu) || least < (bf16 ? 0x0d80u : 0x0400u) - 1u;
         uint32_t idx[NSTEP];
-        if (__ballot(odd) == 0) {
+        if (!always_limited && __ballot(odd) == 0) {
 #pragma unroll
             for (int t = 0; t < NSTEP; ++t) idx[t] = step_indices(t, std::false_type{});
         } else {
-#pragma unroll
-    for (int c = 0; c < E; ++c) {
-        const u32x2 v = *reinterpret_cast<const u32x2*>(Ts + c);
-        T[c] = __builtin_bit_cast(double, u32x2{(uint32_t)__builtin_amdgcn_readfirstlane((int)v.x), (uint32_t)__builtin_amdgcn_readfirstlane((int)v.y)});
-    }
 #pragma unroll
             for (int t = 0; t < NSTEP; ++t) idx[t] = step_indices(t, std::true_type{});
         }
