@@ -1368,9 +1368,9 @@ struct PanelDecomp {
     int ms;                   // parts of M: mb x 32 rows each
 };
 
-// Calls of 33 rows or more without a plan: one pass over the weights measured faster than slices of 32 or 64 rows, but for one
-// row-streaming launch of up to 64 rows (panel_plan) (us, HBM-cold weights, MI355X, slices -> panel): 8B gate+up W4 fp16 M = 64 / 96 / 128 33.0 / 54.3 / 65.0 ->
-// 25.2 / 36 / 40.2, O 14.6 / 25.2 / 28.8 -> 11.8 / 13.5 / 13.5, down 33.9 / 51.0 / 66.3 -> 19.9 / 27.7 / 27.9, 1024 x 4096 18.6 /
+// Calls of 33 rows or more without a plan: one pass over the weights measured faster than slices of 32 or 64 rows, but where
+// one row-streaming launch serves up to 64 rows sooner (panel_plan).  us, HBM-cold weights, MI355X, slices -> panel: 8B gate+up W4 fp16
+// M = 64 / 96 / 128 33.0 / 54.3 / 65.0 -> 25.2 / 36 / 40.2, O 14.6 / 25.2 / 28.8 -> 11.8 / 13.5 / 13.5, down 33.9 / 51.0 / 66.3 -> 19.9 / 27.7 / 27.9, 1024 x 4096 18.6 /
 // 27.8 / 36.7 -> 8.8 / 8.9 / 8.9, 70B gate+up 104 / 163 / 205 -> 93 / 124 / 148; W3 bf16 8B down 37.3 / 55.3 / 73.2 -> 21.5 / 27.3 /
 // 32.8, 70B O 36.6 / 54.9 / 73.3 -> 23.2 / 29.9 / 33.8.
 // The panel height (32 or 64 channels per wavefront), the number of K slices and the parts of M (a part is 32 mb rows; the weights
@@ -1993,10 +1993,10 @@ extern "C" lutq_status lutq_dequant(const void* packed, const void* scales, cons
     p.SB = super_block(N / 16);
     p.SBL = ilog2(p.SB);
     p.tiles = (N / 16) * (int64_t)p.KT;
-    // Workgroups of four wavefronts, eight at 4 bits from 24 tiles per compute unit, as many per unit as run side by side: three (bf16) or
-    // four of eight; of four, four at 2 and 3 bits -- eight, the last of which follow, on matrices of 48 tiles per unit and more (us, four / eight
-    // per unit: 3-bit 8192 x 4096 16.0 / 17.5, 28672 x 4096 60.3 / 57.0; 2-bit fp16 10240 x 4096 19.4 / 20.5, 28672 x 4096 58.7 / 54.0; 4-bit fp16
-    // 4096 x 4096, four of four / four of eight, 9.8 / 9.5, 8192 x 4096 19.7 / 18.7).
+    // Workgroups of eight wavefronts at 4 bits from 24 tiles per compute unit, else of four.  Of eight, as many per unit as run side by
+    // side: three (bf16) or four.  Of four, eight per unit at 4 bits and from 48 tiles per unit (not all run at once), else four (us, four /
+    // eight per unit: 3-bit 8192 x 4096 16.0 / 17.5, 28672 x 4096 60.3 / 57.0; 2-bit fp16 10240 x 4096 19.4 / 20.5, 28672 x 4096 58.7 / 54.0;
+    // 4-bit fp16, four per unit of four / of eight wavefronts: 4096 x 4096 9.8 / 9.5, 8192 x 4096 19.7 / 18.7).
     const int64_t per_unit = (p.tiles + di.cus - 1) / di.cus;
     p.NW = bits == 4 && per_unit >= 24 ? 8 : 4;
     const int64_t resident = p.NW == 8 ? (dtype == LUTQ_BF16 ? 3 : 4) : bits == 4 || per_unit >= 48 ? 8 : 4;
