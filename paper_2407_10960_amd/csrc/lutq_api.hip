@@ -329,6 +329,51 @@ int rowlut_queue_lds(int bits, bool bf16, int amax, int nw, int items) {
     const int slots = items * 256, stage = amax * rowlut16_stage(bits);
     return amax * rowlut16_table_bytes(bits, bf16) + 256 + nw * 1024 + (slots > stage ? slots : stage);
 }
+// Row-streaming kernel with one table per output row (5..32 rows).  Against the per-row-table teams, which hold one row block's
+// table and fetch the activations again for every row block, us (4 bits fp16 where nothing else is said):
+//   * from two row blocks per compute unit up, all of K: four row blocks side by side, or eight in one pass where their tables fit
+//     LDS (8B gate+up M = 6 / 16 / 32 20.6 / 24.0 / 27.1 in two passes of four -> 16.5 / 18.5 / 22.2; W3 bf16 M = 16 25.4 -> 21.8).
+//     (Twelve waves: sixteen took 24.0 us where twelve took 22.8.)
+//   * up to two per unit, K slices: M = 17 / 32 4096 x 14336 20.4 / 30.3 -> 15.7 / 16.3, N = K = 8192 19.6 / 20.3 -> 16.6 / 17.4, 6144 x 4096 15.3 /
+//     20.7 -> 11.7 / 12.2, 1312 x 11264 16.5 / 20.0 -> 11.3 / 11.5 (W2 32.0 / 34.3 -> 11.8 / 11.6), 4096 x 6144 M = 32 15.3 -> 11.8; not 4096 x 4096 (M = 17 8.6 ->
+//     10.4) nor 4096 x 6144 at M = 17 (11.0 -> 11.6).  Nine to sixteen rows: only a long K, M = 12 4096 x 14336 15.5 -> 13.2, 1312 x 11264 11.6 -> 10.0, and
+//     between one and two row blocks per unit (all of K: 6144 x 4096 10.2 -> 9.8, W2 11.7 -> 8.9); M = 8 4096 x 14336 12.1 -> 12.9.
+bool rowlut_rows_decomp(int bits, bool bf16, int64_t M, int64_t N, int64_t K, int group_size, int cus, Decomp* out) {
+    if (M < 5) return false;
+    const int64_t nb = N / 16, kt = K / tile_k(bits);
+    const int mb = M > 16 ? 2 : 1, sg2 = (int)(K / group_size) * 2, tab16 = rowlut16_table_bytes(bits, bf16);
+    Decomp d;
+    d.queue = 0; d.it = 0; d.rows = 1; d.stages = 2; d.r = 4;
+    const bool few = nb <= 2 * (int64_t)cus && (M > 16 ? K >= 8192 || nb > cus || (M > 24 && K >= 6144)
+                                                       : M > 8 && nb < 2 * (int64_t)cus && (K >= 11264 || nb > cus));
+    if (!few && nb < 2 * (int64_t)cus) return false;
+    const int64_t shares = (nb + 3) / 4;
+    int64_t ks = few && (M > 16 || K >= 11264) ? cus / shares : 1;
+    if (ks > kt) ks = kt;
+    if (ks > 1) {
+        d.ks = (int)ks;
+        d.grid = (int)(shares * ks);
+        d.rs = (int)(nb / shares);
+        d.nw = 8;
+    } else {
+        d.grid = (int)(nb < cus ? nb : cus);
+        d.rs = (int)(nb / d.grid);
+        const int64_t most = (nb + d.grid - 1) / d.grid;
+        if (most > 4 && most <= 8 && rows_rowlut_eight(bits, bf16 && bits != 2)) d.r = 8;
+    }
+    if (d.rs > 64) return false;
+    for (; d.r >= 4; d.r /= 2) {
+        const int most = rows_instance_waves(bits, bf16, mb, d.r);
+        if (ks <= 1) d.nw = most > 12 ? 12 : most;
+        if (d.nw > kt) d.nw = (int)(kt < 4 ? 4 : kt);
+        if (d.nw >= 4 && d.nw <= most && rows_blocks_per_round(bits, d.r, sg2, mb, d.nw, tab16) >= 1) {
+            *out = d;
+            return true;
+        }
+    }
+    return false;
+}
+
 bool rowlut_queue_decomp(int bits, bool bf16, bool sch, int64_t M, int64_t N, int64_t K, int cus, Decomp* out) {
     if (M > 4 || !sch) return false;
     const int64_t nb = N / 16, kt = K / tile_k(bits);
@@ -879,27 +924,33 @@ lutq_status prepare_rows(const void* X, const void* packed, const void* scales, 
     const int extra = (int)(nb - (int64_t)d.rs * shares);
     const int amax = d.rs + (extra ? 1 : 0);
     if (ks > 1) {
-        if (rowlut || mb > 2 || ks > kt || amax > d.r || (int64_t)shares * 64 > (int64_t)kCounterBytes) return LUTQ_ERR_PLAN;
+        if (mb > 2 || ks > kt || amax > d.r || (int64_t)shares * 64 > (int64_t)kCounterBytes) return LUTQ_ERR_PLAN;
         // (a dry run with a room of zero does not ask)
         if (!dry && !scratch) return LUTQ_ERR_PLAN;
         if ((!dry || scratch_room) && (size_t)d.grid * d.r * mb * 1024 > scratch_room) return LUTQ_ERR_SCRATCH;
     }
     const int64_t ts = kt / ks;                               // K tiles per slice (the first kt % ks slices: one more)
     // the scales of a pass's row blocks are staged in LDS in 16-byte units: row by row with 16 bytes of padding, or, where a
-    // row is not a whole number of units, as one range (shared tables only)
+    // row is not a whole number of units, as one range
     const int sg2 = (int)(K / group_size) * 2;
     const bool linear = sg2 % 16 != 0;
-    if (linear && rowlut) return LUTQ_ERR_PLAN;
     const int srow = linear ? sg2 : sg2 + 16;
-    if (rowlut && d.r != 4) return LUTQ_ERR_PLAN;           // per-row tables: four row blocks side by side
+    if (rowlut && d.r != 4 && !(d.r == 8 && rows_rowlut_eight(bits, bf16 && bits != 2))) return LUTQ_ERR_PLAN;
     const int tab16 = rowlut ? rowlut16_table_bytes(bits, bf16) : 0;
-    const int red_off = rows_red_off(bits, d.r, sg2, tab16);
     // rounds of the final reduction: as many row blocks at a time as LDS holds beside the table and the scales
+    const int beside = rows_red_off(bits, d.r, sg2, tab16);
+    int red_off = beside, xt_off = beside;
     int rpr = rows_blocks_per_round(bits, d.r, sg2, mb, d.nw, tab16);
-    if (rpr > d.r) rpr = d.r;
-    if (rpr > amax) rpr = amax;
     if (rpr < 1) return LUTQ_ERR_PLAN;
-    const int lds = red_off + rpr * mb * d.nw * 1024;
+    // one pass: the slots may lie over table and scales, where the waves' KiB for turning activations fits behind those
+    const int own_xt = rows_x_turned(mb) ? d.nw * 1024 : 0;
+    if (amax <= d.r && beside + own_xt <= 160 * 1024) {
+        red_off = 0;
+        rpr = 160 / (mb * d.nw);
+    }
+    if (rpr > amax) rpr = amax;
+    const int slots_end = red_off + rpr * mb * d.nw * 1024;
+    const int lds = slots_end > beside + own_xt ? slots_end : beside + own_xt;
     RowsParams q{};
     q.X = static_cast<const uint16_t*>(X);
     q.packed = static_cast<const uint8_t*>(packed);
@@ -932,6 +983,8 @@ lutq_status prepare_rows(const void* X, const void* packed, const void* scales, 
     q.s_magic = linear ? 0u : (uint32_t)((1ull << 32) / (uint64_t)q.s_units + 1);
     q.SROW = srow;
     q.red_off = red_off;
+    q.xt_off = xt_off;
+    q.stage_off = beside - d.r * rowlut16_stage(bits);
     q.tab_total = d.r * tab16;
     q.lut_ltpe = bits == 2 ? lut_log2_threads_per_row<2>(d.nw * 64)
                : bits == 3 ? lut_log2_threads_per_row<3>(d.nw * 64) : lut_log2_threads_per_row<4>(d.nw * 64);
@@ -1081,18 +1134,13 @@ lutq_status prepare_matmul(const void* X, const void* packed, const void* scales
     out->rows = false;
     out->rows_rowlut = false;
     if (rowlut && user_plan && user_plan->scheduling > LUTQ_SCHED_TEAMS) return LUTQ_ERR_PLAN;
-    if (rowlut && !user_plan && M > 4 && nb >= 2 * (int64_t)di.cus && ((K / group_size) * 2) % 16 == 0) {
-        // one table per output row, 5..32 rows, at least two row blocks per compute unit: the row-streaming
-        // kernel with the tables of four row blocks at a time (the teams' per-row-table kernel holds one row
-        // block's and fetches the activations again for every row block)
-        const int grid = di.cus;
-        const int64_t per = nb / grid;
-        int nw = rows_instance_waves(bits, bf16, mb, 4);
-        if (nw > kt) nw = (int)(kt < 4 ? 4 : kt);
-        if (per <= 64 && nw >= 4 && rows_blocks_per_round(bits, 4, (int)(K / group_size) * 2, mb, nw, rowlut16_table_bytes(bits, bf16)) >= 1) {
-            Decomp q;
-            q.r = 4; q.grid = grid; q.nw = nw; q.stages = 2; q.rs = (int)per; q.queue = 0; q.it = 0; q.rows = 1;
-            const lutq_status qs = prepare_rows(X, packed, scales, lut, bits, group_size, M, N, K, bf16, Y, q, out, true);
+    if (rowlut && !user_plan) {
+        Decomp q;
+        if (rowlut_rows_decomp(bits, bf16, M, N, K, group_size, di.cus, &q)) {
+            // (a scratch too small for the slices' sums leaves it to the teams)
+            const lutq_status qs = prepare_rows(X, packed, scales, lut, bits, group_size, M, N, K, bf16, Y, q, out, true,
+                                                dry ? nullptr : static_cast<char*>(workspace) + kCounterBytes,
+                                                dry ? 0 : workspace_bytes - kCounterBytes, dry);
             if (qs == LUTQ_OK) return qs;
             out->rows = false;
             out->rows_rowlut = false;

@@ -490,6 +490,18 @@ __device__ __forceinline__ u32x4 rotate_rows(u32x4 v, int n) {
     }
 }
 
+// An activation fragment (16 rows x 32 columns, one B operand) on its way through LDS.  A load whose lane 16 o + i fetches row
+// i, octet o (operand order) has sixteen rows in each group of lanes that the address unit coalesces: it passes 16 bytes a
+// clock (N = K = 8192, M = 32, every compute unit all of X: 13.4 us).  With four lanes side by side on a row's 64 bytes it passes
+// four times that, and the detour -- one 128-bit LDS write, one read per KiB -- included X takes 4.7 us.
+// So lane 4 r + o loads row r, octet o, and writes it to its 16-byte slot of the fragment's KiB; lane 16 o + i reads slot (o, i).
+// The rows of octet o are permuted so that neither the writes nor the reads of eight or sixteen lanes meet in a bank.
+__device__ __forceinline__ int xfrag_load_row(int lane) { return lane >> 2; }
+__device__ __forceinline__ int xfrag_load_octet(int lane) { return lane & 3; }
+__device__ __forceinline__ uint32_t xfrag_slot(int octet, int row) {
+    return 16u * (uint32_t)(16 * octet + (row ^ ((octet & 1) * 10 + (octet >> 1) * 4)));
+}
+
 // v_mfma_f32_16x16x32: D(16x16, fp32) += A(16x32) * B(32x16).  Lane l = 16*o + i supplies A[i][8o..8o+7]
 // and B[8o..8o+7][i]; it receives D[4o..4o+3][i].
 template <typename DT>

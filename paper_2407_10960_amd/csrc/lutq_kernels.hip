@@ -161,7 +161,11 @@ hipError_t launch_rows_one(const RowsParams& p, int lds_bytes, hipStream_t strea
 
 template <int GROUP>
 hipError_t launch_rows_group(int mb, int amax, bool rowlut, const RowsParams& p, int lds_bytes, hipStream_t stream) {
-    if (rowlut) {                    // one table per output row: four row blocks side by side
+    if (rowlut) {                    // one table per output row: eight row blocks side by side where their tables fit LDS
+        if constexpr (rows_rowlut_eight(LUTQ_INST_BITS, Tab<LUTQ_INST_BITS, LUTQ_INST_DT>::WIDE)) {
+            if (mb == 1 && amax == 8) return launch_rows_one<GROUP, 1, 8, true>(p, lds_bytes, stream);
+            if (mb == 2 && amax == 8) return launch_rows_one<GROUP, 2, 8, true>(p, lds_bytes, stream);
+        }
         if (mb == 1 && amax == 4) return launch_rows_one<GROUP, 1, 4, true>(p, lds_bytes, stream);
         if (mb == 2 && amax == 4) return launch_rows_one<GROUP, 2, 4, true>(p, lds_bytes, stream);
         return hipErrorInvalidValue;

@@ -14,7 +14,7 @@
 //     that row block's accumulators.  Up to AMAX row blocks are accumulated side by side (AMAX x MB x 4
 //     registers); a workgroup with more walks them in passes of AMAX.
 //   * So an activation fragment is fetched once per AMAX weight tiles instead of once per tile or per
-//     pair of tiles, no activation goes through LDS, and there is no barrier inside the K loop: the waves
+//     pair of tiles, no wave waits for another's activations, and there is no barrier inside the K loop: the waves
 //     run out of step and cover each other's memory and table-lookup latencies.
 //   * After a pass the waves' accumulators are added in wave order through LDS, a few row blocks per
 //     round, and written out: bit-reproducible.
@@ -60,7 +60,9 @@ struct RowsParams {
     int s_units;              // 16-byte units per row of scales (SG2 / 16)
     uint32_t s_magic;         // 2^32 / s_units + 1 (unused when s_units == 1)
     int SROW;                 // bytes from row to row of the scales in LDS (SG2 + 16: sixteen rows, sixteen banks)
-    int red_off;              // LDS offset of the reduction slots
+    int red_off;              // LDS offset of the reduction slots (0 where one pass does everything: over the table and the scales)
+    int stage_off;            // RLUT: LDS offset of the raw tables
+    int xt_off;               // TURN: LDS offset of the waves' KiB for turning activations
     int tab_total;            // RLUT: LDS bytes of the pass's per-row tables (AMAX x sixteen copies); the scales follow
     int lut_ltpe;             // log2 of the threads that build one table row together
     int G;                    // workgroups
@@ -74,6 +76,8 @@ struct RowsParams {
 
 // LDS of one launch: [table, 256-byte entry stride][scales of AMAX x 16 rows, SROW bytes each][RPR x MB x NW slots of 1 KiB]
 // RLUT: [AMAX tables of sixteen copies][scales][raw tables of AMAX row blocks][slots]
+// A launch of one pass needs neither table nor scales once its sums are added: its slots begin at offset 0 (8B gate+up M = 32: the
+// sums of seven row blocks in one round instead of two), and the KiB per wave that turns activations has a place of its own.
 
 // Registers: AMAX x MB x 4 accumulators + STEPS x MB x 4 activation operands (twice that where two tiles' are
 // held) + four weight tiles in flight, the lookup ring and addresses (about 84 at 4 bits, 108 and 116 at 2 and
@@ -82,18 +86,30 @@ struct RowsParams {
 // with four / eight row blocks side by side 114 / 149 registers, sixteen / twelve waves; M > 16 191 / 241,
 // eight waves); 0 = no such instance (the registers do not hold it without spilling).
 __host__ __device__ constexpr int rows_tiles_in_flight(int, int) { return 4; }   // (eight measured no faster)
+// Beyond sixteen rows the activations are loaded with four lanes side by side on a row (xfrag_load_row) and turned into
+// operands through LDS: N = K = 8192, one pass of two row blocks over all of K, M = 24 / 32, us: W4 fp16 19.4 / 23.1 -> 18.8 / 19.5,
+// bf16 19.6 / 23.0 -> 19.4 / 20.1, W3 20.8 / 23.8 -> 18.6 / 19.3; 4096 x 14336 in four K slices, M = 32 17.2 -> 15.4.  Up to sixteen rows
+// they are loaded in operand order: the detour's latency costs more than the address unit's time there (M = 8 13.7 -> 16.1,
+// M = 12 14.1 -> 16.1, M = 16 15.0 -> 16.3; with twelve wavefronts M = 16 15.1 -> 14.2 but M = 8 12.4 -> 13.8).
+__host__ __device__ constexpr bool rows_x_turned(int mb) { return mb == 2; }
 // The activations of the next K tile are fetched a whole tile ahead into a second set of registers where that
-// measured faster (4-bit fp16 beyond sixteen rows: 8B gate+up M = 32 21.9 -> 20.8 us); elsewhere the second set
+// measured faster (4 bits beyond sixteen rows: 8B gate+up fp16 M = 32 21.9 -> 20.8 us); elsewhere the second set
 // costs waves (twelve -> eight) or the instance, and the next tile's activations are fetched step by step
 // during the tile's last row block instead.
-__host__ __device__ constexpr bool rows_x_double(int bits, int mb, bool wide_table) { return bits == 4 && mb == 2 && !wide_table; }
+__host__ __device__ constexpr bool rows_x_double(int bits, int mb, int amax, bool wide_table) {
+    return bits == 4 && mb == 2 && (!wide_table || amax == 4);
+}
 __host__ __device__ constexpr int rows_max_waves(int bits, int mb, int amax, bool wide_table) {
     const int steps = bits == 4 ? 4 : 8;
     if (mb > 2 && (bits != 4 || amax != 4)) return 0;   // 33..64 rows: 4 bits, four row blocks side by side
     const int regs = amax * mb * 4 + steps * mb * 4 + (bits == 4 ? 84 : bits == 3 ? 116 : 108) + (wide_table ? 28 : 0)
-                   + (bits == 4 && amax == 8 ? 20 : 0) + (rows_x_double(bits, mb, wide_table) ? steps * mb * 4 + 8 : 0);
+                   + (bits == 4 && amax == 8 ? 20 : 0) + (rows_x_double(bits, mb, amax, wide_table) ? steps * mb * 4 + 8 : 0);
     return regs <= 128 ? 16 : regs <= 168 ? 12 : regs <= 240 ? 8 : 0;
 }
+
+// One table per output row, eight row blocks side by side: where eight sixteen-copy tables leave room for the rest (16 KiB each
+// at 4 bits in fp16, 4 and 8 KiB at 3 bits; 32 KiB otherwise).
+__host__ __device__ constexpr bool rows_rowlut_eight(int bits, bool wide_table) { return bits == 3 || (bits == 4 && !wide_table); }
 
 // RLUT: one table per output row (p.lut = [N, 2^bits]).  The tables of the pass's row blocks are built when the
 // pass begins, sixteen copies per row block (the four lanes of a row share one; rowlut16_build), and slot a reads
@@ -111,17 +127,18 @@ void rows_kernel(const RowsParams p) {
     constexpr int D = 4;                               // steps whose table reads are in flight ahead of their use
     static_assert(STEPS % D == 0, "the ring of table reads runs on from one tile into the next");
     constexpr int NST = rows_tiles_in_flight(BITS, AMAX);   // weight tiles (and their scales) in flight per wave
-    constexpr bool XDB = rows_x_double(BITS, MB, Tab<BITS, DT>::WIDE);
+    constexpr bool XDB = rows_x_double(BITS, MB, AMAX, Tab<BITS, DT>::WIDE);
     // More than 32 rows: the activations come from a copy in operand order (fragment (kt, s, mb) = the 1 KiB the
     // wave's 64 lanes hold for K step s of tile kt and rows 16 mb .. 16 mb + 15, rows beyond M zero), written by
     // rows_xop_kernel just before this launch: every load is one contiguous KiB instead of sixteen rows' 64 bytes.
     constexpr bool XOP = MB > 2;
+    constexpr bool TURN = rows_x_turned(MB);
     static_assert(AMAX % NST == 0, "the row blocks of a pass are walked in rounds of the pipeline's stages");
 
     asm volatile("" ::"s"(p.X), "s"(p.packed), "s"(p.scales), "s"(p.lut), "s"(p.Y), "s"(p.packed_bytes), "s"(p.scale_bytes),
                  "s"(p.x_bytes), "s"(p.M), "s"(p.N), "s"(p.K), "s"(p.KT), "s"(p.SG2), "s"(p.SBL), "s"(p.tile_stride),
                  "s"(p.sblock_bytes), "s"(p.A), "s"(p.extra), "s"(p.NW), "s"(p.TQ), "s"(p.TR), "s"(p.RPR), "s"(p.lut_ltpe),
-                 "s"(p.s_units), "s"(p.s_magic), "s"(p.SROW), "s"(p.red_off), "s"(p.tab_total), "s"(p.KS), "s"(p.TS), "s"(p.KSB), "s"(p.TQ1),
+                 "s"(p.s_units), "s"(p.s_magic), "s"(p.SROW), "s"(p.red_off), "s"(p.stage_off), "s"(p.xt_off), "s"(p.tab_total), "s"(p.KS), "s"(p.TS), "s"(p.KSB), "s"(p.TQ1),
                  "s"(p.TR1));
 
     extern __shared__ __align__(16) char smem[];
@@ -172,7 +189,8 @@ void rows_kernel(const RowsParams p) {
     for (int mb = 0; mb < MB; ++mb) {
         const int m = li + 16 * mb;
         valid[mb] = m < p.M;
-        xlane[mb] = XOP ? (uint32_t)mb * 1024u + 16u * (uint32_t)lane : ((uint32_t)m * (uint32_t)p.K + 8u * (uint32_t)lo) * 2u;
+        const int xr = TURN ? xfrag_load_row(lane) + 16 * mb : m, xo = TURN ? xfrag_load_octet(lane) : lo;
+        xlane[mb] = XOP ? (uint32_t)mb * 1024u + 16u * (uint32_t)lane : ((uint32_t)xr * (uint32_t)p.K + 8u * (uint32_t)xo) * 2u;
     }
     const uint32_t wlane = 16u * lane;
     (void)wlane;
@@ -221,21 +239,17 @@ void rows_kernel(const RowsParams p) {
             load_w(st[a], p0, skip, ka, a);
             __builtin_amdgcn_sched_barrier(0);
         }
-        // Activations of two K tiles: the one being multiplied and the next one, asked for a whole tile ahead.  (A
-        // load covers sixteen rows 2K bytes apart -- sixteen requests to one L2 channel -- and takes its time.)
-        u32x4 bx[XDB ? 2 : 1][STEPS][MB];
-        auto load_x_step = [&](auto buf, int kt, int s) {
+        // bx: operands of the K tile being multiplied; xr: the next tile's activations as they arrive, asked for a whole tile
+        // ahead (without a second set they arrive in bx itself, step by step behind the last products of the tile before).
+        u32x4 bx[STEPS][MB], xr[XDB ? STEPS : 1][MB];
+        auto load_x_step = [&](u32x4 (&x)[MB], int kt, int s) {
             const uint32_t tx = kt < kb ? (uint32_t)kt * (XOP ? STEPS * MB * 1024 : TK * 2) : kOutOfRange;
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb)
-                bx[decltype(buf)::value][s][mb] =
-                    __builtin_amdgcn_raw_buffer_load_b128(rX, tx + xlane[mb] + (XOP ? MB * 1024u : 64u) * s, 0, kAuxNone);
+                x[mb] = __builtin_amdgcn_raw_buffer_load_b128(rX, tx + xlane[mb] + (XOP ? MB * 1024u : 64u) * s, 0, kAuxNone);
         };
-        auto load_x = [&](auto buf, int kt) {
 #pragma unroll
-            for (int s = 0; s < STEPS; ++s) load_x_step(buf, kt, s);
-        };
-        load_x(std::integral_constant<int, 0>{}, ka);
+        for (int s = 0; s < STEPS; ++s) load_x_step(XDB ? xr[s] : bx[s], ka, s);
         __builtin_amdgcn_sched_barrier(0);
         {
             // The pass's scales: rows (rb_first + p0) * 16 onwards, na * 16 rows of SG2 bytes, one contiguous
@@ -253,12 +267,12 @@ void rows_kernel(const RowsParams p) {
             }
         }
         if constexpr (RLUT) {
-            // the raw tables of the pass's rows (one contiguous range) are staged in an area of their own in front
-            // of the reduction slots (those may still be read by a slower wave of the previous pass), and the
+            // the raw tables of the pass's rows (one contiguous range) are staged in an area of their own (the reduction
+            // slots may still be read by a slower wave of the previous pass), and the
             // sixteen-copy tables are built from there (nobody reads tables after a pass's K loop, which every wave
             // has left: the reduction began with a barrier)
             const rsrc_t rT = make_rsrc(p.lut, (uint32_t)p.N * (uint32_t)((1 << BITS) * 2));
-            char* stage = red - AMAX * rowlut16_stage_bytes<BITS>();
+            char* stage = smem + p.stage_off;
             const int words = na * (rowlut16_stage_bytes<BITS>() / 4);
             const uint32_t tbase = (uint32_t)(rb_first + p0) * (uint32_t)rowlut16_stage_bytes<BITS>();
             for (int i = tid; i < words; i += p.NW * 64)
@@ -285,24 +299,39 @@ void rows_kernel(const RowsParams p) {
         for (int s = 0; s < D; ++s) raw[s] = lookup_step<BITS, DT, PERM>(st[0].w, s, la_of(0, skip));
         __builtin_amdgcn_sched_barrier(0);
 
-        // One K tile: buf = which set of bx holds its activations.  With two sets a tile beyond the wave's range
-        // (the second of a pair when the wave owns an odd number) issues the same loads, out of range, and
-        // multiplies nothing.  With one set the tile's last slot always multiplies (an empty pass slot there would
-        // be a row block of zeros: the pass's empty slots are its first ones), because the next tile's activations
-        // are fetched inside it, step by step as this tile's have had their last use.
-        auto tile = [&](auto buf, int kt) {
-            constexpr int B = decltype(buf)::value;
-            if constexpr (XDB) {
-                load_x(std::integral_constant<int, B ^ 1>{}, kt + 1);
+        // Where activations arrive in load order (xfrag_load_row), they are turned into operands through the wave's own KiB of LDS, one
+        // fragment after the other: LDS serves a wave's accesses in order, so nothing is waited for in between.
+        // (Where there are several passes the KiB is the head of the reduction's area: barriers lie between the K loop and every use of that.)
+        char* xt = smem + p.xt_off + wave * 1024;
+        auto turn_x = [&] {
+            if constexpr (TURN) {
+#pragma unroll
+                for (int s = 0; s < STEPS; ++s)
+#pragma unroll
+                    for (int mb = 0; mb < MB; ++mb) {
+                        *reinterpret_cast<u32x4*>(xt + xfrag_slot(xfrag_load_octet(lane), xfrag_load_row(lane))) = XDB ? xr[s][mb] : bx[s][mb];
+                        bx[s][mb] = *reinterpret_cast<const u32x4*>(xt + xfrag_slot(lo, li));
+                    }
                 __builtin_amdgcn_sched_barrier(0);
             }
-            const bool live = !XDB || kt < kb;
+        };
+
+        // One K tile.  Without a second set its last slot always multiplies (an empty pass slot there would be a row block of
+        // zeros: the pass's empty slots are its first ones), because the next tile's activations are fetched inside it, step
+        // by step as this tile's have had their last use.
+        auto tile = [&](int kt) {
+            turn_x();
+            if constexpr (XDB) {
+#pragma unroll
+                for (int s = 0; s < STEPS; ++s) load_x_step(xr[s], kt + 1, s);
+                __builtin_amdgcn_sched_barrier(0);
+            }
 #pragma unroll
             for (int a = 0; a < AMAX; ++a) {
                 Stage& cur = st[a % NST];
                 const Stage& nxt = st[(a + 1) % NST];
                 const LutAddr la_cur = la_of(a, skip), la_nxt = la_of((a + 1) % AMAX, skip);
-                if ((!XDB && a == AMAX - 1) || (live && a >= skip)) {
+                if ((!XDB && a == AMAX - 1) || a >= skip) {
                     // dequantise the tile step by step and multiply it into row block a's accumulators
                     u32x4 aop[2];
 #pragma unroll
@@ -318,11 +347,11 @@ void rows_kernel(const RowsParams p) {
                         if (s > 0) {
 #pragma unroll
                             for (int mb = 0; mb < MB; ++mb)
-                                acc[a][mb] = mfma16x16x32<DT>(aop[(s - 1) & 1], bx[B][s - 1][mb], acc[a][mb]);
+                                acc[a][mb] = mfma16x16x32<DT>(aop[(s - 1) & 1], bx[s - 1][mb], acc[a][mb]);
                             __builtin_amdgcn_sched_barrier(0);
                             if constexpr (!XDB) {
                                 if (a == AMAX - 1) {
-                                    load_x_step(std::integral_constant<int, 0>{}, kt + 1, s - 1);
+                                    load_x_step(bx[s - 1], kt + 1, s - 1);
                                     __builtin_amdgcn_sched_barrier(0);
                                 }
                             }
@@ -340,14 +369,7 @@ void rows_kernel(const RowsParams p) {
                 __builtin_amdgcn_sched_barrier(0);
             }
         };
-        if constexpr (XDB) {
-            for (int kt = ka; kt < kb; kt += 2) {
-                tile(std::integral_constant<int, 0>{}, kt);
-                tile(std::integral_constant<int, 1>{}, kt + 1);
-            }
-        } else {
-            for (int kt = ka; kt < kb; ++kt) tile(std::integral_constant<int, 0>{}, kt);
-        }
+        for (int kt = ka; kt < kb; ++kt) tile(kt);
 
         // ---- add the waves' sums in wave order, RPR row blocks per round, and store ----
         for (int a0 = 0; a0 < na; a0 += p.RPR) {   // a0: first row block (of the pass) of this round
