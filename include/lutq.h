@@ -195,8 +195,9 @@ typedef struct {
 #define LUTQ_SCHED_QUEUE 2
 #define LUTQ_SCHED_ROWS 3
 
-/* Fills *plan with the library's choice for this problem on the current device.  For M > 32 that is the
- * decomposition of the slices, the one a plan can ask for (a call without a plan takes all rows in one launch). */
+/* Fills *plan with the library's rules' choice for this problem on the current device.  Up to 32 rows a call with this plan is
+ * a call without one: both take another launch where estimated times say that it is clearly faster.  For M > 32 the plan is the decomposition of the slices, the one a plan can
+ * ask for (a call without a plan takes all rows in one launch). */
 lutq_status lutq_plan_default(int bits, int group_size, int64_t M, int64_t N, int64_t K,
                               lutq_dtype dtype, lutq_plan* plan);
 

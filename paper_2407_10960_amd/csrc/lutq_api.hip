@@ -11,6 +11,7 @@
 #include "lutq.h"
 #include "lutq_calib.h"
 #include "lutq_launch.hpp"
+#include "lutq_estimates.hpp"
 #include "lutq_layout.hpp"
 
 namespace {
@@ -802,6 +803,28 @@ extern "C" const char* lutq_status_string(lutq_status s) {
     return "unknown status";
 }
 
+namespace {
+bool estimated_plan(int bits, int group_size, int64_t M, int64_t N, int64_t K, lutq_dtype dtype, int cus, size_t workspace_bytes, bool fitted_workspace, lutq_plan* out);
+
+lutq_plan plan_of(const Decomp& d) {
+    return lutq_plan{d.r, d.grid, d.nw, d.stages, d.rs, d.rows ? LUTQ_SCHED_ROWS : d.queue ? LUTQ_SCHED_QUEUE : LUTQ_SCHED_TEAMS, d.it};
+}
+bool same_plan(const lutq_plan& a, const lutq_plan& b) {
+    return a.row_blocks_per_wave == b.row_blocks_per_wave && a.grid == b.grid && a.waves_per_workgroup == b.waves_per_workgroup &&
+           a.tiles_in_flight == b.tiles_in_flight && a.row_groups_per_workgroup == b.row_groups_per_workgroup && a.scheduling == b.scheduling &&
+           a.tiles_per_item == b.tiles_per_item;
+}
+
+// The plan of the rules for up to 32 rows: work queue, K-sliced row streaming, row streaming, teams.
+Decomp ruled_decomp(int bits, int group_size, int64_t M, int64_t N, int64_t K, bool bf16, bool sch, int cus, bool small_scratch) {
+    Decomp d;
+    if (!default_queue_decomp(bits, bf16, sch, M, N, K, cus, &d) && !sliced_rows_decomp(bits, bf16, M, N, K, group_size, cus, &d) &&
+        !default_rows_decomp(bits, bf16, M, N, K, group_size, cus, &d))
+        d = default_decomp(bits, bf16, sch, M, N, K, cus, 0, group_size, small_scratch);
+    return d;
+}
+}  // namespace
+
 extern "C" size_t lutq_workspace_bytes(int64_t N, int64_t K, int bits, int group_size) {
     if (check_problem(bits, group_size, N, K) != LUTQ_OK) return 0;
     return kWorkspaceBytes;
@@ -822,17 +845,8 @@ extern "C" lutq_status lutq_plan_default_for(int bits, int group_size, int64_t M
         wide = false;
         M = 32;
     }
-    if (!wide && !default_queue_decomp(bits, dtype == LUTQ_BF16, sch, M, N, K, compute_units, &d) &&
-        !sliced_rows_decomp(bits, dtype == LUTQ_BF16, M, N, K, group_size, compute_units, &d) &&
-        !default_rows_decomp(bits, dtype == LUTQ_BF16, M, N, K, group_size, compute_units, &d))
-        d = default_decomp(bits, dtype == LUTQ_BF16, sch, M, N, K, compute_units, 0, group_size);
-    plan->row_blocks_per_wave = d.r;
-    plan->grid = d.grid;
-    plan->waves_per_workgroup = d.nw;
-    plan->tiles_in_flight = d.stages;
-    plan->row_groups_per_workgroup = d.rs;
-    plan->scheduling = d.rows ? LUTQ_SCHED_ROWS : d.queue ? LUTQ_SCHED_QUEUE : LUTQ_SCHED_TEAMS;
-    plan->tiles_per_item = d.it;
+    if (!wide) d = ruled_decomp(bits, group_size, M, N, K, dtype == LUTQ_BF16, sch, compute_units, false);
+    *plan = plan_of(d);
     return LUTQ_OK;
 }
 
@@ -1165,6 +1179,12 @@ lutq_status prepare_matmul(const void* X, const void* packed, const void* scales
         const int sched = user_plan ? user_plan->scheduling : 0;
         if (sched < 0 || sched > LUTQ_SCHED_ROWS) return LUTQ_ERR_PLAN;
         Decomp q;
+        // no plan, or the one that lutq_plan_default gives, which stands for none: another where estimated to be clearly faster
+        lutq_plan estimated;
+        if (!small_scratch && ((sched == 0 && plan_is_empty) || same_plan(*user_plan, plan_of(ruled_decomp(bits, group_size, M, N, K, bf16, sch, di.cus, false)))) &&
+            estimated_plan(bits, group_size, M, N, K, dtype, di.cus, dry && !fitted_workspace ? kWorkspaceBytes : workspace_bytes, fitted_workspace, &estimated))
+            return prepare_matmul(X, packed, scales, lut, bits, group_size, M, N, K, dtype, Y, workspace, workspace_bytes, &estimated,
+                                  rowlut, dry_run_cus, out, fitted_workspace, false);
         if (sched == LUTQ_SCHED_ROWS) {
             // tiles_per_item: K tiles per slice where K is cut across workgroups (grid = shares x slices)
             int ks = 1;
@@ -1351,6 +1371,85 @@ lutq_status prepare_matmul(const void* X, const void* packed, const void* scales
     out->mb = mb; out->r = r; out->stages = d.stages; out->xm = xm;
     out->sch = sch; out->wide = wide; out->xsh = xsh; out->rowlut = rowlut;
     return LUTQ_OK;
+}
+
+// The plan of a call of up to 32 rows without one, where estimates say that the rules' takes clearly longer (lutq_estimates.hpp);
+// false: the rules' plan.  Candidates: row streaming from five rows up, four or eight row blocks side by side, all of K or
+// any number of K slices, up to two workgroups per compute unit; one team per row block of four to sixteen waves.  Only a
+// candidate that this scratch and the instances can run is taken.  The rules stay where they are within a margin: they were
+// measured on the shapes that models have, and the estimates are no better than 7 to 16 %.
+bool estimate_plan(int bits, int group_size, int64_t M, int64_t N, int64_t K, lutq_dtype dtype, int cus, size_t workspace_bytes, bool fitted_workspace, lutq_plan* out) {
+    const int64_t nb = N / 16, kt = K / tile_k(bits);
+    const bool bf16 = dtype == LUTQ_BF16, sch = (K / group_size) % 8 == 0;
+    const int mb = M > 16 ? 2 : 1;
+    const double megabytes = ((double)N * (double)K * bits / 8. + (double)N * (double)(K / group_size) * 2.) * 1e-6;
+    const Decomp ruled = ruled_decomp(bits, group_size, M, N, K, bf16, sch, cus, false);
+    if (ruled.queue) return false;
+    // (1..4 rows: the rules hold but for shapes that they deal to few workgroups -- 8624 x 14848 M = 2 bf16 55.5 us, one team per row block 22.7)
+    const double margin = M > 4 && !ruled.rows ? 0.87 : 0.8;
+    double best = margin * (ruled.rows ? rows_estimate_us(bits, M, nb, kt, megabytes, ruled.r, ruled.grid, ruled.nw, ruled.ks > 1 ? ruled.ks : 1, cus)
+                                       : teams_estimate_us(bits, M, nb, kt, megabytes, ruled.r, ruled.grid, ruled.nw, ruled.rs,
+                                                           M > 4 && teams_can_share_x(bits, mb, ruled.rs), cus));
+    bool found = false;
+    auto consider = [&](double us, const lutq_plan& plan) {
+        if (us >= best) return;
+        Prepared q{};
+        if (prepare_matmul(nullptr, nullptr, nullptr, nullptr, bits, group_size, M, N, K, dtype, nullptr, nullptr, workspace_bytes, &plan, false,
+                           cus, &q, true) != LUTQ_OK)
+            return;
+        best = us;
+        *out = plan;
+        found = true;
+    };
+    // (beyond 12 us the estimates of one team per row block are too low at 17..32 rows and a long K: 8192 x 28672 M = 32 fp16 44 -> 115 us)
+    for (int nw : {4, 5, 6, 8, 12, 16}) {
+        if (nb > kMaxGrid || (!sch && nw > 8)) continue;
+        const double us = teams_estimate_us(bits, M, nb, kt, megabytes, 1, (int)nb, nw, 1, false, cus);
+        if (M <= 4 || us <= 12.) consider(us, lutq_plan{1, (int)nb, nw, 2, 1, LUTQ_SCHED_TEAMS, 0});
+    }
+    if (M < 5) return found;
+    for (int side : {4, 8}) {
+        const int most = rows_instance_waves(bits, bf16, mb, side);
+        for (int nw : {most > 12 ? 12 : most, 8}) {
+            if (nw < 4 || nw > most) continue;
+            for (int64_t grid : {nb < cus ? nb : (int64_t)cus, (int64_t)2 * cus})
+                if (grid <= nb && nb / grid <= 64)
+                    consider(rows_estimate_us(bits, M, nb, kt, megabytes, side, (int)grid, nw, 1, cus),
+                             lutq_plan{side, (int)grid, nw, 2, (int)(nb / grid), LUTQ_SCHED_ROWS, 0});
+            const int64_t shares = (nb + side - 1) / side;
+            for (int64_t ks = 2; ks <= kt && ks <= 40 && shares * ks <= 2 * (int64_t)cus; ++ks) {
+                const int64_t it = (kt + ks - 1) / ks;        // (slice counts that a plan can name)
+                if ((kt + it - 1) / it == ks)
+                    consider(rows_estimate_us(bits, M, nb, kt, megabytes, side, (int)(shares * ks), nw, (int)ks, cus),
+                             lutq_plan{side, (int)(shares * ks), nw, 2, (int)(nb / shares), LUTQ_SCHED_ROWS, (int)it});
+            }
+        }
+    }
+    return found;
+}
+
+// The same, remembered per thread for the last problems by their sizes and types (the choice takes some ten microseconds).
+bool estimated_plan(int bits, int group_size, int64_t M, int64_t N, int64_t K, lutq_dtype dtype, int cus, size_t workspace_bytes, bool fitted_workspace, lutq_plan* out) {
+    struct Entry {
+        int64_t N, K;
+        size_t room;
+        int bits, group_size, M, dtype, cus, found;
+        lutq_plan plan;
+    };
+    constexpr int kEntries = 128;
+    static thread_local Entry table[kEntries];        // (zero: N = 0, which no problem has)
+    // more scratch than any launch uses is the same as that
+    const size_t room = fitted_workspace ? workspace_bytes : kWorkspaceBytes;
+    uint64_t h = (uint64_t)N * 0x9e3779b97f4a7c15ull ^ (uint64_t)K * 0xc2b2ae3d27d4eb4full ^ (uint64_t)(M * 64 + bits * 8 + (dtype == LUTQ_BF16)) * 0x165667b19e3779f9ull ^
+                 (uint64_t)group_size * 0x27d4eb2f165667c5ull;
+    Entry& e = table[(h >> 40) % kEntries];
+    if (e.N != N || e.K != K || e.room != room || e.bits != bits || e.group_size != group_size || e.M != (int)M || e.dtype != (int)dtype || e.cus != cus) {
+        lutq_plan plan{};
+        const bool found = estimate_plan(bits, group_size, M, N, K, dtype, cus, room, fitted_workspace, &plan);
+        e = Entry{N, K, room, bits, group_size, (int)M, (int)dtype, cus, found, plan};
+    }
+    if (e.found) *out = e.plan;
+    return e.found != 0;
 }
 
 lutq_status launch_prepared(const Prepared& q, int bits, int group_size, lutq_dtype dtype, void* stream) {
@@ -1815,17 +1914,16 @@ std::vector<lutq_plan> tune_candidates(int bits, int group_size, int64_t M, int6
     std::vector<lutq_plan> out;
     auto push_unique = [&](const lutq_plan& c) {
         for (const lutq_plan& o : out)
-            if (o.row_blocks_per_wave == c.row_blocks_per_wave && o.grid == c.grid &&
-                o.waves_per_workgroup == c.waves_per_workgroup && o.tiles_in_flight == c.tiles_in_flight &&
-                o.row_groups_per_workgroup == c.row_groups_per_workgroup && o.scheduling == c.scheduling &&
-                o.tiles_per_item == c.tiles_per_item)
-                return;
+            if (same_plan(o, c)) return;
         out.push_back(c);
     };
     // (beyond 32 rows what a call without a plan takes is no plan of its own but the empty one)
     if (M > 32) out.push_back(lutq_plan{});
     lutq_plan def;
     if (lutq_plan_default(bits, group_size, M, N, K, dtype, &def) == LUTQ_OK) push_unique(def);
+    // what a call of up to 32 rows without a plan takes, where that is not the rules' plan
+    lutq_plan estimated;
+    if (M <= 32 && estimated_plan(bits, group_size, M, N, K, dtype, cus, kWorkspaceBytes, false, &estimated)) push_unique(estimated);
     const int64_t nb = N / 16, kt = K / tile_k(bits);
     if (M <= 4 && (K / group_size) % 8 == 0) {
         // work-queue plans with uneven shares: one workgroup per compute unit (or per two), R = 1
