@@ -804,7 +804,25 @@ extern "C" const char* lutq_status_string(lutq_status s) {
 }
 
 namespace {
-bool estimated_plan(int bits, int group_size, int64_t M, int64_t N, int64_t K, lutq_dtype dtype, int cus, size_t workspace_bytes, bool fitted_workspace, lutq_plan* out);
+// Panel launch (panel_kernel): 17..128 activation rows in one pass over the weights.
+struct PanelDecomp {
+    int mb, rp, ks;           // blocks of 32 activation rows per workgroup, panel height / 32, K slices
+    int64_t shares;           // shares of the output channels: 64 rp each
+    int ms;                   // parts of M: mb x 32 rows each
+};
+
+struct Estimated {
+    bool found = false;       // another plan than the rules'
+    lutq_plan plan{};
+    bool panel = false;       // ... or a panel launch, which no plan names (calls of 17..32 rows, not slices of more)
+    PanelDecomp panels{};
+};
+Estimated estimated_launch(int bits, int group_size, int64_t M, int64_t N, int64_t K, lutq_dtype dtype, int cus, size_t workspace_bytes, bool fitted_workspace);
+bool estimated_plan(int bits, int group_size, int64_t M, int64_t N, int64_t K, lutq_dtype dtype, int cus, size_t workspace_bytes, bool fitted_workspace, lutq_plan* out) {
+    const Estimated e = estimated_launch(bits, group_size, M, N, K, dtype, cus, workspace_bytes, fitted_workspace);
+    if (e.found) *out = e.plan;
+    return e.found;
+}
 
 lutq_plan plan_of(const Decomp& d) {
     return lutq_plan{d.r, d.grid, d.nw, d.stages, d.rs, d.rows ? LUTQ_SCHED_ROWS : d.queue ? LUTQ_SCHED_QUEUE : LUTQ_SCHED_TEAMS, d.it};
@@ -1378,28 +1396,29 @@ lutq_status prepare_matmul(const void* X, const void* packed, const void* scales
 // any number of K slices, up to two workgroups per compute unit; one team per row block of four to sixteen waves.  Only a
 // candidate that this scratch and the instances can run is taken.  The rules stay where they are within a margin: they were
 // measured on the shapes that models have, and the estimates are no better than 7 to 16 %.
-bool estimate_plan(int bits, int group_size, int64_t M, int64_t N, int64_t K, lutq_dtype dtype, int cus, size_t workspace_bytes, bool fitted_workspace, lutq_plan* out) {
+Estimated estimate_launch(int bits, int group_size, int64_t M, int64_t N, int64_t K, lutq_dtype dtype, int cus, size_t workspace_bytes) {
+    Estimated e;
     const int64_t nb = N / 16, kt = K / tile_k(bits);
     const bool bf16 = dtype == LUTQ_BF16, sch = (K / group_size) % 8 == 0;
     const int mb = M > 16 ? 2 : 1;
     const double megabytes = ((double)N * (double)K * bits / 8. + (double)N * (double)(K / group_size) * 2.) * 1e-6;
     const Decomp ruled = ruled_decomp(bits, group_size, M, N, K, bf16, sch, cus, false);
-    if (ruled.queue) return false;
+    if (ruled.queue) return e;
     // (1..4 rows: the rules hold but for shapes that they deal to few workgroups -- 8624 x 14848 M = 2 bf16 55.5 us, one team per row block 22.7)
-    const double margin = M > 4 && !ruled.rows ? 0.87 : 0.8;
-    double best = margin * (ruled.rows ? rows_estimate_us(bits, M, nb, kt, megabytes, ruled.r, ruled.grid, ruled.nw, ruled.ks > 1 ? ruled.ks : 1, cus)
+    const double margin = M <= 4 ? 0.75 : ruled.rows ? 0.8 : 0.82;
+    double now = (ruled.rows ? rows_estimate_us(bits, M, nb, kt, megabytes, ruled.r, ruled.grid, ruled.nw, ruled.ks > 1 ? ruled.ks : 1, cus)
                                        : teams_estimate_us(bits, M, nb, kt, megabytes, ruled.r, ruled.grid, ruled.nw, ruled.rs,
                                                            M > 4 && teams_can_share_x(bits, mb, ruled.rs), cus));
-    bool found = false;
+    double best = margin * now;
     auto consider = [&](double us, const lutq_plan& plan) {
         if (us >= best) return;
         Prepared q{};
         if (prepare_matmul(nullptr, nullptr, nullptr, nullptr, bits, group_size, M, N, K, dtype, nullptr, nullptr, workspace_bytes, &plan, false,
                            cus, &q, true) != LUTQ_OK)
             return;
-        best = us;
-        *out = plan;
-        found = true;
+        best = now = us;
+        e.plan = plan;
+        e.found = true;
     };
     // (beyond 12 us the estimates of one team per row block are too low at 17..32 rows and a long K: 8192 x 28672 M = 32 fp16 44 -> 115 us)
     for (int nw : {4, 5, 6, 8, 12, 16}) {
@@ -1407,13 +1426,14 @@ bool estimate_plan(int bits, int group_size, int64_t M, int64_t N, int64_t K, lu
         const double us = teams_estimate_us(bits, M, nb, kt, megabytes, 1, (int)nb, nw, 1, false, cus);
         if (M <= 4 || us <= 12.) consider(us, lutq_plan{1, (int)nb, nw, 2, 1, LUTQ_SCHED_TEAMS, 0});
     }
-    if (M < 5) return found;
+    if (M < 5) return e;
     for (int side : {4, 8}) {
         const int most = rows_instance_waves(bits, bf16, mb, side);
         for (int nw : {most > 12 ? 12 : most, 8}) {
             if (nw < 4 || nw > most) continue;
             for (int64_t grid : {nb < cus ? nb : (int64_t)cus, (int64_t)2 * cus})
-                if (grid <= nb && nb / grid <= 64)
+                // (with fewer K tiles than waves the estimates are too low: 57104 x 1280 W3 bf16 M = 8 16.1 -> 19.8)
+                if (grid <= nb && nb / grid <= 64 && kt >= nw)
                     consider(rows_estimate_us(bits, M, nb, kt, megabytes, side, (int)grid, nw, 1, cus),
                              lutq_plan{side, (int)grid, nw, 2, (int)(nb / grid), LUTQ_SCHED_ROWS, 0});
             const int64_t shares = (nb + side - 1) / side;
@@ -1425,31 +1445,42 @@ bool estimate_plan(int bits, int group_size, int64_t M, int64_t N, int64_t K, lu
             }
         }
     }
-    return found;
+    // 17..32 rows: the panel launch, with all of K or in K slices, where estimated a good tenth faster than what was chosen so far
+    if (M <= 16 || M * K * 2 >= (int64_t)1 << 31) return e;
+    const size_t room = workspace_bytes > kCounterBytes ? workspace_bytes - kCounterBytes : 0;
+    best = 0.87 * now;
+    for (int rp = 1; rp <= 2; ++rp) {
+        const int64_t shares = (nb + 4 * rp - 1) / (4 * rp);
+        for (int64_t ks = 1; ks <= 32; ++ks) {
+            if (ks > 1 && (shares * ks > cus || ks * kPanelWK > kt || shares * 64 > (int64_t)kCounterBytes || (size_t)(shares * ks) * panel_slot_bytes(1, rp) > room)) break;
+            const double us = panel_estimate_us(bits, bf16, nb, kt, megabytes, rp, ks, cus);
+            if (us < best) {
+                best = us;
+                e.panel = true;
+                e.panels = PanelDecomp{1, rp, (int)ks, shares, 1};
+            }
+        }
+    }
+    return e;
 }
 
 // The same, remembered per thread for the last problems by their sizes and types (the choice takes some ten microseconds).
-bool estimated_plan(int bits, int group_size, int64_t M, int64_t N, int64_t K, lutq_dtype dtype, int cus, size_t workspace_bytes, bool fitted_workspace, lutq_plan* out) {
+Estimated estimated_launch(int bits, int group_size, int64_t M, int64_t N, int64_t K, lutq_dtype dtype, int cus, size_t workspace_bytes, bool fitted_workspace) {
     struct Entry {
         int64_t N, K;
         size_t room;
-        int bits, group_size, M, dtype, cus, found;
-        lutq_plan plan;
+        int bits, group_size, M, dtype, cus;
+        Estimated e;
     };
     constexpr int kEntries = 128;
-    static thread_local Entry table[kEntries];        // (zero: N = 0, which no problem has)
-    // more scratch than any launch uses is the same as that
+    static thread_local Entry table[kEntries] = {};   // (N = 0, which no problem has)
     const size_t room = fitted_workspace ? workspace_bytes : kWorkspaceBytes;
-    uint64_t h = (uint64_t)N * 0x9e3779b97f4a7c15ull ^ (uint64_t)K * 0xc2b2ae3d27d4eb4full ^ (uint64_t)(M * 64 + bits * 8 + (dtype == LUTQ_BF16)) * 0x165667b19e3779f9ull ^
-                 (uint64_t)group_size * 0x27d4eb2f165667c5ull;
-    Entry& e = table[(h >> 40) % kEntries];
-    if (e.N != N || e.K != K || e.room != room || e.bits != bits || e.group_size != group_size || e.M != (int)M || e.dtype != (int)dtype || e.cus != cus) {
-        lutq_plan plan{};
-        const bool found = estimate_plan(bits, group_size, M, N, K, dtype, cus, room, fitted_workspace, &plan);
-        e = Entry{N, K, room, bits, group_size, (int)M, (int)dtype, cus, found, plan};
-    }
-    if (e.found) *out = e.plan;
-    return e.found != 0;
+    const uint64_t h = (uint64_t)N * 0x9e3779b97f4a7c15ull ^ (uint64_t)K * 0xc2b2ae3d27d4eb4full ^ (uint64_t)(M * 64 + bits * 8 + (dtype == LUTQ_BF16)) * 0x165667b19e3779f9ull ^
+                       (uint64_t)group_size * 0x27d4eb2f165667c5ull;
+    Entry& t = table[(h >> 40) % kEntries];
+    if (t.N != N || t.K != K || t.room != room || t.bits != bits || t.group_size != group_size || t.M != (int)M || t.dtype != (int)dtype || t.cus != cus)
+        t = Entry{N, K, room, bits, group_size, (int)M, (int)dtype, cus, estimate_launch(bits, group_size, M, N, K, dtype, cus, room)};
+    return t.e;
 }
 
 lutq_status launch_prepared(const Prepared& q, int bits, int group_size, lutq_dtype dtype, void* stream) {
@@ -1507,13 +1538,6 @@ int slice_rows(int bits, int group_size, int64_t M, int64_t N, int64_t K, bool b
     }
     return have && take ? 64 : 32;
 }
-
-// Panel launch (panel_kernel): 33..128 activation rows in one pass over the weights.
-struct PanelDecomp {
-    int mb, rp, ks;           // blocks of 32 activation rows per workgroup, panel height / 32, K slices
-    int64_t shares;           // shares of the output channels: 64 rp each
-    int ms;                   // parts of M: mb x 32 rows each
-};
 
 // Calls of 33 rows or more without a plan: one pass over the weights measured faster than slices of 32 or 64 rows, but where
 // one row-streaming launch serves up to 64 rows sooner (panel_plan).  us, HBM-cold weights, MI355X, slices -> panel: 8B gate+up W4 fp16
@@ -1636,6 +1660,19 @@ bool panel_plan(int bits, int group_size, int64_t M, int64_t N, int64_t K, lutq_
              xop_bytes(M, K) <= room && wide_rows_us(bf16, M, N, K, cus) <= panel_us_w4(bf16, N, K, cus, *out));
 }
 
+// The same for 17..32 rows: no plan, or the one that stands for none, and none registered.
+bool panel_plan_32(int bits, int group_size, int64_t M, int64_t N, int64_t K, lutq_dtype dtype, const lutq_plan* user_plan, int cus,
+                   size_t workspace_bytes, PanelDecomp* out) {
+    lutq_plan registered;
+    if (user_plan ? !plan_is_zero(*user_plan) &&
+                        !same_plan(*user_plan, plan_of(ruled_decomp(bits, group_size, M, N, K, dtype == LUTQ_BF16, (K / group_size) % 8 == 0, cus, false)))
+                  : plan_table_find(bits, group_size, M, N, K, dtype, &registered) && !plan_is_zero(registered))
+        return false;
+    const Estimated e = estimated_launch(bits, group_size, M, N, K, dtype, cus, workspace_bytes, workspace_bytes != kWorkspaceBytes);
+    if (e.panel) *out = e.panels;
+    return e.panel;
+}
+
 lutq_status launch_panel(const void* X, const void* packed, const void* scales, const void* lut, int bits, int group_size,
                          int64_t M, int64_t N, int64_t K, lutq_dtype dtype, void* Y, void* workspace, void* stream, bool pairs,
                          const PanelDecomp& d) {
@@ -1682,6 +1719,16 @@ lutq_status matmul_sliced(const void* X, const void* packed, const void* scales,
     // over the weights), one launch each on the same stream (the weights are streamed once per slice).  Every
     // slice is validated before the first launch.
     int64_t step = 32;
+    const bool arguments_ok = packed && scales && lut && workspace && aligned16(X) && aligned16(packed) && aligned16(scales) && aligned16(Y) &&
+                              aligned16(workspace) && (reinterpret_cast<uintptr_t>(lut) & 1u) == 0 &&
+                              workspace_bytes >= (fitted_workspace ? kCounterBytes : kWorkspaceBytes);
+    if (M > 16 && M <= 32 && !rowlut && arguments_ok && check_problem(bits, group_size, N, K) == LUTQ_OK && (dtype == LUTQ_F16 || dtype == LUTQ_BF16)) {
+        // (any other call gets its status where the launch is prepared)
+        const DeviceInfo di = device_info();
+        PanelDecomp pd;
+        if (di.ok && panel_plan_32(bits, group_size, M, N, K, dtype, user_plan, di.cus, fitted_workspace ? workspace_bytes : kWorkspaceBytes, &pd))
+            return launch_panel(X, packed, scales, lut, bits, group_size, M, N, K, dtype, Y, workspace, stream, pairs, pd);
+    }
     if (M > 32) {
         lutq_status st = check_problem(bits, group_size, N, K);
         if (st != LUTQ_OK) return st;

@@ -5,8 +5,8 @@
 // units of 16, K 1024 to 28672, all bit widths, groups and types) they took 20.5 % longer than the best of about 23 plans timed,
 // up to 3 times (7024 x 26624 group 256, W4 fp16, M = 31: 97.4 us, row streaming in K slices 32.9); on 5603 of 1..4 rows 5.7 %.
 // Fitted by least squares of the relative error to 91 900 and 78 000 timings (HBM-cold weights, MI355X); the estimates are off by
-// 7 to 16 %.  On the half of the problems that was not fitted to, the plan chosen takes 2.9 % longer than the best one timed (14.7 %
-// less than the rules'), with 3 % of the problems more than 3 % slower than under the rules.
+// 7 to 16 %.  On the half of the problems of 5..32 rows that was not fitted to, the plan chosen (with the margins of lutq_api.hip) takes 14 % less
+// than the rules', with 0.8 % of the problems more than 3 % slower and 0.14 % more than 10 %.
 #pragma once
 
 #include <stdint.h>
@@ -25,24 +25,37 @@ static const double kRowsFit[3][2][9] = {
      {3.2231, 0.0000, 0.7073, 0.1668, 0.0090, 0.0497, 1.6573, 0.0367, 0.1003}},  // 4 bits
 };
 // Teams: fixed; workgroups per compute unit; pairs of them; K tiles of a wave times R; K tiles of a wave, waves, workgroups per unit and
-// R; the same without R (activations; once per K part where they are shared); waves per unit; partial sums across workgroups; megabytes.
+// R; the same without R (activations: once per K part where they are shared, by the share of the class's rows); waves per unit; partial sums across workgroups; megabytes.
 // [bits - 2][1..2, 3..4, 5..8, 9..16, 17..32 rows]
 static const double kTeamsFit[3][5][9] = {
     {{1.6409, 0.0654, 1.4913, 0.1391, 0.0414, 0.0000, 0.0244, 5.2359, 0.1070},
-     {1.9096, 0.0743, 1.2368, 0.1239, 0.0456, 0.0007, 0.0350, 5.0144, 0.1273},
-     {2.0780, 0.2659, 1.0915, 0.1107, 0.0492, 0.0248, 0.0188, 5.2675, 0.0996},
-     {2.4407, 0.8836, 0.0000, 0.0687, 0.0453, 0.1079, 0.0403, 6.4777, 0.0974},
-     {2.5104, 1.1028, 0.0000, 0.0464, 0.0618, 0.2342, 0.0551, 5.4605, 0.1705}},  // 2 bits
+     {1.8954, 0.0712, 1.2359, 0.1263, 0.0441, 0.0046, 0.0342, 5.0205, 0.1237},
+     {2.1169, 0.2716, 1.0189, 0.1114, 0.0462, 0.0427, 0.0148, 5.2647, 0.0894},
+     {2.3578, 0.9090, 0.0000, 0.0738, 0.0440, 0.1493, 0.0412, 6.4583, 0.0916},
+     {2.5721, 1.1437, 0.0318, 0.0536, 0.0611, 0.3182, 0.0422, 5.4064, 0.1625}},  // 2 bits
     {{2.3574, 0.0000, 0.3799, 0.1997, 0.0537, 0.0000, 0.0586, 5.1606, 0.0854},
      {2.5379, 0.0000, 0.2058, 0.1476, 0.0642, 0.0000, 0.0669, 5.2634, 0.0955},
-     {2.9110, 0.0000, 0.3815, 0.0894, 0.0766, 0.0009, 0.0424, 5.3716, 0.1165},
-     {2.4949, 0.5909, 0.0000, 0.0922, 0.0689, 0.0822, 0.0750, 6.3849, 0.1122},
-     {2.2451, 0.9636, 0.1101, 0.0626, 0.1058, 0.2136, 0.0596, 5.5085, 0.0807}},  // 3 bits
-    {{1.5471, 0.0423, 1.6155, 0.1086, 0.0260, 0.0044, 0.0022, 5.3370, 0.0711},
-     {1.6524, 0.0423, 1.4947, 0.0915, 0.0291, 0.0064, 0.0057, 5.1905, 0.0743},
-     {1.9126, 0.0000, 1.3596, 0.0645, 0.0370, 0.0163, 0.0000, 5.4496, 0.0561},
-     {2.4709, 0.0000, 0.7909, 0.0061, 0.0453, 0.0489, 0.0000, 5.4751, 0.0485},
-     {2.8904, 0.5873, 0.0000, 0.0096, 0.0410, 0.1313, 0.0000, 5.6291, 0.0558}},  // 4 bits
+     {2.8459, 0.0000, 0.3825, 0.1002, 0.0707, 0.0179, 0.0379, 5.4114, 0.1036},
+     {2.5230, 0.5696, 0.0000, 0.0872, 0.0674, 0.1206, 0.0700, 6.3827, 0.1022},
+     {2.1240, 0.7204, 0.5162, 0.0553, 0.1022, 0.3028, 0.0537, 5.5270, 0.0800}},  // 3 bits
+    {{1.5489, 0.0440, 1.6252, 0.1075, 0.0267, 0.0043, 0.0024, 5.3358, 0.0724},
+     {1.6439, 0.0389, 1.4969, 0.0923, 0.0286, 0.0086, 0.0057, 5.1918, 0.0730},
+     {1.9103, 0.0000, 1.3233, 0.0651, 0.0364, 0.0237, 0.0000, 5.4417, 0.0533},
+     {2.5424, 0.0000, 0.7121, 0.0038, 0.0446, 0.0690, 0.0000, 5.4326, 0.0451},
+     {2.8315, 0.6381, 0.0000, 0.0000, 0.0425, 0.1783, 0.0000, 5.6294, 0.0525}},  // 4 bits
+};
+
+// Panels of 17..32 rows (one block of 32): rounds of workgroups; rounds times K tiles of a wavefront, 32 and 64 channels; K slices: fixed, per
+// slice, per slice and 32 channels; megabytes; rounds of 64 channels.  (4241 drawn problems, 20 000 timings; 5 to 7 % off.  Where
+// scale rows are long -- group 32 and K >= 20000 -- row streaming has no room for them in LDS: 4272 x 22272 group 32 W2 fp16 M = 23 65.7 -> 19.3 us.)
+// [bits - 2][fp16, bf16]
+static const double kPanelFit[3][2][8] = {
+    {{3.4259, 1.5523, 2.3415, 2.1674, 0.1105, 0.0710, 0.0794, 0.5328},
+     {3.2026, 2.1303, 3.5668, 2.1872, 0.1366, 0.0533, 0.0966, 0.4059}},  // 2 bits: fp16, bf16
+    {{3.3496, 1.9388, 3.2046, 2.1605, 0.1118, 0.0620, 0.0755, 0.7623},
+     {3.4298, 2.4676, 4.2472, 1.9216, 0.1600, 0.0329, 0.0879, 0.8455}},  // 3 bits: fp16, bf16
+    {{3.5020, 1.0709, 1.7295, 2.0795, 0.1202, 0.0760, 0.0700, 0.4264},
+     {3.5226, 1.3007, 2.1226, 2.0311, 0.1346, 0.0687, 0.0752, 0.5778}},  // 4 bits: fp16, bf16
 };
 
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
@@ -59,13 +72,22 @@ inline double rows_estimate_us(int bits, int64_t M, int64_t nb, int64_t kt, doub
 
 // r row blocks per wave, rs teams of nw / rs waves, `grid` workgroups; shared: the teams' activations go through LDS once
 inline double teams_estimate_us(int bits, int64_t M, int64_t nb, int64_t kt, double megabytes, int r, int grid, int nw, int rs, bool shared, int cus) {
-    const double* f = kTeamsFit[bits - 2][M <= 2 ? 0 : M <= 4 ? 1 : M <= 8 ? 2 : M <= 16 ? 3 : 4];
+    static const double kMost[5] = {2., 4., 8., 16., 32.};
+    const int c = M <= 2 ? 0 : M <= 4 ? 1 : M <= 8 ? 2 : M <= 16 ? 3 : 4;
+    const double* f = kTeamsFit[bits - 2][c];
     const int64_t sets = nb / r / rs;
     const bool split = grid != sets;
     const double per = (double)ceil_div(grid, cus), ks = (double)(nw / rs);
     const double tiles = (double)ceil_div(split ? ceil_div(sets * kt, grid) : kt, nw / rs);
     return f[0] + f[1] * per + f[2] * (double)ceil_div(ceil_div(grid, cus), 2) + f[3] * tiles * r + f[4] * per * tiles * nw * r +
-           f[5] * per * tiles * (shared ? ks : (double)nw) + f[6] * nw * per + (split ? f[7] : 0.) + f[8] * megabytes;
+           f[5] * per * tiles * (shared ? ks : (double)nw) * (double)M / kMost[c] + f[6] * nw * per + (split ? f[7] : 0.) + f[8] * megabytes;
+}
+
+// rp: panel height / 32; a workgroup is two panels by four parts of K
+inline double panel_estimate_us(int bits, bool bf16, int64_t nb, int64_t kt, double megabytes, int rp, int64_t ks, int cus) {
+    const double* f = kPanelFit[bits - 2][bf16];
+    const double rounds = (double)ceil_div(ceil_div(nb, 4 * rp) * ks, cus), tiles = (double)ceil_div(ceil_div(kt, ks), 4);
+    return rounds * (f[0] + (rp == 1 ? f[1] * tiles : f[2] * tiles + f[7])) + (ks > 1 ? f[3] + (double)ks * (f[4] + f[5] * rp) : 0.) + f[6] * megabytes;
 }
 
 }  // namespace lutq

@@ -12,6 +12,9 @@ from test_gpu_parity import check_y
 SHAPES = [(4, 256, 22, 1328, 23296, "bf16"), (2, 64, 21, 1136, 13312, "f16"), (3, 32, 20, 2368, 4096, "f16"), (4, 64, 13, 1248, 21504, "bf16"),
           (2, 32, 9, 21904, 1536, "bf16"), (3, 64, 15, 8880, 4352, "bf16"), (4, 256, 12, 12304, 1536, "bf16"), (2, 64, 14, 14256, 3328, "bf16"),
           (4, 256, 17, 26704, 1792, "f16"), (3, 32, 9, 5072, 1536, "bf16"), (4, 64, 11, 10304, 1280, "f16"), (3, 256, 10, 22672, 1536, "bf16"),
+          # panels of one block of 32 rows, with and without K slices
+          (4, 32, 17, 1072, 22528, "f16"), (2, 32, 25, 2128, 12288, "bf16"), (3, 64, 32, 4272, 8192, "f16"), (4, 64, 27, 9200, 3584, "bf16"),
+          (2, 32, 32, 1152, 20992, "f16"), (3, 32, 18, 6000, 5376, "bf16"),
           (4, 128, 6, 4448, 11648, "bf16"), (2, 32, 1, 19056, 1024, "f16"), (4, 32, 2, 11536, 3968, "f16"), (3, 64, 3, 9040, 2560, "bf16")]
 
 
