@@ -18,12 +18,12 @@
 //   * The tables hold 16-bit pairs at every type: bf16 pairs are widened in registers, since LDS (operands, lookups) and not
 //     the vector unit is what the matrix instructions wait for here.
 //   * What bounds it: no unit is full.  8B gate+up, M = 128, W4 fp16, 42 us (two slices of 64 rows on the row-streaming kernel took
-//     65.0; the dense fp16 product of the same shape 56): matrix units busy 42 % of a compute unit's time, LDS 42 %, vector units
-//     27 %; a wavefront issues 31 % of its time, waits at s_waitcnt 37 % and to issue 32 %.  Builds with parts left out: the matrix
-//     instructions and the reduction alone take 27.5 us, with the lookups and operand reads 28.9; the staging of the activations adds
-//     8-11 us, the pairs' handshake 2, the weight loads 3.  Deeper activation prefetch, K ranges walked from a different start per
-//     workgroup, and issue priority for the wavefront that is behind changed nothing.  8B down, M = 64: 19 / 39 / 23 %, at
-//     s_waitcnt 49 %; 70B o, W3 bf16, M = 100: 23 / 40 / 50 %.
+//     65.0; the dense fp16 product of the same shape 56).  The matrix instructions alone take 21 us of it on 224 compute units (1.66 PFLOP/s is what
+//     32x32x16 reaches here), launch, table and reduction 6.  Counters of the build before the waits below were taken out: matrix units busy 42 %
+//     of a compute unit's time, LDS 42 %, vector units 27 %; a wavefront issues 31 % of its time, waits at s_waitcnt 37 % and to issue
+//     32 %.  The waits that could be taken out (scales behind a branch, one loop for both looks at the partner's words) gave 3-8 %.  What did not:
+//     operands two units ahead and two sets of table values (M = 64 27 -> 28 us), deeper activation and weight prefetch (0.96-1.0), K ranges walked from a
+//     different start per workgroup, issue priority for the wavefront that is behind.
 //   * K parts are added in order through LDS at the end.  Where panels are too few to fill the chip, K is also cut into KS
 //     slices across workgroups: partial sums go to global slots, one arrival counter per (share, wavefront), and whichever
 //     slice's wavefront arrives last adds the slots in slice order (the protocol of matmul_kernel's fix-up: nobody waits).
@@ -85,6 +85,7 @@ struct PanelParams {
 };
 
 constexpr int kAuxDevice = 16;   // sc1: past the compute unit's and the die's own caches, what agent-scope atomic accesses use
+constexpr int kPanelPark = 2048;      // LDS bytes per wavefront for parked scales: 64 rows' eight scales, and as much that is never read
 constexpr int kPanelQuarter = 1088;   // LDS bytes from one parked quarter tile to the next
 constexpr int kPanelWN = 2, kPanelWK = 4, kPanelWaves = kPanelWN * kPanelWK;
 // columns of K per activation chunk
@@ -98,14 +99,14 @@ __host__ __device__ constexpr int panel_stages(int bits, int mb, int rp) { retur
 __host__ __device__ constexpr bool panel_instance_exists(int bits, int mb, int rp) { return !(bits == 3 && mb == 4 && rp == 2); }
 __host__ __device__ constexpr int panel_xbuf_bytes(int mb) { return 32 * mb * panel_kc(mb) * 2; }
 // [table, 256-byte entry stride][per K part: two activation buffers], of which the final reduction takes four tiles' sums; then
-// [per wavefront: 64 rows' eight scales, 1 KiB][per wavefront: two progress words]
+// [per wavefront: 64 rows' eight scales, kPanelPark][per wavefront: two progress words]
 template <int BITS>
 __host__ __device__ constexpr int panel_park_off(int mb) {
     const int n = lut_row_table_bytes<BITS>() + kPanelWK * 2 * panel_xbuf_bytes(mb), red = 4 * kPanelWaves * 4 * kPanelQuarter;
     return n > red ? n : red;
 }
 template <int BITS>
-__host__ __device__ constexpr int panel_lds_bytes(int mb) { return panel_park_off<BITS>(mb) + kPanelWaves * 1024 + 128; }
+__host__ __device__ constexpr int panel_lds_bytes(int mb) { return panel_park_off<BITS>(mb) + kPanelWaves * kPanelPark + 128; }
 __host__ __device__ constexpr size_t panel_slot_bytes(int mb, int rp) { return (size_t)rp * mb * 8 * 1024; }
 
 // SCH: scales are fetched eight at a time per row (K / group a multiple of 8) and parked in LDS, else tile by tile.
@@ -125,6 +126,8 @@ __global__ __launch_bounds__(64 * kPanelWaves) void panel_kernel(const PanelPara
     constexpr int SL = KC / 8;                         // 16-byte slots of one row of a chunk
     constexpr int XL = MB * SL / 4;                    // activation loads per wavefront and chunk
     constexpr int XB = panel_xbuf_bytes(MB);
+    // the next tile's scales are asked for a tile ahead; 128 rows by 64 channels, and 96 at 3 bits, have no registers for that
+    constexpr bool CHUNK_EARLY = !(RP == 2 && (MB == 4 || (MB == 3 && BITS == 3)));
     static_assert(CH % 2 == 0 && (CH * P) % D == 0, "buffer and register rings restart with every round of P tiles");
 
     asm volatile("" ::"s"(p.X), "s"(p.packed), "s"(p.scales), "s"(p.lut), "s"(p.Y), "s"(p.packed_bytes), "s"(p.scale_bytes),
@@ -155,8 +158,11 @@ __global__ __launch_bounds__(64 * kPanelWaves) void panel_kernel(const PanelPara
     // the slice's tiles over the four K parts
     const int st_n = p.TS + (slice < p.KSB ? 1 : 0);
     const int st_0 = slice * p.TS + (slice < p.KSB ? slice : p.KSB);
-    const int ka = st_0 + (st_n / kPanelWK) * kp + (kp < st_n % kPanelWK ? kp : st_n % kPanelWK);
-    const int len = st_n / kPanelWK + (kp < st_n % kPanelWK ? 1 : 0);
+    // (from 65 rows up the first two parts, whose wavefronts are the older ones on their SIMDs and run ahead, get up to three
+    // sixteenths more: 8B gate+up M = 128 42.7 -> 42.2 us, 70B gate+up 154.9 -> 151.0, 70B o W3 bf16 M = 100 32.9 -> 31.6)
+    const int skew = MB > 2 ? st_n / kPanelWK * 3 / 16 : 0;
+    const int ka = st_0 + (st_n / kPanelWK) * kp + (kp < st_n % kPanelWK ? kp : st_n % kPanelWK) + (kp == 2 ? 2 * skew : (kp & 1) * skew);
+    const int len = st_n / kPanelWK + (kp < st_n % kPanelWK ? 1 : 0) + (kp < 2 ? skew : -skew);
     // a row block beyond the last one gets a base of exactly 2 GiB: every offset formed from it stays out of range
     uint32_t wbase[2 * RP];
 #pragma unroll
@@ -182,7 +188,7 @@ __global__ __launch_bounds__(64 * kPanelWaves) void panel_kernel(const PanelPara
         WFrag<BITS> w[2 * RP];
         ScaleWords<NS> s[SCH ? 1 : RP];
     };
-    char* park = smem + panel_park_off<BITS>(MB) + wave * 1024;
+    char* park = smem + panel_park_off<BITS>(MB) + wave * kPanelPark;
     u32x4 chunk[RP];                                   // SCH: the next eight scales of row l32 of each half panel
     auto load_stage = [&](Stage& st, int i) {           // tile i of the wavefront's range; nothing beyond the last
         const bool in = i < len;
@@ -196,7 +202,7 @@ __global__ __launch_bounds__(64 * kPanelWaves) void panel_kernel(const PanelPara
             load_scales<NS>(st.s[rp], rS, in ? slane + (uint32_t)rp * 32u * (uint32_t)p.SG2 + (uint32_t)(kt / TPS) * (NS * 2) : kOutOfRange);
     };
     // the eight scales that tile i is the first to use, or that the range begins with; any other tile: nothing
-    auto chunk_begins = [&](int i, int kt) { return kt % TPC == 0 || i == 0; };
+    auto chunk_begins = [&](int i, int kt) { return (uint32_t)kt % TPC == 0 || i == 0; };
     auto load_chunk = [&](int i) {
         const int kt = ka + i;
         const bool in = i < len && chunk_begins(i, kt);
@@ -276,7 +282,7 @@ __global__ __launch_bounds__(64 * kPanelWaves) void panel_kernel(const PanelPara
     // waiting for anything later: neither can wait for ever.)  The K parts run free of each other, so that one part's LDS
     // and memory phases fall into another's multiplications (a workgroup barrier per chunk: 4.4 us per K tile and wavefront at
     // M = 128 with the taller panel, this 3.6).
-    uint32_t* flags = reinterpret_cast<uint32_t*>(smem + panel_park_off<BITS>(MB) + kPanelWaves * 1024);
+    uint32_t* flags = reinterpret_cast<uint32_t*>(smem + panel_park_off<BITS>(MB) + kPanelWaves * kPanelPark);
     if (tid < 2 * kPanelWaves) flags[tid] = 0;
     uint32_t* own = flags + 2 * wave;
     uint32_t* other = flags + 2 * (wave ^ 1);
@@ -292,13 +298,18 @@ __global__ __launch_bounds__(64 * kPanelWaves) void panel_kernel(const PanelPara
         if (lane == 0) __hip_atomic_store(own + word, (uint32_t)v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         asm volatile("" ::: "memory");
     };
-    // the partner's words are asked for a unit ahead of their use; only if it is late are they asked for again
-    u32x2 seen;
-    auto ask = [&] {
-        seen = __builtin_bit_cast(u32x2, __hip_atomic_load(reinterpret_cast<uint64_t*>(other), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
-    };
+    // the partner's words are asked for ahead of their use; only if it is late are they asked for again
+    // (The first look is straight-line code: with one loop for both looks the wait in front of it was one for every LDS read under way,
+    // twice per chunk.)
+    uint32_t seen[2];
+    auto ask = [&](int word) { seen[word] = __hip_atomic_load(other + word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); };
     auto wait_for = [&](int word, int v) {
-        while ((int)__builtin_amdgcn_readfirstlane(word ? seen.y : seen.x) < v) ask();
+        if ((int)__builtin_amdgcn_readfirstlane(seen[word]) < v) {
+            do {
+                ask(word);
+                asm volatile("" : "+v"(seen[word]));
+            } while ((int)__builtin_amdgcn_readfirstlane(seen[word]) < v);
+        }
         asm volatile("" ::: "memory");
     };
 
@@ -306,6 +317,9 @@ __global__ __launch_bounds__(64 * kPanelWaves) void panel_kernel(const PanelPara
     // unit n + 1 is scaled and unit n + 2's table reads are issued, piece by piece between the matrix instructions: a wavefront
     // issues in order, and whatever stands in front of a matrix instruction keeps the matrix unit waiting.
     constexpr int U = 2 * SPC, UT = CH * U, NM = RP * MB;
+    // units of a chunk: the next chunk is stored at the end of US (with four units early, three before it is read: 12288 x 4096 W4 M = 50
+    // 16.5 -> 15.6 us; with two units the later of the two is 2 % faster); the partner's words are asked for at the start of A_DONE and A_READY
+    constexpr int US = 0, A_DONE = U == 4 ? U - 1 : US, A_READY = U == 4 ? U - 2 : U - 1;
     constexpr int NPC = (BITS == 2 ? 2 : 4) * RP;       // pieces of a unit: one table read (a pair, or at 2 bits a quad) each
     u32x4 b[MB];
     u32x4 a[2][RP];                                    // operands of the unit being multiplied and of the next one
@@ -342,16 +356,19 @@ __global__ __launch_bounds__(64 * kPanelWaves) void panel_kernel(const PanelPara
     // the scales of tile i (stage t): from the parked eight, which are replaced first where the tile is the first to use the next
     auto take_scales = [&](ScaleWords<NS> (&w)[RP], const Stage& t, int i) {
         if constexpr (SCH) {
+            // No branch: where the tile is not the first to use its eight, what is stored goes to the wavefront's other KiB, and
+            // the next eight are asked for at once (or with the tile's first chunk).  Behind a branch the wait for them was one for every load
+            // under way, weights and activations of the tiles ahead among them, once per K tile: with that and the pairs' straight-line look, W4 fp16
+            // 8B gate+up M = 128 42.8 -> 41.3 us, 70B gate+up 157 -> 148, 8B o M = 128 13.6 -> 12.5, down M = 64 21.2 -> 20.0, 12288 x 4096 M = 50 17.3 -> 16.2.
             const int kt = ka + i;
-            if (chunk_begins(i, kt)) {
-                asm volatile("" ::: "memory");          // (LDS operations of one wavefront complete in order)
-                if (h == 0)
+            char* const dst = park + (chunk_begins(i, kt) ? 0 : 1024) + 16 * l32;
+            asm volatile("" ::: "memory");              // (LDS operations of one wavefront complete in order)
 #pragma unroll
-                    for (int rp = 0; rp < RP; ++rp) *reinterpret_cast<u32x4*>(park + rp * 512 + 16 * l32) = chunk[rp];
-                asm volatile("" ::: "memory");
-            }
+            for (int rp = 0; rp < RP; ++rp) *reinterpret_cast<u32x4*>(dst + rp * 512) = chunk[rp];
+            asm volatile("" ::: "memory");
 #pragma unroll
-            for (int rp = 0; rp < RP; ++rp) lds_load_scales<NS>(w[rp], park + rp * 512 + 16 * l32 + ((kt % TPC) / TPS) * (NS * 2));
+            for (int rp = 0; rp < RP; ++rp) lds_load_scales<NS>(w[rp], park + rp * 512 + 16 * l32 + (((uint32_t)kt % TPC) / TPS) * (NS * 2));
+            if constexpr (CHUNK_EARLY) load_chunk(i + 1);
         } else {
 #pragma unroll
             for (int rp = 0; rp < RP; ++rp) w[rp] = t.s[rp];
@@ -369,6 +386,7 @@ __global__ __launch_bounds__(64 * kPanelWaves) void panel_kernel(const PanelPara
         scale(a[0], sw[0], 0, i);
         look(st[0], 0, 1, i);
     }
+    ask(1);
     __builtin_amdgcn_sched_barrier(0);
 
     // tile ti of a round of P (ti is a constant): stage ti; its first chunk asks for the tile P - 1 ahead, after the chunk's
@@ -390,7 +408,8 @@ __global__ __launch_bounds__(64 * kPanelWaves) void panel_kernel(const PanelPara
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const int n = c * U + u, n1 = (n + 1) % UT, n2 = (n + 2) % UT;
-                if (u == SPC - 1 || u == U - 1) ask();
+                if (u == A_DONE) ask(1);
+                if (u == A_READY) ask(0);
 #pragma unroll
                 for (int i = 0; i < NM; ++i) {
                     const int mb = i / RP, rp = i % RP;
@@ -413,16 +432,18 @@ __global__ __launch_bounds__(64 * kPanelWaves) void panel_kernel(const PanelPara
                     }
                     __builtin_amdgcn_sched_barrier(0);
                 }
-                if (u == SPC - 1) {
+                if (u == US) {
                     // chunk g + 1 to the other buffer, chunk g + 1 + D on its way
                     wait_for(1, g);
+                    if constexpr (SCH && !CHUNK_EARLY) {
+                        if (c == 0) load_chunk(t + 1);
+                    }
                     store_x(xr[(R0 + c) % D], (c + 1) & 1);
                     publish(0, g + 1);
                     load_x(xr[(R0 + c) % D], t + (c + 1 + D) / CH, (c + 1 + D) % CH);
                     __builtin_amdgcn_sched_barrier(0);
                     if (c == 0) {
                         load_stage(st[(ti + P - 1) % P], t + P - 1);
-                        if constexpr (SCH) load_chunk(t + 1);
                         __builtin_amdgcn_sched_barrier(0);
                     }
                 }
