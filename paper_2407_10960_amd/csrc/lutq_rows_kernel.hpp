@@ -234,6 +234,7 @@ void rows_kernel(const RowsParams p) {
             for (int mb = 0; mb < MB; ++mb) acc[a][mb] = f32x4{0.f, 0.f, 0.f, 0.f};
 
         Stage st[NST];
+        if constexpr (!XDB)
 #pragma unroll
         for (int a = 0; a < NST; ++a) {
             load_w(st[a], p0, skip, ka, a);
@@ -248,9 +249,20 @@ void rows_kernel(const RowsParams p) {
             for (int mb = 0; mb < MB; ++mb)
                 x[mb] = __builtin_amdgcn_raw_buffer_load_b128(rX, tx + xlane[mb] + (XOP ? MB * 1024u : 64u) * s, 0, kAuxNone);
         };
+        // With a second set the activations are asked for first, as a K tile leaves them under way: loads are waited for in order, and a
+        // wait inside the loop is one for whichever of the two orders that meet at its head is worse.  With the activations last, every K tile
+        // began with a wait for all its weights (N = K = 8192 M = 32 fp16 19.5 -> 18.1 us, 4096 x 14336 15.4 -> 14.6, bf16 12288 x 4096 M = 24
+        // 13.0 -> 12.4).  Without a second set the order of the loop (activations before the last weight tile) measured 0-1 %
+        // faster on a long K and 3-5 % slower on a short one or in bf16 with eight row blocks side by side: weights first there.
 #pragma unroll
         for (int s = 0; s < STEPS; ++s) load_x_step(XDB ? xr[s] : bx[s], ka, s);
         __builtin_amdgcn_sched_barrier(0);
+        if constexpr (XDB)
+#pragma unroll
+        for (int a = 0; a < NST; ++a) {
+            load_w(st[a], p0, skip, ka, a);
+            __builtin_amdgcn_sched_barrier(0);
+        }
         {
             // The pass's scales: rows (rb_first + p0) * 16 onwards, na * 16 rows of SG2 bytes, one contiguous
             // range.  (Every wave is past the previous pass's K loop: its reduction began with a barrier.)
