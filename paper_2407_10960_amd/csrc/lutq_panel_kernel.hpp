@@ -1,4 +1,4 @@
-// The fused kernel for 33 to 128 activation rows, in one pass over the weights.
+// The fused kernel for 33 to 128 activation rows, in one pass over the weights; also for 17 to 32 where estimated to be the fastest.
 //
 // What is computed is that of matmul_kernel (Algorithm 1 of the paper).  From some forty rows up the matrix instructions
 // take longer than the weight stream (8B gate+up at M = 128: 30 GFLOP, 12 us at 2.5 PFLOP/s, against 58.7 MB of weights),
