@@ -195,9 +195,10 @@ typedef struct {
 #define LUTQ_SCHED_QUEUE 2
 #define LUTQ_SCHED_ROWS 3
 
-/* Fills *plan with the library's rules' choice for this problem on the current device.  Up to 32 rows a call with this plan is
- * a call without one: both take another launch where estimated times say that it is clearly faster.  For M > 32 the plan is the decomposition of the slices, the one a plan can
- * ask for (a call without a plan takes all rows in one launch). */
+/* Fills *plan with the choice of the library's rules for this problem on the current device.  Passed back, it is what runs.  A
+ * call without a plan (NULL, or the all-zero plan) takes that launch, or up to 32 rows another where estimated times say that it is
+ * clearly faster.  For M > 32 the plan is the decomposition of the slices, the one a plan can ask for (a call without a plan takes
+ * all rows in one launch). */
 lutq_status lutq_plan_default(int bits, int group_size, int64_t M, int64_t N, int64_t K,
                               lutq_dtype dtype, lutq_plan* plan);
 
@@ -206,7 +207,7 @@ lutq_status lutq_plan_default(int bits, int group_size, int64_t M, int64_t N, in
 lutq_status lutq_plan_default_for(int bits, int group_size, int64_t M, int64_t N, int64_t K,
                                   lutq_dtype dtype, int compute_units, lutq_plan* plan);
 
-/* Whether lutq_matmul_plan would accept `plan` (NULL = the default plan) for this problem on a device
+/* Whether lutq_matmul_plan would accept `plan` (NULL = the library's choice) for this problem on a device
  * with `compute_units` compute units: LUTQ_OK, or the status lutq_matmul_plan would return for the
  * plan and the problem (BITS, GROUP, SHAPE, DTYPE, PLAN).  Host logic only; no device is touched. */
 lutq_status lutq_plan_check(int bits, int group_size, int64_t M, int64_t N, int64_t K, lutq_dtype dtype,
@@ -269,8 +270,8 @@ lutq_status lutq_matmul_plan(const void* X, const void* packed, const void* scal
  * counters + 16 MiB of partial-sum slots), which every GPU the library runs on holds from the first use
  * of the library on it until the process ends.  The call allocates nothing and calls no allocating
  * routine; the first call on a device looks the array's address up once (make that call outside a
- * graph capture).  Every other argument and the result are those of lutq_matmul_plan (plan may be NULL
- * for the default decomposition), bit for bit under the same plan.
+ * graph capture).  Every other argument and the result are those of lutq_matmul_plan, bit for bit under the
+ * same plan (NULL, the library's choice, may be another decomposition here: see below).
  * A launch needs partial-sum slots only when its plan cuts output tiles across workgroups:
  * grid x row groups per workgroup x 2 slots of R x ceil(M/16) x 1 KiB (M capped at 32).  If that exceeds
  * the 16 MiB, a call with a plan returns LUTQ_ERR_SCRATCH before anything is launched (Y untouched), and a

@@ -49,6 +49,13 @@ int lutq_calib_matmul_trace(const void* X, const void* packed, const void* scale
 int lutq_calib_route(int bits, int group_size, int64_t M, int64_t N, int64_t K, int dtype, int compute_units,
                      size_t workspace_bytes, int route[5]);
 
+/* The launch of a call of 1..32 rows with `plan` (NULL: without one; the plan table counts then) on a device with `compute_units`
+ * compute units and a workspace of `workspace_bytes` (at least 64 KiB): *runs = the decomposition that is launched, with every field
+ * given; all zero where it is one that no plan names (panels of 32 rows).  Host logic only, no device is touched.
+ * Return values: 0, or the status lutq_matmul_plan would give the problem and the plan (SHAPE also for M > 32). */
+int lutq_calib_plan(int bits, int group_size, int64_t M, int64_t N, int64_t K, int dtype, int compute_units,
+                    size_t workspace_bytes, const lutq_plan* plan, lutq_plan* runs);
+
 #ifdef __cplusplus
 }
 #endif

@@ -34,6 +34,7 @@ from .binding import (  # noqa: F401
     calib_copy,
     calib_matmul_trace,
     calib_route,
+    calib_plan,
     TRACE_STAMPS,
     EXPORTED_SYMBOLS,
 )

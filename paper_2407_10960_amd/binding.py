@@ -15,7 +15,7 @@ _NATIVE = None       # _lutq_torch: plain calls on the current stream (see _nati
 EXPORTED_SYMBOLS = (
     "lutq_status_string", "lutq_packed_bytes", "lutq_pack", "lutq_unpack", "lutq_workspace_bytes",
     "lutq_plan_default", "lutq_plan_default_for", "lutq_plan_check", "lutq_pack_layout", "lutq_plan_table_set", "lutq_plan_table_lookup", "lutq_matmul", "lutq_matmul_plan", "lutq_matmul_static", "lutq_matmul_channel", "lutq_matmul_pairs", "lutq_matmul_quads", "lutq_tune", "lutq_tune_candidates", "lutq_quantize", "lutq_dequant",
-    "lutq_calib_stream_read", "lutq_calib_copy", "lutq_calib_matmul_trace", "lutq_calib_route",
+    "lutq_calib_stream_read", "lutq_calib_copy", "lutq_calib_matmul_trace", "lutq_calib_route", "lutq_calib_plan",
 )
 
 LUTQ_F16, LUTQ_BF16 = 0, 1
@@ -135,6 +135,8 @@ def load_library():
                                             ctypes.POINTER(_CPlan), vp, sz, ctypes.POINTER(ctypes.c_int)]
     lib.lutq_calib_route.restype = ci
     lib.lutq_calib_route.argtypes = [ci, ci, i64, i64, i64, ci, ci, sz, ctypes.POINTER(ctypes.c_int)]
+    lib.lutq_calib_plan.restype = ci
+    lib.lutq_calib_plan.argtypes = [ci, ci, i64, i64, i64, ci, ci, sz, ctypes.POINTER(_CPlan), ctypes.POINTER(_CPlan)]
     _LIB = lib
     return lib
 
@@ -531,6 +533,19 @@ def calib_route(bits: int, group_size: int, M: int, N: int, K: int, dtype_code: 
     _check(load_library().lutq_calib_route(bits, group_size, M, N, K, dtype_code, compute_units, workspace_bytes, r),
            "lutq_calib_route")
     return tuple(r)
+
+
+def calib_plan(bits: int, group_size: int, M: int, N: int, K: int, dtype_code: int = LUTQ_F16, compute_units: int = 256,
+               workspace_bytes: int | None = None, plan: Plan | None = None) -> Plan:
+    """The launch of a call of 1..32 rows with `plan` (None: without one; registered plans count), every field given; the empty
+    Plan() where it is panels of 32 rows, which no plan names.  Host logic, no device needed."""
+    if workspace_bytes is None:
+        workspace_bytes = lutq_workspace_bytes(N, K, bits, group_size)
+    cp, runs = plan._c() if plan is not None else None, _CPlan()
+    _check(load_library().lutq_calib_plan(bits, group_size, M, N, K, dtype_code, compute_units, workspace_bytes,
+                                          ctypes.byref(cp) if cp is not None else None, ctypes.byref(runs)), "lutq_calib_plan")
+    return Plan(runs.row_blocks_per_wave, runs.grid, runs.waves_per_workgroup, runs.tiles_in_flight,
+                runs.row_groups_per_workgroup, runs.scheduling, runs.tiles_per_item)
 
 
 TRACE_STAMPS = ("start", "arguments arrived", "first loads issued", "table built", "first tile multiplied",

@@ -1197,9 +1197,9 @@ lutq_status prepare_matmul(const void* X, const void* packed, const void* scales
         const int sched = user_plan ? user_plan->scheduling : 0;
         if (sched < 0 || sched > LUTQ_SCHED_ROWS) return LUTQ_ERR_PLAN;
         Decomp q;
-        // no plan, or the one that lutq_plan_default gives, which stands for none: another where estimated to be clearly faster
+        // no plan: another than the rules' where estimated to be clearly faster (a plan that is given means itself, the rules' too)
         lutq_plan estimated;
-        if (!small_scratch && ((sched == 0 && plan_is_empty) || same_plan(*user_plan, plan_of(ruled_decomp(bits, group_size, M, N, K, bf16, sch, di.cus, false)))) &&
+        if (!small_scratch && sched == 0 && plan_is_empty &&
             estimated_plan(bits, group_size, M, N, K, dtype, di.cus, dry && !fitted_workspace ? kWorkspaceBytes : workspace_bytes, fitted_workspace, &estimated))
             return prepare_matmul(X, packed, scales, lut, bits, group_size, M, N, K, dtype, Y, workspace, workspace_bytes, &estimated,
                                   rowlut, dry_run_cus, out, fitted_workspace, false);
@@ -1272,7 +1272,7 @@ lutq_status prepare_matmul(const void* X, const void* packed, const void* scales
             // (a scratch too small for the slices' sums -- the built-in one of lutq_matmul_static -- leaves it to the others)
             const lutq_status rs = prepare_rows(X, packed, scales, lut, bits, group_size, M, N, K, bf16, Y, q, out, false,
                                                 dry ? nullptr : static_cast<char*>(workspace) + kCounterBytes,
-                                                dry ? 0 : workspace_bytes - kCounterBytes, dry);
+                                                dry && !fitted_workspace ? 0 : workspace_bytes - kCounterBytes, dry);
             if (rs == LUTQ_OK) return rs;
             out->rows = false;
             q = Decomp{};
@@ -1660,13 +1660,11 @@ bool panel_plan(int bits, int group_size, int64_t M, int64_t N, int64_t K, lutq_
              xop_bytes(M, K) <= room && wide_rows_us(bf16, M, N, K, cus) <= panel_us_w4(bf16, N, K, cus, *out));
 }
 
-// The same for 17..32 rows: no plan, or the one that stands for none, and none registered.
+// The same for 17..32 rows: no plan from the caller, and none registered.
 bool panel_plan_32(int bits, int group_size, int64_t M, int64_t N, int64_t K, lutq_dtype dtype, const lutq_plan* user_plan, int cus,
                    size_t workspace_bytes, PanelDecomp* out) {
     lutq_plan registered;
-    if (user_plan ? !plan_is_zero(*user_plan) &&
-                        !same_plan(*user_plan, plan_of(ruled_decomp(bits, group_size, M, N, K, dtype == LUTQ_BF16, (K / group_size) % 8 == 0, cus, false)))
-                  : plan_table_find(bits, group_size, M, N, K, dtype, &registered) && !plan_is_zero(registered))
+    if (user_plan ? !plan_is_zero(*user_plan) : plan_table_find(bits, group_size, M, N, K, dtype, &registered) && !plan_is_zero(registered))
         return false;
     const Estimated e = estimated_launch(bits, group_size, M, N, K, dtype, cus, workspace_bytes, workspace_bytes != kWorkspaceBytes);
     if (e.panel) *out = e.panels;
@@ -1915,6 +1913,38 @@ extern "C" int lutq_calib_route(int bits, int group_size, int64_t M, int64_t N, 
     const int out[5] = {slice, one ? d.mb : 0, one ? d.rp : 0, one ? d.ks : 0, one ? d.ms : 0};
     std::copy(out, out + 5, route);
     return st;
+}
+
+extern "C" int lutq_calib_plan(int bits, int group_size, int64_t M, int64_t N, int64_t K, int dtype, int compute_units,
+                               size_t workspace_bytes, const lutq_plan* plan, lutq_plan* runs) {
+    if (!runs) return LUTQ_ERR_NULL;
+    lutq_status st = check_problem(bits, group_size, N, K);
+    if (st != LUTQ_OK) return st;
+    if (M < 1 || M > 32 || compute_units < 1 || compute_units > 4096) return LUTQ_ERR_SHAPE;
+    if (dtype != LUTQ_F16 && dtype != LUTQ_BF16) return LUTQ_ERR_DTYPE;
+    if (workspace_bytes < kCounterBytes) return LUTQ_ERR_WORKSPACE;
+    const lutq_dtype dt = (lutq_dtype)dtype;
+    const bool fitted = workspace_bytes != kWorkspaceBytes;
+    PanelDecomp panels;
+    if (M > 16 && panel_plan_32(bits, group_size, M, N, K, dt, plan, compute_units, workspace_bytes, &panels)) {
+        *runs = lutq_plan{};
+        return LUTQ_OK;
+    }
+    Prepared q{};
+    auto dry = [&](const lutq_plan* p) {
+        return prepare_matmul(nullptr, nullptr, nullptr, nullptr, bits, group_size, M, N, K, dt, nullptr, nullptr, workspace_bytes, p, false,
+                              compute_units, &q, fitted);
+    };
+    lutq_plan registered;
+    if (plan || !plan_table_find(bits, group_size, M, N, K, dt, &registered) || (st = dry(&registered)) != LUTQ_OK) st = dry(plan);
+    if (st != LUTQ_OK) return st;
+    if (q.rows)
+        *runs = lutq_plan{q.r, q.rp.G, q.rp.NW, 2, q.rp.A, LUTQ_SCHED_ROWS, q.rp.KS > 1 ? (q.rp.KT + q.rp.KS - 1) / q.rp.KS : 0};
+    else if (q.queue)
+        *runs = lutq_plan{q.r, q.dp.G, q.dp.NW, 2, q.dp.A, LUTQ_SCHED_QUEUE, q.dp.IT};
+    else
+        *runs = lutq_plan{q.r, q.p.G, q.p.NW, q.stages, q.p.RS, LUTQ_SCHED_TEAMS, 0};
+    return LUTQ_OK;
 }
 
 extern "C" int lutq_calib_matmul_trace(const void* X, const void* packed, const void* scales, const void* lut,

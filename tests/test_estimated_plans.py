@@ -27,9 +27,14 @@ def test_call_without_plan(shape):
     d = DeviceCase(lutq, case)
     first = to_bits(d.matmul(lutq))
     check_y(first, case, str(shape))
-    # the plan that lutq_plan_default gives stands for none; the library's own scratch may lead to another launch
+    # the empty plan stands for none; that of lutq_plan_default means the rules' launch, also on the library's own scratch
+    assert np.array_equal(first, to_bits(d.matmul(lutq, plan=lutq.Plan())))
     plan = lutq.lutq_plan_default(bits, group, M, N, K, 0 if dtype == "f16" else 1)
-    assert np.array_equal(first, to_bits(d.matmul(lutq, plan=plan)))
+    ruled = to_bits(d.matmul(lutq, plan=plan))
+    check_y(ruled, case, f"{shape} {plan}")
+    Y = torch.full((M, N), float("nan"), dtype=d.X.dtype, device="cuda")
+    lutq.lutq_matmul_static(d.X, d.packed, d.S, d.T, bits, group, Y, plan=plan)
+    assert np.array_equal(ruled, to_bits(Y))
     Y = torch.full((M, N), float("nan"), dtype=d.X.dtype, device="cuda")
     lutq.lutq_matmul_static(d.X, d.packed, d.S, d.T, bits, group, Y)
     torch.cuda.synchronize()
