@@ -1631,23 +1631,28 @@ bool plan_is_zero(const lutq_plan& p) {
              p.tiles_per_item);
 }
 
-// Whether a call of M > 32 rows without a plan is one that a registered plan serves: it goes in slices of 32 rows (those of 64 have
-// one decomposition and take no plan from the table) and the entry for 32 rows asks for something that can run in this scratch.
+// Whether a plan is registered for calls of M <= 32 rows and asks for something that the kernels can run in this scratch.
 bool registered_plan_runs(int bits, int group_size, int64_t M, int64_t N, int64_t K, lutq_dtype dtype, int cus, size_t workspace_bytes) {
     lutq_plan registered;
-    if (!plan_table_find(bits, group_size, 32, N, K, dtype, &registered) || plan_is_zero(registered)) return false;
-    lutq_status st;
-    if (slice_rows(bits, group_size, M, N, K, dtype == LUTQ_BF16, nullptr, false, cus, &st) != 32) return false;
+    if (!plan_table_find(bits, group_size, M, N, K, dtype, &registered) || plan_is_zero(registered)) return false;
     Prepared q{};
-    return prepare_matmul(nullptr, nullptr, nullptr, nullptr, bits, group_size, 32, N, K, dtype, nullptr, nullptr, workspace_bytes,
+    return prepare_matmul(nullptr, nullptr, nullptr, nullptr, bits, group_size, M, N, K, dtype, nullptr, nullptr, workspace_bytes,
                           &registered, false, cus, &q, true) == LUTQ_OK;
+}
+
+// Whether a call of M > 32 rows without a plan is one that a registered plan serves: it goes in slices of 32 rows (those of 64 have
+// one decomposition and take no plan from the table) and the entry for 32 rows can run.
+bool registered_slices_run(int bits, int group_size, int64_t M, int64_t N, int64_t K, lutq_dtype dtype, int cus, size_t workspace_bytes) {
+    lutq_status st;
+    return registered_plan_runs(bits, group_size, 32, N, K, dtype, cus, workspace_bytes) &&
+           slice_rows(bits, group_size, M, N, K, dtype == LUTQ_BF16, nullptr, false, cus, &st) == 32;
 }
 
 // Whether a call of M > 32 rows goes to the panel kernel: no plan from the caller, none registered that serves it, and no
 // row-streaming launch that is the faster.
 bool panel_plan(int bits, int group_size, int64_t M, int64_t N, int64_t K, lutq_dtype dtype, const lutq_plan* user_plan, int cus,
                 size_t workspace_bytes, PanelDecomp* out) {
-    if (user_plan ? !plan_is_zero(*user_plan) : registered_plan_runs(bits, group_size, M, N, K, dtype, cus, workspace_bytes)) return false;
+    if (user_plan ? !plan_is_zero(*user_plan) : registered_slices_run(bits, group_size, M, N, K, dtype, cus, workspace_bytes)) return false;
     const size_t room = workspace_bytes > kCounterBytes ? workspace_bytes - kCounterBytes : 0;
     if (!panel_decomp(bits, M, N, K, cus, room, out)) return false;
     // 4 bits, up to 64 rows: one row-streaming launch is the alternative, where it exists and its copy of the activations fits the
@@ -1660,15 +1665,14 @@ bool panel_plan(int bits, int group_size, int64_t M, int64_t N, int64_t K, lutq_
              xop_bytes(M, K) <= room && wide_rows_us(bf16, M, N, K, cus) <= panel_us_w4(bf16, N, K, cus, *out));
 }
 
-// The same for 17..32 rows: no plan from the caller, and none registered.
+// The same for 17..32 rows: no plan from the caller, none registered that can run, and panels estimated to be the fastest.
 bool panel_plan_32(int bits, int group_size, int64_t M, int64_t N, int64_t K, lutq_dtype dtype, const lutq_plan* user_plan, int cus,
                    size_t workspace_bytes, PanelDecomp* out) {
-    lutq_plan registered;
-    if (user_plan ? !plan_is_zero(*user_plan) : plan_table_find(bits, group_size, M, N, K, dtype, &registered) && !plan_is_zero(registered))
-        return false;
+    if (user_plan && !plan_is_zero(*user_plan)) return false;
     const Estimated e = estimated_launch(bits, group_size, M, N, K, dtype, cus, workspace_bytes, workspace_bytes != kWorkspaceBytes);
-    if (e.panel) *out = e.panels;
-    return e.panel;
+    if (!e.panel || (!user_plan && registered_plan_runs(bits, group_size, M, N, K, dtype, cus, workspace_bytes))) return false;
+    *out = e.panels;
+    return true;
 }
 
 lutq_status launch_panel(const void* X, const void* packed, const void* scales, const void* lut, int bits, int group_size,

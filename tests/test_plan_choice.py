@@ -3,6 +3,10 @@ one, or with the empty one, takes the library's choice."""
 import numpy as np
 import pytest
 
+import lutq_inputs as gen
+from gpu_util import DeviceCase, to_bits
+from test_gpu_parity import check_y
+
 
 def problems(seed, count, m_min=1):
     """(bits, group, M, N, K, dtype, compute units)"""
@@ -39,3 +43,48 @@ def test_a_given_plan_is_what_runs(lutq, small_scratch):
             assert lutq.calib_plan(*p, ws, plan=free) == free, p
             others += free != rules
     assert others > 100 and panels > 50
+
+
+# panels of 32 rows are the library's choice on these: (bits, group, M, N, K, dtype)
+PANELS = [(4, 32, 17, 1072, 22528, 0), (3, 64, 32, 4272, 8192, 0), (2, 32, 32, 1152, 20992, 0)]
+IMPOSSIBLE = ((1, 0, 8, 2, 3), (1, 256, 16, 2, 1, 2, 4), (0, 0, 0, 0, 0, 7))   # waves that are no three teams, a queue, no scheduling
+
+
+@pytest.mark.parametrize("p", PANELS)
+def test_a_registered_plan_keeps_a_call_off_the_panels_only_if_it_runs(lutq, p):
+    bits, group, M, N, K, dt = p
+
+    def registered(plan, m_max=32):
+        try:
+            lutq.lutq_plan_table_set([(bits, group, dt, 1, m_max, N, K, plan)])
+            return lutq.calib_plan(*p)
+        finally:
+            lutq.lutq_plan_table_set([])
+
+    assert lutq.calib_plan(*p) == lutq.Plan()
+    rules = lutq.lutq_plan_default_for(*p)
+    assert registered(rules) == rules
+    assert registered(rules, 16) == lutq.Plan() and registered(lutq.Plan()) == lutq.Plan()
+    for plan in IMPOSSIBLE:
+        assert lutq.lutq_plan_check(*p, 256, lutq.Plan(*plan)) == 10
+        assert registered(lutq.Plan(*plan)) == lutq.Plan(), plan
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("p", PANELS)
+def test_registered_plans_give_the_bits_of_the_same_plan_passed(lutq, p):
+    bits, group, M, N, K, dt = p
+    c = gen.make_case(N + M, M, N, K, bits, group, "bf16" if dt else "f16", "random_index")
+    d = DeviceCase(lutq, c)
+    free = to_bits(d.matmul(lutq))
+    check_y(free, c, str(p))
+    rules = lutq.lutq_plan_default(*p)
+    given = to_bits(d.matmul(lutq, plan=rules))
+    check_y(given, c, f"{p} {rules}")
+    for plan, want in [(rules, given), (lutq.Plan(), free)] + [(lutq.Plan(*q), free) for q in IMPOSSIBLE]:
+        try:
+            lutq.lutq_plan_table_set([(bits, group, dt, 1, 32, N, K, plan)])
+            assert np.array_equal(to_bits(d.matmul(lutq)), want), plan
+        finally:
+            lutq.lutq_plan_table_set([])
+    assert not np.array_equal(free, given)           # (two orders of summation)
