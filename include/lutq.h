@@ -331,9 +331,9 @@ lutq_status lutq_matmul_quads(const void* X, const void* packed, const void* sca
                               void* workspace, size_t workspace_bytes, void* stream);
 
 /* Instance selection by measurement (Section 4.1: the fastest kernel configuration is picked per
- * shape; Section 3.3: how the K range is cut across workgroups is part of that choice).  Times the
- * default plan and the candidate plans that lutq_tune_candidates lists, first with a few launches
- * each, then the eight fastest and the default in three rounds of `reps` launches (the minimum per
+ * shape; Section 3.3: how the K range is cut across workgroups is part of that choice).  Times what a
+ * call without a plan launches and the other plans that lutq_tune_candidates lists, first with a few launches
+ * each, then the eight fastest and that launch in three rounds of `reps` launches (the minimum per
  * plan counts), with events on `stream`, and
  * writes the fastest to *best and, if best_us is not NULL, its microseconds per launch to *best_us.
  *   packed, scales  host arrays of `ring` >= 1 device pointers each: weight sets of the same shape
@@ -349,9 +349,9 @@ lutq_status lutq_tune(const void* X, const void* const* packed, const void* cons
                       lutq_dtype dtype, void* Y, void* workspace, size_t workspace_bytes, void* stream,
                       int reps, lutq_plan* best, float* best_us);
 
-/* The plans lutq_tune tries for this problem on the current device, the default plan first.  For M > 32
- * that is the all-zero plan, which asks for what a call without a plan takes (a registered all-zero plan
- * is the library's choice, too); lutq_plan_default's plan of the slices comes second.
+/* The plans lutq_tune tries for this problem on the current device, what a call without a plan launches first: the
+ * all-zero plan, followed by lutq_plan_default's, where the two are different launches (M > 32, and up to 32 rows where
+ * estimated times choose), else lutq_plan_default's.  (A registered all-zero plan is the library's choice, too.)
  * Writes min(*count, capacity) of them to plans (host) and their number to *count; plans may be
  * NULL when capacity is 0.  Some of them have no kernel instance: lutq_matmul_plan answers those
  * with LUTQ_ERR_PLAN, and lutq_tune skips them. */

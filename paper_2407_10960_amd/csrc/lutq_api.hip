@@ -1985,26 +1985,26 @@ extern "C" int lutq_calib_matmul_trace(const void* X, const void* packed, const 
 
 namespace {
 
-// Candidate work decompositions of lutq_tune: the default plan first (beyond 32 rows the empty plan, which is what a call
-// without one takes, then that of its slices), then every combination of row blocks per wave, teams, waves per team, grid (one workgroup per set of row groups, or 1/2, 1, 2, 4
+// Candidate work decompositions of lutq_tune: what a call without a plan launches first (as the empty plan where that is not
+// the rules' plan, which comes second then), then every combination of row blocks per wave, teams, waves per team, grid (one workgroup per set of row groups, or 1/2, 1, 2, 4
 // workgroups per compute unit with the K range cut where they do not divide the tiles) and pipeline
 // depth that passes the ranges of lutq_plan.  Combinations without a kernel instance are rejected by
 // lutq_matmul_plan when they are tried.
 std::vector<lutq_plan> tune_candidates(int bits, int group_size, int64_t M, int64_t N, int64_t K, lutq_dtype dtype,
                                        int cus) {
     std::vector<lutq_plan> out;
+    const Estimated e = M > 32 ? Estimated{} : estimated_launch(bits, group_size, M, N, K, dtype, cus, kWorkspaceBytes, false);
     auto push_unique = [&](const lutq_plan& c) {
+        if (e.found && !e.panel && same_plan(e.plan, c)) return;        // (the empty plan's launch)
         for (const lutq_plan& o : out)
             if (same_plan(o, c)) return;
         out.push_back(c);
     };
-    // (beyond 32 rows what a call without a plan takes is no plan of its own but the empty one)
-    if (M > 32) out.push_back(lutq_plan{});
+    // the call without a plan first: as the empty plan where that is another launch than the rules' plan, which comes next
+    if (M > 32 || e.found || e.panel) out.push_back(lutq_plan{});
     lutq_plan def;
     if (lutq_plan_default(bits, group_size, M, N, K, dtype, &def) == LUTQ_OK) push_unique(def);
-    // what a call of up to 32 rows without a plan takes, where that is not the rules' plan
-    lutq_plan estimated;
-    if (M <= 32 && estimated_plan(bits, group_size, M, N, K, dtype, cus, kWorkspaceBytes, false, &estimated)) push_unique(estimated);
+    if (e.panel && e.found) push_unique(e.plan);          // (the best that was estimated before panels were)
     const int64_t nb = N / 16, kt = K / tile_k(bits);
     if (M <= 4 && (K / group_size) % 8 == 0) {
         // work-queue plans with uneven shares: one workgroup per compute unit (or per two), R = 1
@@ -2110,12 +2110,12 @@ extern "C" lutq_status lutq_tune(const void* X, const void* const* packed, const
     if (ring < 1 || reps < 1) return LUTQ_ERR_SHAPE;
     for (int i = 0; i < ring; ++i)
         if (!packed[i] || !scales[i]) return LUTQ_ERR_NULL;
-    lutq_plan def;
-    lutq_status st = lutq_plan_default(bits, group_size, M, N, K, dtype, &def);
+    const lutq_plan def{};
+    lutq_plan rules;
+    lutq_status st = lutq_plan_default(bits, group_size, M, N, K, dtype, &rules);
     if (st != LUTQ_OK) return st;
-    if (M > 32) def = lutq_plan{};
     hipStream_t s = static_cast<hipStream_t>(stream);
-    // the default plan validates every other argument; its launches also bring the clocks up
+    // the library's own choice validates every other argument; its launches also bring the clocks up
     int next = 0;
     auto run = [&](const lutq_plan& c, int n) {
         lutq_status r = LUTQ_OK;

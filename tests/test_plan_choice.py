@@ -88,3 +88,33 @@ def test_registered_plans_give_the_bits_of_the_same_plan_passed(lutq, p):
         finally:
             lutq.lutq_plan_table_set([])
     assert not np.array_equal(free, given)           # (two orders of summation)
+
+
+# (bits, group, M, N, K, dtype): panels; row streaming in K slices; the rules' plan
+TUNED = [((2, 32, 23, 4272, 22272, 0), "panels"), ((4, 64, 13, 1248, 21504, 1), "estimated"), ((4, 128, 8, 4096, 4096, 0), "rules")]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("p,what", TUNED)
+def test_tuner_times_the_call_without_a_plan_and_the_rules(lutq, p, what):
+    """Each launch is timed once; the tuner's result, registered, leaves a call with the launch that was timed."""
+    import torch
+    bits, group, M, N, K, dt = p
+    c = gen.make_case(N + M, M, N, K, bits, group, "bf16" if dt else "f16", "random_index")
+    d = DeviceCase(lutq, c)
+    rules, free = lutq.lutq_plan_default(*p), lutq.calib_plan(*p)
+    assert what == ("panels" if free == lutq.Plan() else "rules" if free == rules else "estimated")
+    cands = lutq.lutq_tune_candidates(*p)
+    assert cands[:2] == [lutq.Plan(), rules] if what != "rules" else cands[0] == rules and lutq.Plan() not in cands
+    assert len(set(map(repr, cands))) == len(cands) and (what != "estimated" or free not in cands)
+    Y = torch.empty((M, N), dtype=d.X.dtype, device="cuda")
+    best, us = lutq.lutq_tune(d.X, [d.packed, d.packed.clone()], [d.S, d.S.clone()], d.T, bits, group, Y, d.ws, reps=2)
+    assert us > 0.5 and best in cands
+    want = to_bits(d.matmul(lutq, plan=best))
+    check_y(want, c, f"{p} {best}")
+    try:
+        lutq.lutq_plan_table_set([(bits, group, dt, 1, 32, N, K, best)])
+        assert np.array_equal(to_bits(d.matmul(lutq)), want)
+    finally:
+        lutq.lutq_plan_table_set([])
+    assert not d.ws[:65536].any().item()
