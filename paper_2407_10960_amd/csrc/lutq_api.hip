@@ -975,7 +975,8 @@ lutq_status prepare_rows(const void* X, const void* packed, const void* scales, 
     int rpr = rows_blocks_per_round(bits, d.r, sg2, mb, d.nw, tab16);
     if (rpr < 1) return LUTQ_ERR_PLAN;
     // one pass: the slots may lie over table and scales, where the waves' KiB for turning activations fits behind those
-    const int own_xt = rows_x_turned(mb) ? d.nw * 1024 : 0;
+    const bool turn = rows_x_turned(bits, mb, d.r, bf16, (int)M);
+    const int own_xt = turn ? d.nw * 1024 : 0;
     if (amax <= d.r && beside + own_xt <= 160 * 1024) {
         red_off = 0;
         rpr = 160 / (mb * d.nw);
@@ -1015,6 +1016,7 @@ lutq_status prepare_rows(const void* X, const void* packed, const void* scales, 
     q.s_magic = linear ? 0u : (uint32_t)((1ull << 32) / (uint64_t)q.s_units + 1);
     q.SROW = srow;
     q.red_off = red_off;
+    q.turn = turn;
     q.xt_off = xt_off;
     q.stage_off = beside - d.r * rowlut16_stage(bits);
     q.tab_total = d.r * tab16;

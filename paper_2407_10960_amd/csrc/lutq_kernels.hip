@@ -141,14 +141,14 @@ hipError_t launch_decode_group(int r, bool rowlut, const DecodeParams& p, int ld
 }
 
 // Row-streaming kernel for 5..64 activation rows: MB blocks of sixteen rows, AMAX = 4 or 8 row blocks side by side.
-template <int GROUP, int MB, int AMAX, bool RLUT = false>
+template <int GROUP, int MB, int AMAX, bool RLUT = false, bool TURN = false>
 hipError_t launch_rows_one(const RowsParams& p, int lds_bytes, hipStream_t stream) {
     constexpr int max_waves = rows_max_waves(LUTQ_INST_BITS, MB, AMAX, Tab<LUTQ_INST_BITS, LUTQ_INST_DT>::WIDE);
     if constexpr (max_waves == 0) {
         return hipErrorInvalidValue;
     } else {
         if (p.NW > max_waves) return hipErrorInvalidValue;
-        auto kernel = rows_kernel<LUTQ_INST_BITS, GROUP, MB, LUTQ_INST_DT, AMAX, RLUT>;
+        auto kernel = rows_kernel<LUTQ_INST_BITS, GROUP, MB, LUTQ_INST_DT, AMAX, RLUT, TURN>;
         if (lds_bytes > 64 * 1024) {
             static hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
                                                          hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
@@ -159,21 +159,29 @@ hipError_t launch_rows_one(const RowsParams& p, int lds_bytes, hipStream_t strea
     }
 }
 
+// 17..32 rows: activations turned into operands through LDS, or loaded as such (rows_x_turned)
+template <int GROUP, int AMAX, bool RLUT = false>
+hipError_t launch_rows_two(const RowsParams& p, int lds_bytes, hipStream_t stream) {
+    if constexpr (rows_turned_exists(LUTQ_INST_BITS, 2, AMAX, Tab<LUTQ_INST_BITS, LUTQ_INST_DT>::WIDE))
+        if (p.turn) return launch_rows_one<GROUP, 2, AMAX, RLUT, true>(p, lds_bytes, stream);
+    return p.turn ? hipErrorInvalidValue : launch_rows_one<GROUP, 2, AMAX, RLUT>(p, lds_bytes, stream);
+}
+
 template <int GROUP>
 hipError_t launch_rows_group(int mb, int amax, bool rowlut, const RowsParams& p, int lds_bytes, hipStream_t stream) {
     if (rowlut) {                    // one table per output row: eight row blocks side by side where their tables fit LDS
         if constexpr (rows_rowlut_eight(LUTQ_INST_BITS, Tab<LUTQ_INST_BITS, LUTQ_INST_DT>::WIDE)) {
             if (mb == 1 && amax == 8) return launch_rows_one<GROUP, 1, 8, true>(p, lds_bytes, stream);
-            if (mb == 2 && amax == 8) return launch_rows_one<GROUP, 2, 8, true>(p, lds_bytes, stream);
+            if (mb == 2 && amax == 8) return launch_rows_two<GROUP, 8, true>(p, lds_bytes, stream);
         }
         if (mb == 1 && amax == 4) return launch_rows_one<GROUP, 1, 4, true>(p, lds_bytes, stream);
-        if (mb == 2 && amax == 4) return launch_rows_one<GROUP, 2, 4, true>(p, lds_bytes, stream);
+        if (mb == 2 && amax == 4) return launch_rows_two<GROUP, 4, true>(p, lds_bytes, stream);
         return hipErrorInvalidValue;
     }
     if (mb == 1 && amax == 4) return launch_rows_one<GROUP, 1, 4>(p, lds_bytes, stream);
     if (mb == 1 && amax == 8) return launch_rows_one<GROUP, 1, 8>(p, lds_bytes, stream);
-    if (mb == 2 && amax == 4) return launch_rows_one<GROUP, 2, 4>(p, lds_bytes, stream);
-    if (mb == 2 && amax == 8) return launch_rows_one<GROUP, 2, 8>(p, lds_bytes, stream);
+    if (mb == 2 && amax == 4) return launch_rows_two<GROUP, 4>(p, lds_bytes, stream);
+    if (mb == 2 && amax == 8) return launch_rows_two<GROUP, 8>(p, lds_bytes, stream);
     if (mb == 3 && amax == 4) return launch_rows_one<GROUP, 3, 4>(p, lds_bytes, stream);   // 33..64 rows (4 bits)
     if (mb == 4 && amax == 4) return launch_rows_one<GROUP, 4, 4>(p, lds_bytes, stream);
     return hipErrorInvalidValue;

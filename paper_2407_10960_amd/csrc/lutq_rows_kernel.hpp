@@ -62,6 +62,7 @@ struct RowsParams {
     int SROW;                 // bytes from row to row of the scales in LDS (SG2 + 16: sixteen rows, sixteen banks)
     int red_off;              // LDS offset of the reduction slots (0 where one pass does everything: over the table and the scales)
     int stage_off;            // RLUT: LDS offset of the raw tables
+    int turn;                 // two blocks of sixteen rows: which instance runs, TURN or not (the kernel does not read it)
     int xt_off;               // TURN: LDS offset of the waves' KiB for turning activations
     int tab_total;            // RLUT: LDS bytes of the pass's per-row tables (AMAX x sixteen copies); the scales follow
     int lut_ltpe;             // log2 of the threads that build one table row together
@@ -86,12 +87,20 @@ struct RowsParams {
 // with four / eight row blocks side by side 114 / 149 registers, sixteen / twelve waves; M > 16 191 / 241,
 // eight waves); 0 = no such instance (the registers do not hold it without spilling).
 __host__ __device__ constexpr int rows_tiles_in_flight(int, int) { return 4; }   // (eight measured no faster)
-// Beyond sixteen rows the activations are loaded with four lanes side by side on a row (xfrag_load_row) and turned into
+// Beyond some twenty rows the activations are loaded with four lanes side by side on a row (xfrag_load_row) and turned into
 // operands through LDS: N = K = 8192, one pass of two row blocks over all of K, M = 24 / 32, us: W4 fp16 19.4 / 23.1 -> 18.8 / 19.5,
-// bf16 19.6 / 23.0 -> 19.4 / 20.1, W3 20.8 / 23.8 -> 18.6 / 19.3; 4096 x 14336 in four K slices, M = 32 17.2 -> 15.4.  Up to sixteen rows
-// they are loaded in operand order: the detour's latency costs more than the address unit's time there (M = 8 13.7 -> 16.1,
-// M = 12 14.1 -> 16.1, M = 16 15.0 -> 16.3; with twelve wavefronts M = 16 15.1 -> 14.2 but M = 8 12.4 -> 13.8).
-__host__ __device__ constexpr bool rows_x_turned(int mb) { return mb == 2; }
+// bf16 19.6 / 23.0 -> 19.4 / 20.1, W3 20.8 / 23.8 -> 18.6 / 19.3; 4096 x 14336 in four K slices, M = 32 17.2 -> 15.4.  Fewer rows
+// are loaded in operand order: rows that do not exist cost the address unit nothing, and the detour's latency stays (M = 8 13.7 -> 16.1,
+// M = 12 14.1 -> 16.1, M = 16 15.0 -> 16.3; with twelve wavefronts M = 16 15.1 -> 14.2 but M = 8 12.4 -> 13.8).  Speed of turned against
+// operand order over 3100 drawn calls, fp16 / bf16: 17 rows 0.99 / 0.97, 18-19 0.99 / 0.98, 20-21 1.01 / 0.99, 22-23 1.02 / 1.01, 24-25 1.03 /
+// 1.02, 26-32 1.07 / 1.05; but 4-bit bf16 with eight row blocks side by side, which has no second set of activations (below), 0.96 at
+// 17..23 rows and 0.98 at 26..32 (24304 x 24832 M = 18 88.5 -> 98.2 us).
+__host__ __device__ constexpr bool rows_turned_exists(int bits, int mb, int amax, bool wide_table) {
+    return mb == 2 && !(bits == 4 && amax == 8 && wide_table);
+}
+__host__ __device__ constexpr bool rows_x_turned(int bits, int mb, int amax, bool bf16, int rows) {
+    return rows_turned_exists(bits, mb, amax, bf16) && rows >= (bf16 ? 23 : 21);
+}
 // The activations of the next K tile are fetched a whole tile ahead into a second set of registers where that
 // measured faster (4 bits beyond sixteen rows: 8B gate+up fp16 M = 32 21.9 -> 20.8 us); elsewhere the second set
 // costs waves (twelve -> eight) or the instance, and the next tile's activations are fetched step by step
@@ -114,7 +123,7 @@ __host__ __device__ constexpr bool rows_rowlut_eight(int bits, bool wide_table) 
 // RLUT: one table per output row (p.lut = [N, 2^bits]).  The tables of the pass's row blocks are built when the
 // pass begins, sixteen copies per row block (the four lanes of a row share one; rowlut16_build), and slot a reads
 // the copies of its own row block with the generic entry address.
-template <int BITS, int GROUP, int MB, typename DT, int AMAX, bool RLUT = false>
+template <int BITS, int GROUP, int MB, typename DT, int AMAX, bool RLUT = false, bool TURN = false>
 __global__ __launch_bounds__(64 * (rows_max_waves(BITS, MB, AMAX, Tab<BITS, DT>::WIDE) > 0 ? rows_max_waves(BITS, MB, AMAX, Tab<BITS, DT>::WIDE) : 4))
 void rows_kernel(const RowsParams p) {
     using Gm = Geo<BITS>;
@@ -132,7 +141,6 @@ void rows_kernel(const RowsParams p) {
     // wave's 64 lanes hold for K step s of tile kt and rows 16 mb .. 16 mb + 15, rows beyond M zero), written by
     // rows_xop_kernel just before this launch: every load is one contiguous KiB instead of sixteen rows' 64 bytes.
     constexpr bool XOP = MB > 2;
-    constexpr bool TURN = rows_x_turned(MB);
     static_assert(AMAX % NST == 0, "the row blocks of a pass are walked in rounds of the pipeline's stages");
 
     asm volatile("" ::"s"(p.X), "s"(p.packed), "s"(p.scales), "s"(p.lut), "s"(p.Y), "s"(p.packed_bytes), "s"(p.scale_bytes),
@@ -324,6 +332,12 @@ void rows_kernel(const RowsParams p) {
                         *reinterpret_cast<u32x4*>(xt + xfrag_slot(xfrag_load_octet(lane), xfrag_load_row(lane))) = XDB ? xr[s][mb] : bx[s][mb];
                         bx[s][mb] = *reinterpret_cast<const u32x4*>(xt + xfrag_slot(lo, li));
                     }
+                __builtin_amdgcn_sched_barrier(0);
+            } else if constexpr (XDB) {
+#pragma unroll
+                for (int s = 0; s < STEPS; ++s)
+#pragma unroll
+                    for (int mb = 0; mb < MB; ++mb) bx[s][mb] = xr[s][mb];
                 __builtin_amdgcn_sched_barrier(0);
             }
         };
