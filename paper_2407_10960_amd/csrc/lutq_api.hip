@@ -1395,9 +1395,13 @@ lutq_status prepare_matmul(const void* X, const void* packed, const void* scales
 
 // The plan of a call of up to 32 rows without one, where estimates say that the rules' takes clearly longer (lutq_estimates.hpp);
 // false: the rules' plan.  Candidates: row streaming from five rows up, four or eight row blocks side by side, all of K or
-// any number of K slices, up to two workgroups per compute unit; one team per row block of four to sixteen waves.  Only a
-// candidate that this scratch and the instances can run is taken.  The rules stay where they are within a margin: they were
-// measured on the shapes that models have, and the estimates are no better than 7 to 16 %.
+// any number of K slices, up to two workgroups per compute unit; one team per row block of four to sixteen waves (beyond sixteen
+// rows at 4 bits only: at 2 and 3 bits 5120 to 7920 x 1280 M = 21..32 8.5 -> 10.4 us with five waves instead of four, 62 calls together 0.97 times as
+// fast as the rules' launch).  Only a candidate that this scratch and the instances can run is taken.  The rules stay where they are within a
+// margin: they were measured on the shapes that models have, and the estimates are no better than 6 to 13 %.  On 5800 drawn problems, with
+// estimates fitted to others, margins of 0.84 / 0.88 / 0.92 left 0.1 / 0.4 / 1.5 % of the calls of 5..16 rows and 0.2 / 0.2 / 0.3 % of those of 17..32 more
+// than 3 % slower than the rules' launch, for 1.109 / 1.116 / 1.122 and 1.344 / 1.348 / 1.349 times its speed.  (Without the scale rows and the uneven
+// parts among the estimates' terms: 1.0 % and 1.8 %, up to 30 % slower, for 1.106 and 1.327.)
 Estimated estimate_launch(int bits, int group_size, int64_t M, int64_t N, int64_t K, lutq_dtype dtype, int cus, size_t workspace_bytes) {
     Estimated e;
     const int64_t nb = N / 16, kt = K / tile_k(bits);
@@ -1407,8 +1411,9 @@ Estimated estimate_launch(int bits, int group_size, int64_t M, int64_t N, int64_
     const Decomp ruled = ruled_decomp(bits, group_size, M, N, K, bf16, sch, cus, false);
     if (ruled.queue) return e;
     // (1..4 rows: the rules hold but for shapes that they deal to few workgroups -- 8624 x 14848 M = 2 bf16 55.5 us, one team per row block 22.7)
-    const double margin = M <= 4 ? 0.75 : ruled.rows ? 0.8 : 0.82;
-    double now = (ruled.rows ? rows_estimate_us(bits, M, nb, kt, megabytes, ruled.r, ruled.grid, ruled.nw, ruled.ks > 1 ? ruled.ks : 1, cus)
+    const double margin = M <= 4 ? 0.75 : 0.9;
+    const int64_t groups = K / group_size;
+    double now = (ruled.rows ? rows_estimate_us(bits, M, nb, kt, groups, megabytes, ruled.r, ruled.grid, ruled.nw, ruled.ks > 1 ? ruled.ks : 1, cus)
                                        : teams_estimate_us(bits, M, nb, kt, megabytes, ruled.r, ruled.grid, ruled.nw, ruled.rs,
                                                            M > 4 && teams_can_share_x(bits, mb, ruled.rs), cus));
     double best = margin * now;
@@ -1424,7 +1429,7 @@ Estimated estimate_launch(int bits, int group_size, int64_t M, int64_t N, int64_
     };
     // (beyond 12 us the estimates of one team per row block are too low at 17..32 rows and a long K: 8192 x 28672 M = 32 fp16 44 -> 115 us)
     for (int nw : {4, 5, 6, 8, 12, 16}) {
-        if (nb > kMaxGrid || (!sch && nw > 8)) continue;
+        if (nb > kMaxGrid || (!sch && nw > 8) || (M > 16 && bits != 4)) continue;
         const double us = teams_estimate_us(bits, M, nb, kt, megabytes, 1, (int)nb, nw, 1, false, cus);
         if (M <= 4 || us <= 12.) consider(us, lutq_plan{1, (int)nb, nw, 2, 1, LUTQ_SCHED_TEAMS, 0});
     }
@@ -1436,21 +1441,21 @@ Estimated estimate_launch(int bits, int group_size, int64_t M, int64_t N, int64_
             for (int64_t grid : {nb < cus ? nb : (int64_t)cus, (int64_t)2 * cus})
                 // (with fewer K tiles than waves the estimates are too low: 57104 x 1280 W3 bf16 M = 8 16.1 -> 19.8)
                 if (grid <= nb && nb / grid <= 64 && kt >= nw)
-                    consider(rows_estimate_us(bits, M, nb, kt, megabytes, side, (int)grid, nw, 1, cus),
+                    consider(rows_estimate_us(bits, M, nb, kt, groups, megabytes, side, (int)grid, nw, 1, cus),
                              lutq_plan{side, (int)grid, nw, 2, (int)(nb / grid), LUTQ_SCHED_ROWS, 0});
             const int64_t shares = (nb + side - 1) / side;
             for (int64_t ks = 2; ks <= kt && ks <= 40 && shares * ks <= 2 * (int64_t)cus; ++ks) {
                 const int64_t it = (kt + ks - 1) / ks;        // (slice counts that a plan can name)
                 if ((kt + it - 1) / it == ks)
-                    consider(rows_estimate_us(bits, M, nb, kt, megabytes, side, (int)(shares * ks), nw, (int)ks, cus),
+                    consider(rows_estimate_us(bits, M, nb, kt, groups, megabytes, side, (int)(shares * ks), nw, (int)ks, cus),
                              lutq_plan{side, (int)(shares * ks), nw, 2, (int)(nb / shares), LUTQ_SCHED_ROWS, (int)it});
             }
         }
     }
-    // 17..32 rows: the panel launch, with all of K or in K slices, where estimated a good tenth faster than what was chosen so far
+    // 17..32 rows: the panel launch, with all of K or in K slices, where estimated clearly faster than what was chosen so far
     if (M <= 16 || M * K * 2 >= (int64_t)1 << 31) return e;
     const size_t room = workspace_bytes > kCounterBytes ? workspace_bytes - kCounterBytes : 0;
-    best = 0.87 * now;
+    best = 0.92 * now;
     for (int rp = 1; rp <= 2; ++rp) {
         const int64_t shares = (nb + 4 * rp - 1) / (4 * rp);
         for (int64_t ks = 1; ks <= 32; ++ks) {
@@ -1466,7 +1471,7 @@ Estimated estimate_launch(int bits, int group_size, int64_t M, int64_t N, int64_
     return e;
 }
 
-// The same, remembered per thread for the last problems by their sizes and types (the choice takes some ten microseconds).
+// The same, remembered per thread for the last problems by their sizes and types (the choice takes one to two microseconds).
 Estimated estimated_launch(int bits, int group_size, int64_t M, int64_t N, int64_t K, lutq_dtype dtype, int cus, size_t workspace_bytes, bool fitted_workspace) {
     struct Entry {
         int64_t N, K;
