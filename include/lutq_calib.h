@@ -40,21 +40,23 @@ int lutq_calib_matmul_trace(const void* X, const void* packed, const void* scale
                             void* Y, void* workspace, size_t workspace_bytes, void* stream,
                             const lutq_plan* plan, void* trace, size_t trace_bytes, int* workgroups);
 
-/* How lutq_matmul serves a call of 33..128 rows without a plan on a device with `compute_units` compute
+/* How lutq_matmul serves a call without a plan on a device with `compute_units` compute
  * units (1..4096) and a workspace of `workspace_bytes`; host logic only, no device is touched (the plan
  * table counts).  route[0] = 0: one launch for all rows, each workgroup on 32 route[1] activation rows by
  * 64 route[2] output channels, with K cut into route[3] slices and M into route[4] parts; else
- * route[0] = the rows per launch of the slices it is served in (32 or 64) and the others are 0.
- * Return values: 0, or the status lutq_matmul would give the problem (SHAPE also for M <= 32). */
+ * route[0] = the rows per launch of the slices it is served in (32 or 64) and the others are 0.  Up to 32 rows the call is one launch in
+ * either case, and route[0] = 0 says that it is panels (17..32 rows, route[1] = 1).
+ * Return values: 0, or the status lutq_matmul would give the problem (7 also for less than 64 KiB of workspace up to 32 rows). */
 int lutq_calib_route(int bits, int group_size, int64_t M, int64_t N, int64_t K, int dtype, int compute_units,
                      size_t workspace_bytes, int route[5]);
 
-/* The launch of a call of 1..32 rows with `plan` (NULL: without one; the plan table counts then) on a device with `compute_units`
+/* The launch of a call of 1..32 rows with `plan` (NULL: without one; the plan table counts then), or, row_tables != 0, of a call of
+ * lutq_matmul_channel (plan NULL; the table does not count), on a device with `compute_units`
  * compute units and a workspace of `workspace_bytes` (at least 64 KiB): *runs = the decomposition that is launched, with every field
  * given; all zero where it is one that no plan names (panels of 32 rows).  Host logic only, no device is touched.
  * Return values: 0, or the status lutq_matmul_plan would give the problem and the plan (SHAPE also for M > 32). */
 int lutq_calib_plan(int bits, int group_size, int64_t M, int64_t N, int64_t K, int dtype, int compute_units,
-                    size_t workspace_bytes, const lutq_plan* plan, lutq_plan* runs);
+                    size_t workspace_bytes, const lutq_plan* plan, int row_tables, lutq_plan* runs);
 
 #ifdef __cplusplus
 }

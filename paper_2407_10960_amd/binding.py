@@ -136,7 +136,7 @@ def load_library():
     lib.lutq_calib_route.restype = ci
     lib.lutq_calib_route.argtypes = [ci, ci, i64, i64, i64, ci, ci, sz, ctypes.POINTER(ctypes.c_int)]
     lib.lutq_calib_plan.restype = ci
-    lib.lutq_calib_plan.argtypes = [ci, ci, i64, i64, i64, ci, ci, sz, ctypes.POINTER(_CPlan), ctypes.POINTER(_CPlan)]
+    lib.lutq_calib_plan.argtypes = [ci, ci, i64, i64, i64, ci, ci, sz, ctypes.POINTER(_CPlan), ci, ctypes.POINTER(_CPlan)]
     _LIB = lib
     return lib
 
@@ -525,8 +525,9 @@ def calib_copy(src, dst, grid: int, stream=None):
 
 def calib_route(bits: int, group_size: int, M: int, N: int, K: int, dtype_code: int = LUTQ_F16, compute_units: int = 256,
                 workspace_bytes: int | None = None) -> tuple:
-    """How lutq_matmul serves 33..128 rows without a plan: (0, blocks of 32 rows and panel height / 32 per workgroup, K
-    slices, parts of M) for the one launch, else (rows per slice, 0, 0, 0, 0).  Host logic, no device needed."""
+    """How lutq_matmul serves a call without a plan: (0, blocks of 32 rows and panel height / 32 per workgroup, K
+    slices, parts of M) for the one launch, else (rows per slice, 0, 0, 0, 0) -- up to 32 rows, one
+    launch too: panels, else (32, 0, 0, 0, 0).  Host logic, no device needed."""
     if workspace_bytes is None:
         workspace_bytes = lutq_workspace_bytes(N, K, bits, group_size)
     r = (ctypes.c_int * 5)()
@@ -536,14 +537,15 @@ def calib_route(bits: int, group_size: int, M: int, N: int, K: int, dtype_code: 
 
 
 def calib_plan(bits: int, group_size: int, M: int, N: int, K: int, dtype_code: int = LUTQ_F16, compute_units: int = 256,
-               workspace_bytes: int | None = None, plan: Plan | None = None) -> Plan:
-    """The launch of a call of 1..32 rows with `plan` (None: without one; registered plans count), every field given; the empty
-    Plan() where it is panels of 32 rows, which no plan names.  Host logic, no device needed."""
+               workspace_bytes: int | None = None, plan: Plan | None = None, row_tables: bool = False) -> Plan:
+    """The launch of a call of 1..32 rows with `plan` (None: without one; registered plans count), or of lutq_matmul_channel
+    (row_tables), every field given; the empty Plan() where it is panels of 32 rows, which no plan names.  Host logic, no device needed."""
     if workspace_bytes is None:
         workspace_bytes = lutq_workspace_bytes(N, K, bits, group_size)
     cp, runs = plan._c() if plan is not None else None, _CPlan()
     _check(load_library().lutq_calib_plan(bits, group_size, M, N, K, dtype_code, compute_units, workspace_bytes,
-                                          ctypes.byref(cp) if cp is not None else None, ctypes.byref(runs)), "lutq_calib_plan")
+                                          ctypes.byref(cp) if cp is not None else None, int(row_tables),
+                                          ctypes.byref(runs)), "lutq_calib_plan")
     return Plan(runs.row_blocks_per_wave, runs.grid, runs.waves_per_workgroup, runs.tiles_in_flight,
                 runs.row_groups_per_workgroup, runs.scheduling, runs.tiles_per_item)
 

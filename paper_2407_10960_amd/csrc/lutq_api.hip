@@ -1916,10 +1916,12 @@ extern "C" int lutq_calib_route(int bits, int group_size, int64_t M, int64_t N, 
     if (!route) return LUTQ_ERR_NULL;
     lutq_status st = check_problem(bits, group_size, N, K);
     if (st != LUTQ_OK) return st;
-    if (M <= 32 || M > kMaxRows || compute_units < 1 || compute_units > 4096) return LUTQ_ERR_SHAPE;
+    if (M < 1 || M > kMaxRows || compute_units < 1 || compute_units > 4096) return LUTQ_ERR_SHAPE;
     if (dtype != LUTQ_F16 && dtype != LUTQ_BF16) return LUTQ_ERR_DTYPE;
+    if (M <= 32 && workspace_bytes < kCounterBytes) return LUTQ_ERR_WORKSPACE;
     PanelDecomp d;
-    const bool one = panel_plan(bits, group_size, M, N, K, (lutq_dtype)dtype, nullptr, compute_units, workspace_bytes, &d);
+    const bool one = M > 32 ? panel_plan(bits, group_size, M, N, K, (lutq_dtype)dtype, nullptr, compute_units, workspace_bytes, &d)
+                            : M > 16 && panel_plan_32(bits, group_size, M, N, K, (lutq_dtype)dtype, nullptr, compute_units, workspace_bytes, &d);
     const int slice = one ? 0 : slice_rows(bits, group_size, M, N, K, dtype == LUTQ_BF16, nullptr, false, compute_units, &st);
     const int out[5] = {slice, one ? d.mb : 0, one ? d.rp : 0, one ? d.ks : 0, one ? d.ms : 0};
     std::copy(out, out + 5, route);
@@ -1927,8 +1929,9 @@ extern "C" int lutq_calib_route(int bits, int group_size, int64_t M, int64_t N, 
 }
 
 extern "C" int lutq_calib_plan(int bits, int group_size, int64_t M, int64_t N, int64_t K, int dtype, int compute_units,
-                               size_t workspace_bytes, const lutq_plan* plan, lutq_plan* runs) {
+                               size_t workspace_bytes, const lutq_plan* plan, int row_tables, lutq_plan* runs) {
     if (!runs) return LUTQ_ERR_NULL;
+    if (row_tables && plan) return LUTQ_ERR_PLAN;         // (lutq_matmul_channel takes none)
     lutq_status st = check_problem(bits, group_size, N, K);
     if (st != LUTQ_OK) return st;
     if (M < 1 || M > 32 || compute_units < 1 || compute_units > 4096) return LUTQ_ERR_SHAPE;
@@ -1937,17 +1940,17 @@ extern "C" int lutq_calib_plan(int bits, int group_size, int64_t M, int64_t N, i
     const lutq_dtype dt = (lutq_dtype)dtype;
     const bool fitted = workspace_bytes != kWorkspaceBytes;
     PanelDecomp panels;
-    if (M > 16 && panel_plan_32(bits, group_size, M, N, K, dt, plan, compute_units, workspace_bytes, &panels)) {
+    if (M > 16 && !row_tables && panel_plan_32(bits, group_size, M, N, K, dt, plan, compute_units, workspace_bytes, &panels)) {
         *runs = lutq_plan{};
         return LUTQ_OK;
     }
     Prepared q{};
     auto dry = [&](const lutq_plan* p) {
-        return prepare_matmul(nullptr, nullptr, nullptr, nullptr, bits, group_size, M, N, K, dt, nullptr, nullptr, workspace_bytes, p, false,
+        return prepare_matmul(nullptr, nullptr, nullptr, nullptr, bits, group_size, M, N, K, dt, nullptr, nullptr, workspace_bytes, p, row_tables != 0,
                               compute_units, &q, fitted);
     };
     lutq_plan registered;
-    if (plan || !plan_table_find(bits, group_size, M, N, K, dt, &registered) || (st = dry(&registered)) != LUTQ_OK) st = dry(plan);
+    if (plan || row_tables || !plan_table_find(bits, group_size, M, N, K, dt, &registered) || (st = dry(&registered)) != LUTQ_OK) st = dry(plan);
     if (st != LUTQ_OK) return st;
     if (q.rows)
         *runs = lutq_plan{q.r, q.rp.G, q.rp.NW, 2, q.rp.A, LUTQ_SCHED_ROWS, q.rp.KS > 1 ? (q.rp.KT + q.rp.KS - 1) / q.rp.KS : 0};
