@@ -292,11 +292,13 @@ lutq_status lutq_matmul_static(const void* X, const void* packed, const void* sc
  *   every other argument as in lutq_matmul (scales of 1.0 give tables without group scales).
  * M <= 4 with K / group_size a multiple of 8: the work-queue kernel with the tables of all of a
  * workgroup's row blocks built once and resident (sixteen copies per row block: the four lanes that
- * work on a row share one).  5 <= M <= 32 with at least two row blocks per compute unit: the row-streaming
- * kernel with the tables of four row blocks at a time.  Otherwise a workgroup holds the tables of one 16-row block at a time and
+ * work on a row share one).  5 <= M <= 32: the row-streaming kernel with the tables of four or eight row blocks side by side, where
+ * there are at least two row blocks per compute unit; on smaller matrices too from 9 or 17 rows up, if K is long, then with K cut into
+ * up to sixteen slices across workgroups, whose partial sums and counters are in the workspace.  Otherwise a workgroup holds the tables
+ * of one 16-row block at a time and
  * rebuilds its on-chip copies for every row block it works on (one row block per workgroup, K split
- * over its waves and, for few row blocks, over workgroups).  The work decomposition is the library's
- * in both cases.  Errors: those of lutq_matmul. */
+ * over its waves and, for few row blocks, over workgroups, with partial sums in the workspace).  The work decomposition is the library's
+ * in all cases.  Errors: those of lutq_matmul. */
 lutq_status lutq_matmul_channel(const void* X, const void* packed, const void* scales, const void* luts,
                                 int bits, int group_size, int64_t M, int64_t N, int64_t K,
                                 lutq_dtype dtype, void* Y,

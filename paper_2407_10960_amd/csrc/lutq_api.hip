@@ -334,11 +334,17 @@ int rowlut_queue_lds(int bits, bool bf16, int amax, int nw, int items) {
 // table and fetch the activations again for every row block, us (4 bits fp16 where nothing else is said):
 //   * from two row blocks per compute unit up, all of K: four row blocks side by side, or eight in one pass where their tables fit
 //     LDS (8B gate+up M = 6 / 16 / 32 20.6 / 24.0 / 27.1 in two passes of four -> 16.5 / 18.5 / 22.2; W3 bf16 M = 16 25.4 -> 21.8).
-//     (Twelve waves: sixteen took 24.0 us where twelve took 22.8.)
+//     (Twelve waves: sixteen took 24.0 us where twelve took 22.8.)  Scale rows that are not whole 16-byte units: at 2 and 4 bits and in fp16 1.05 to
+//     1.3 times as fast at 5..8 rows, from nine rows 1.2 to 2.2; 3-bit bf16 of five and six rows 0.95 (33264 x 3840 M = 6 25.9 -> 30.9), not taken.
 //   * up to two per unit, K slices: M = 17 / 32 4096 x 14336 20.4 / 30.3 -> 15.7 / 16.3, N = K = 8192 19.6 / 20.3 -> 16.6 / 17.4, 6144 x 4096 15.3 /
 //     20.7 -> 11.7 / 12.2, 1312 x 11264 16.5 / 20.0 -> 11.3 / 11.5 (W2 32.0 / 34.3 -> 11.8 / 11.6), 4096 x 6144 M = 32 15.3 -> 11.8; not 4096 x 4096 (M = 17 8.6 ->
 //     10.4) nor 4096 x 6144 at M = 17 (11.0 -> 11.6).  Nine to sixteen rows: only a long K, M = 12 4096 x 14336 15.5 -> 13.2, 1312 x 11264 11.6 -> 10.0, and
-//     between one and two row blocks per unit (all of K: 6144 x 4096 10.2 -> 9.8, W2 11.7 -> 8.9); M = 8 4096 x 14336 12.1 -> 12.9.
+//     between one and two row blocks per unit (all of K: 6144 x 4096 10.2 -> 9.8, W2 11.7 -> 8.9; not at 4 bits with a short K: 7312 x 1536 bf16
+//     M = 10 7.0 -> 7.7, fifteen of K = 1152..2304 0.95 together, thirty of K = 2560..8192 1.10); M = 8 4096 x 14336 12.1 -> 12.9.
+//     At most sixteen slices: the workgroup that adds their sums takes longer than the rest where there are more.  Times of 600 drawn calls
+//     of one to 128 row blocks and K from 4096 with no bound / 32 / 16 / 12 / 8 slices, us: of more than 64 possible ones 25.9 / 19.4 / 18.6 / 18.9 / 19.9 (17..32
+//     rows) and 20.2 / 14.6 / 13.9 / 14.1 / 14.6 (9..16), of 24..31 16.2 / 16.1 / 14.9 / 14.7 / 14.8.  Without the bound a third of the calls of
+//     9..16 rows and up to seven row blocks took longer than the teams (80 x 17408 group 32 W3 bf16 M = 11 12.6 -> 17.7).
 bool rowlut_rows_decomp(int bits, bool bf16, int64_t M, int64_t N, int64_t K, int group_size, int cus, Decomp* out) {
     if (M < 5) return false;
     const int64_t nb = N / 16, kt = K / tile_k(bits);
@@ -346,10 +352,12 @@ bool rowlut_rows_decomp(int bits, bool bf16, int64_t M, int64_t N, int64_t K, in
     Decomp d;
     d.queue = 0; d.it = 0; d.rows = 1; d.stages = 2; d.r = 4;
     const bool few = nb <= 2 * (int64_t)cus && (M > 16 ? K >= 8192 || nb > cus || (M > 24 && K >= 6144)
-                                                       : M > 8 && nb < 2 * (int64_t)cus && (K >= 11264 || nb > cus));
+                                                       : M > 8 && nb < 2 * (int64_t)cus && (K >= 11264 || (nb > cus && (bits != 4 || K >= 2560))));
     if (!few && nb < 2 * (int64_t)cus) return false;
+    if (bits == 3 && bf16 && M <= 6 && sg2 % 16 != 0) return false;
     const int64_t shares = (nb + 3) / 4;
     int64_t ks = few && (M > 16 || K >= 11264) ? cus / shares : 1;
+    if (ks > 16) ks = 16;
     if (ks > kt) ks = kt;
     if (ks > 1) {
         d.ks = (int)ks;

@@ -40,3 +40,28 @@ def test_row_tables(shape, bits, dtype):
     What = orc.dequant_channel(case.Q, tables, case.S, group, dtype)
     check_y(to_bits(Y), case, f"{shape} b{bits} {dtype}", What)
     assert not d.ws[:65536].any().item()
+
+
+# (bits, group, M, N, K, dtype), what is launched
+LAUNCHED = [((3, 32, 11, 80, 17408, 1), "slices"), ((4, 32, 12, 64, 13312, 0), "slices"), ((3, 64, 9, 16, 29440, 0), "slices"),
+            ((3, 32, 25, 64, 22528, 1), "slices"), ((2, 256, 30, 48, 12288, 0), "slices"),
+            ((4, 128, 10, 7312, 1536, 1), "teams"), ((4, 128, 11, 5152, 1920, 1), "teams"), ((3, 64, 6, 33264, 3840, 1), "teams"),
+            ((4, 128, 12, 4800, 5632, 0), "rows"), ((3, 128, 16, 7264, 2048, 1), "rows"), ((4, 64, 6, 33264, 3840, 0), "rows")]
+
+
+def test_launches_with_one_table_per_row():
+    """At most sixteen K slices; four-bit calls of 9..16 rows with one to two row blocks per compute unit and a short K, and 3-bit bf16
+    calls of five and six rows with scale rows that are not whole 16-byte units, stay with the teams."""
+    import paper_2407_10960_amd as lutq
+    for p, what in LAUNCHED:
+        plan = lutq.calib_plan(*p, row_tables=True)
+        assert plan.scheduling == (1 if what == "teams" else 3), (p, plan)
+        assert (what == "slices") == (plan.tiles_per_item > 0), (p, plan)
+    rng = np.random.default_rng(1)
+    for _ in range(2000):
+        bits, group, M = int(rng.choice([2, 3, 4])), int(rng.choice([32, 64, 128, 256])), int(rng.integers(5, 33))
+        N, K = 16 * int(np.exp(rng.uniform(0, 7))), 256 * int(rng.integers(16, 128))
+        plan = lutq.calib_plan(bits, group, M, N, K, int(rng.integers(0, 2)), row_tables=True)
+        if plan.tiles_per_item:
+            shares = -(-(N // 16) // 4)
+            assert plan.grid % shares == 0 and 2 <= plan.grid // shares <= 16, (bits, group, M, N, K, plan)
