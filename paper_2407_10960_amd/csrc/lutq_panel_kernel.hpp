@@ -158,8 +158,8 @@ __global__ __launch_bounds__(64 * kPanelWaves) void panel_kernel(const PanelPara
     // the slice's tiles over the four K parts
     const int st_n = p.TS + (slice < p.KSB ? 1 : 0);
     const int st_0 = slice * p.TS + (slice < p.KSB ? slice : p.KSB);
-    // (from 65 rows up the first two parts, whose wavefronts are the older ones on their SIMDs and run ahead, get up to three
-    // sixteenths more: 8B gate+up M = 128 42.7 -> 42.2 us, 70B gate+up 154.9 -> 151.0, 70B o W3 bf16 M = 100 32.9 -> 31.6)
+    // (with more than 64 rows in a workgroup the first two parts, whose wavefronts are the older ones on their SIMDs and run ahead, get up
+    // to three sixteenths more: 8B gate+up M = 128 42.7 -> 42.2 us, 70B gate+up 154.9 -> 151.0; up to 64 rows, parts of M among them, not measured)
     const int skew = MB > 2 ? st_n / kPanelWK * 3 / 16 : 0;
     const int ka = st_0 + (st_n / kPanelWK) * kp + (kp < st_n % kPanelWK ? kp : st_n % kPanelWK) + (kp == 2 ? 2 * skew : (kp & 1) * skew);
     const int len = st_n / kPanelWK + (kp < st_n % kPanelWK ? 1 : 0) + (kp < 2 ? skew : -skew);
@@ -188,6 +188,7 @@ __global__ __launch_bounds__(64 * kPanelWaves) void panel_kernel(const PanelPara
         WFrag<BITS> w[2 * RP];
         ScaleWords<NS> s[SCH ? 1 : RP];
     };
+    static_assert(RP * 512 <= kPanelPark / 2, "parked scales end where the half that is never read begins");
     char* park = smem + panel_park_off<BITS>(MB) + wave * kPanelPark;
     u32x4 chunk[RP];                                   // SCH: the next eight scales of row l32 of each half panel
     auto load_stage = [&](Stage& st, int i) {           // tile i of the wavefront's range; nothing beyond the last
@@ -361,7 +362,7 @@ __global__ __launch_bounds__(64 * kPanelWaves) void panel_kernel(const PanelPara
             // under way, weights and activations of the tiles ahead among them, once per K tile: with that and the pairs' straight-line look, W4 fp16
             // 8B gate+up M = 128 42.8 -> 41.3 us, 70B gate+up 157 -> 148, 8B o M = 128 13.6 -> 12.5, down M = 64 21.2 -> 20.0, 12288 x 4096 M = 50 17.3 -> 16.2.
             const int kt = ka + i;
-            char* const dst = park + (chunk_begins(i, kt) ? 0 : 1024) + 16 * l32;
+            char* const dst = park + (chunk_begins(i, kt) ? 0 : kPanelPark / 2) + 16 * l32;
             asm volatile("" ::: "memory");              // (LDS operations of one wavefront complete in order)
 #pragma unroll
             for (int rp = 0; rp < RP; ++rp) *reinterpret_cast<u32x4*>(dst + rp * 512) = chunk[rp];
