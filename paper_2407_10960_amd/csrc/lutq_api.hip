@@ -832,6 +832,11 @@ bool estimated_plan(int bits, int group_size, int64_t M, int64_t N, int64_t K, l
     return e.found;
 }
 
+bool plan_is_zero(const lutq_plan& p) {
+    return !(p.scheduling || p.row_blocks_per_wave || p.grid || p.waves_per_workgroup || p.tiles_in_flight || p.row_groups_per_workgroup ||
+             p.tiles_per_item);
+}
+
 lutq_plan plan_of(const Decomp& d) {
     return lutq_plan{d.r, d.grid, d.nw, d.stages, d.rs, d.rows ? LUTQ_SCHED_ROWS : d.queue ? LUTQ_SCHED_QUEUE : LUTQ_SCHED_TEAMS, d.it};
 }
@@ -1130,6 +1135,7 @@ lutq_status prepare_matmul(const void* X, const void* packed, const void* scales
                                               workspace_bytes, &registered, rowlut, dry_run_cus, out, fitted_workspace, false);
         if (st != LUTQ_ERR_PLAN && st != LUTQ_ERR_SCRATCH) return st;
     }
+    if (user_plan && plan_is_zero(*user_plan)) user_plan = nullptr;      // (what stands for no plan is none from here on)
     // dry_run_cus > 0: only the plan is checked, for a device of that many compute units; no pointer is
     // looked at and no device is queried
     const bool dry = dry_run_cus > 0;
@@ -1424,13 +1430,19 @@ Estimated estimate_launch(int bits, int group_size, int64_t M, int64_t N, int64_
     double now = (ruled.rows ? rows_estimate_us(bits, M, nb, kt, groups, megabytes, ruled.r, ruled.grid, ruled.nw, ruled.ks > 1 ? ruled.ks : 1, cus)
                                        : teams_estimate_us(bits, M, nb, kt, megabytes, ruled.r, ruled.grid, ruled.nw, ruled.rs,
                                                            M > 4 && teams_can_share_x(bits, mb, ruled.rs), cus));
-    double best = margin * now;
-    auto consider = [&](double us, const lutq_plan& plan) {
-        if (us >= best) return;
+    auto runs = [&](const lutq_plan* plan, bool small_scratch) {
         Prepared q{};
-        if (prepare_matmul(nullptr, nullptr, nullptr, nullptr, bits, group_size, M, N, K, dtype, nullptr, nullptr, workspace_bytes, &plan, false,
-                           cus, &q, true) != LUTQ_OK)
-            return;
+        return prepare_matmul(nullptr, nullptr, nullptr, nullptr, bits, group_size, M, N, K, dtype, nullptr, nullptr, workspace_bytes, plan, false,
+                              cus, &q, true, false, small_scratch) == LUTQ_OK;
+    };
+    // (where neither the rules' plan nor their plan for little scratch fits, whatever does fit is taken: 45408 x 26624 W2 M = 31, eleven teams, in
+    // lutq_matmul_static's 16 MiB)
+    const lutq_plan ruled_plan = plan_of(ruled);
+    const bool fits = workspace_bytes >= kWorkspaceBytes || runs(&ruled_plan, false) || runs(nullptr, true);
+    double best = fits ? margin * now : 1e30;
+    if (!fits) now = best;
+    auto consider = [&](double us, const lutq_plan& plan) {
+        if (us >= best || !runs(&plan, false)) return;
         best = now = us;
         e.plan = plan;
         e.found = true;
@@ -1639,11 +1651,6 @@ double panel_us_w4(bool bf16, int64_t N, int64_t K, int cus, const PanelDecomp& 
     const int64_t tiles = ((K / 128 + d.ks - 1) / d.ks + kPanelWK - 1) / kPanelWK;
     return (double)rounds * (f[0] + f[1] * (double)tiles) + f[5] * (double)N * (double)K * 5e-7 +
            (d.ks > 1 ? f[2] + f[3] * (double)grid / (double)(rounds * cus) + f[4] * d.ks : 0.);
-}
-
-bool plan_is_zero(const lutq_plan& p) {
-    return !(p.scheduling || p.row_blocks_per_wave || p.grid || p.waves_per_workgroup || p.tiles_in_flight || p.row_groups_per_workgroup ||
-             p.tiles_per_item);
 }
 
 // Whether a plan is registered for calls of M <= 32 rows and asks for something that the kernels can run in this scratch.

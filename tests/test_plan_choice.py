@@ -45,6 +45,21 @@ def test_a_given_plan_is_what_runs(lutq, small_scratch):
     assert others > 100 and panels > 50
 
 
+def test_a_call_without_a_plan_fits_the_built_in_scratch(lutq):
+    """Also where neither the rules' plan nor the one for little scratch does (the first three)."""
+    ws = lutq.STATIC_SCRATCH_BYTES
+    refused = [(2, 256, 31, 45408, 26624, 0, 256), (2, 32, 31, 18720, 7168, 1, 256), (4, 32, 24, 64480, 16896, 0, 256)]
+    for p in refused:
+        with pytest.raises(lutq.LutqError) as e:
+            lutq.calib_plan(*p, ws, plan=lutq.lutq_plan_default_for(*p))
+        assert e.value.code == 11
+    # (the last of these: only a plan of few partial sums fits)
+    for p in refused + [(4, 64, 32, 57344, 8192, 1, 256)] + list(problems(7, 3000)):
+        plan = lutq.calib_plan(*p, ws)
+        assert plan == lutq.Plan() or plan.grid > 0
+        assert lutq.calib_plan(*p, ws, plan=lutq.Plan()) == plan, p
+
+
 # panels of 32 rows are the library's choice on these: (bits, group, M, N, K, dtype)
 PANELS = [(4, 32, 17, 1072, 22528, 0), (3, 64, 32, 4272, 8192, 0), (2, 32, 32, 1152, 20992, 0)]
 IMPOSSIBLE = ((1, 0, 8, 2, 3), (1, 256, 16, 2, 1, 2, 4), (0, 0, 0, 0, 0, 7))   # waves that are no three teams, a queue, no scheduling
