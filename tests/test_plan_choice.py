@@ -60,6 +60,16 @@ def test_a_call_without_a_plan_fits_the_built_in_scratch(lutq):
         assert lutq.calib_plan(*p, ws, plan=lutq.Plan()) == plan, p
 
 
+def test_a_remembered_choice_is_that_of_its_problem(lutq):
+    """The choice is kept for the last problems: more of them than there is room for, twice over, at two scratch sizes."""
+    first = {}
+    for turn in range(2):
+        for p in problems(6, 1500):
+            for ws in (None, lutq.STATIC_SCRATCH_BYTES):
+                assert first.setdefault((p, ws), (lutq.calib_plan(*p, ws), lutq.calib_route(*p, ws))) == \
+                    (lutq.calib_plan(*p, ws), lutq.calib_route(*p, ws)), p
+
+
 # panels of 32 rows are the library's choice on these: (bits, group, M, N, K, dtype)
 PANELS = [(4, 32, 17, 1072, 22528, 0), (3, 64, 32, 4272, 8192, 0), (2, 32, 32, 1152, 20992, 0)]
 IMPOSSIBLE = ((1, 0, 8, 2, 3), (1, 256, 16, 2, 1, 2, 4), (0, 0, 0, 0, 0, 7))   # waves that are no three teams, a queue, no scheduling
