@@ -25,7 +25,7 @@ int lutq_calib_stream_read(const void* src, size_t bytes, int grid, void* sink4,
  * Reads `bytes` and writes `bytes` of HBM traffic.  Same return codes. */
 int lutq_calib_copy(const void* src, void* dst, size_t bytes, int grid, void* stream);
 
-/* One launch of lutq_matmul_plan (same arguments, same result in Y; plan NULL = the default plan;
+/* One launch of lutq_matmul_plan (same arguments, same result in Y; plan NULL = the library's choice;
  * dtype 0 = fp16, 1 = bf16; M <= 4) through a measurement build of the kernel that also records where
  * the time of a launch goes: every wavefront reads the device's constant 100 MHz clock at eight points,
  *   0 wave started, 1 kernel arguments arrived, 2 first loads issued, 3 table built (barrier passed),
