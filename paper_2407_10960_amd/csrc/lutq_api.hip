@@ -1441,8 +1441,9 @@ Estimated estimate_launch(int bits, int group_size, int64_t M, int64_t N, int64_
     const bool fits = workspace_bytes >= kWorkspaceBytes || runs(&ruled_plan, false) || runs(nullptr, true);
     double best = fits ? margin * now : 1e30;
     if (!fits) now = best;
-    auto consider = [&](double us, const lutq_plan& plan) {
-        if (us >= best || !runs(&plan, false)) return;
+    const double ruled_us = now;
+    auto consider = [&](double us, const lutq_plan& plan, double share = 1.) {       // share: of the rules' time, at most
+        if (us >= best || us >= share * ruled_us || !runs(&plan, false)) return;
         best = now = us;
         e.plan = plan;
         e.found = true;
@@ -1450,10 +1451,17 @@ Estimated estimate_launch(int bits, int group_size, int64_t M, int64_t N, int64_
     // (beyond 12 us the estimates of one team per row block are too low at 17..32 rows and a long K: 8192 x 28672 M = 32 fp16 44 -> 115 us)
     for (int nw : {4, 5, 6, 8, 12, 16}) {
         if (nb > kMaxGrid || (!sch && nw > 8) || (M > 16 && bits != 4)) continue;
+        // (more than three workgroups to a compute unit of which two fit: 12464 x 1280 W3 M = 16 8.6 -> 12.7 us with five waves instead of four)
+        if (M > 4 && M <= 16 && nw > 4 && nb > 3 * (int64_t)cus) continue;
         const double us = teams_estimate_us(bits, M, nb, kt, megabytes, 1, (int)nb, nw, 1, false, cus);
         if (M <= 4 || us <= 12.) consider(us, lutq_plan{1, (int)nb, nw, 2, 1, LUTQ_SCHED_TEAMS, 0});
     }
     if (M < 5) return e;
+    // Row streaming of 5..16 rows.  Over all of K, where the rules' launch is row streaming too: never (twenty calls together 0.97 times as
+    // fast as the rules', one of them 4 % faster).  Over all of K instead of teams: where estimated at least 15 % faster, 20 % with less than two K
+    // tiles to a wave (of 506 calls estimated 11 to 15 % faster 69 were more than 3 % slower; with few K tiles 49 of 435 up to 20 %).  K slices of less
+    // than six tiles: not at all (thirteen together 1.0, seven of them up to 14 % slower).
+    const double whole = M > 16 ? 1. : ruled.rows ? 0. : 0.87, whole_few = M > 16 ? 1. : ruled.rows ? 0. : 0.83;
     for (int side : {4, 8}) {
         const int most = rows_instance_waves(bits, bf16, mb, side);
         for (int nw : {most > 12 ? 12 : most, 8}) {
@@ -1462,11 +1470,11 @@ Estimated estimate_launch(int bits, int group_size, int64_t M, int64_t N, int64_
                 // (with fewer K tiles than waves the estimates are too low: 57104 x 1280 W3 bf16 M = 8 16.1 -> 19.8)
                 if (grid <= nb && nb / grid <= 64 && kt >= nw)
                     consider(rows_estimate_us(bits, M, nb, kt, groups, megabytes, side, (int)grid, nw, 1, cus),
-                             lutq_plan{side, (int)grid, nw, 2, (int)(nb / grid), LUTQ_SCHED_ROWS, 0});
+                             lutq_plan{side, (int)grid, nw, 2, (int)(nb / grid), LUTQ_SCHED_ROWS, 0}, fits ? kt < 2 * nw ? whole_few : whole : 1.);
             const int64_t shares = (nb + side - 1) / side;
             for (int64_t ks = 2; ks <= kt && ks <= 40 && shares * ks <= 2 * (int64_t)cus; ++ks) {
                 const int64_t it = (kt + ks - 1) / ks;        // (slice counts that a plan can name)
-                if ((kt + it - 1) / it == ks)
+                if ((kt + it - 1) / it == ks && (it >= 6 || M > 16 || !fits))
                     consider(rows_estimate_us(bits, M, nb, kt, groups, megabytes, side, (int)(shares * ks), nw, (int)ks, cus),
                              lutq_plan{side, (int)(shares * ks), nw, 2, (int)(nb / shares), LUTQ_SCHED_ROWS, (int)it});
             }

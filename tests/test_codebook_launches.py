@@ -14,7 +14,7 @@ CALLS = {(4, 64, 3, 112, 512, "f16"): (1, 1, False), (4, 32, 1, 4096, 512, "f16"
          (4, 32, 16, 48, 7168, "f16"): (ROWS, 4, True), (4, 64, 32, 48, 3584, "f16"): (ROWS, 4, True),
          (4, 32, 24, 24576, 256, "bf16"): (ROWS, 8, False), (4, 32, 32, 48, 2560, "f16"): (0, 0, False),
          (2, 64, 3, 112, 512, "bf16"): (1, 1, False), (2, 32, 1, 8192, 1024, "f16"): (QUEUE, 1, False),
-         (2, 32, 16, 4112, 2048, "f16"): (ROWS, 4, False), (2, 32, 16, 24576, 2048, "f16"): (ROWS, 8, False),
+         (2, 32, 16, 4112, 2048, "f16"): (ROWS, 4, False), (2, 64, 6, 20560, 2048, "f16"): (ROWS, 8, False),
          (2, 64, 16, 48, 10240, "f16"): (ROWS, 4, True), (2, 128, 24, 48, 10240, "bf16"): (ROWS, 4, True),
          (2, 32, 32, 48, 3584, "f16"): (ROWS, 4, False), (2, 32, 24, 48, 5120, "f16"): (0, 0, False)}
 

@@ -149,6 +149,8 @@ def test_tuner_times_the_call_without_a_plan_and_the_rules(lutq, p, what):
 MEASURED = [((3, 32, 6, 880, 20480, 0), 10.3, 15.1), ((3, 32, 5, 1216, 16384, 0), 9.8, 13.9), ((3, 32, 15, 512, 13824, 1), 10.0, 13.9),
             ((2, 32, 10, 512, 16384, 0), 10.5, 12.9), ((3, 32, 10, 41056, 2048, 0), 16.5, 20.5), ((3, 32, 24, 688, 5632, 0), 10.5, 12.5),
             ((3, 32, 26, 800, 5632, 1), 10.9, 13.1), ((3, 32, 24, 608, 4608, 1), 10.1, 11.9),
+            ((3, 64, 16, 12464, 1280, 0), 8.6, 12.7), ((3, 64, 16, 13232, 1280, 1), 9.4, 13.6), ((2, 64, 14, 28720, 1280, 1), 17.9, 20.7),
+            ((3, 128, 8, 42448, 2048, 1), 15.6, 17.8), ((4, 128, 13, 4224, 1664, 1), 5.6, 6.4), ((3, 64, 14, 16032, 2304, 1), 9.8, 11.2),
             ((2, 64, 15, 25328, 2048, 0), 18.4, 10.0), ((4, 256, 23, 5232, 4864, 0), 18.1, 10.7), ((3, 128, 30, 30704, 1280, 0), 25.6, 11.2),
             ((4, 256, 24, 1104, 16384, 0), 18.9, 11.6), ((3, 256, 32, 6704, 4864, 0), 22.3, 12.0), ((2, 256, 10, 30512, 3328, 0), 25.9, 12.9),
             ((4, 32, 21, 1888, 16768, 0), 25.8, 13.9), ((3, 64, 12, 4464, 15104, 1), 29.0, 18.1), ((2, 128, 8, 20784, 11264, 0), 39.9, 23.9)]
