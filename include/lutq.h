@@ -272,9 +272,9 @@ lutq_status lutq_matmul_plan(const void* X, const void* packed, const void* scal
  * routine; the first call on a device looks the array's address up once (make that call outside a
  * graph capture).  Every other argument and the result are those of lutq_matmul_plan, bit for bit under the
  * same plan (NULL, the library's choice, may be another decomposition here: see below).
- * A launch needs partial-sum slots only when its plan cuts output tiles across workgroups:
- * grid x row groups per workgroup x 2 slots of R x ceil(M/16) x 1 KiB (M capped at 32).  If that exceeds
- * the 16 MiB, a call with a plan returns LUTQ_ERR_SCRATCH before anything is launched (Y untouched), and a
+ * A launch needs partial-sum slots only when its plan cuts output tiles across workgroups: teams
+ * grid x row groups per workgroup x 2 slots of R x ceil(M/16) x 1 KiB (M capped at 32), row streaming in K slices
+ * grid x R slots of ceil(M/16) x 1 KiB.  If that exceeds the 16 MiB, a call with a plan returns LUTQ_ERR_SCRATCH before anything is launched (Y untouched), and a
  * call without one takes the library's choice among the decompositions that need little scratch (of the
  * LLaMA-3 8B/70B shapes only 70B gate+up in bf16 beyond sixteen rows does not fit with its first choice).
  * All calls on one GPU share the one array: calls that may overlap on a GPU (different streams) race

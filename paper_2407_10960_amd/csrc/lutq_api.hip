@@ -1593,9 +1593,11 @@ int slice_rows(int bits, int group_size, int64_t M, int64_t N, int64_t K, bool b
 // part per K tile that a wavefront works on (t0 + t1 per 32 activation rows; the taller panel takes less per weight), more where
 // the chip is full, and with K slices the exchange of partial sums.  Parts of M fill the chip where the matrix is small, without
 // that exchange (8B O M = 128: 4 K slices 18.5, 4 parts of M 13.5; 1024 x 4096 14.0 -> 9.1); a large one is faster in one.  The constants
-// are fitted per bit width to 1260 measurements in all (fourteen shapes from 1024 x 4096 to 28672 x 4096, M = 64, 96, 128); the
-// choice was within 0.6 % of the fastest plan measured on average, 7 % at worst.  With the shorter prefetch that 33..64 rows at 4 bits
-// have since (panel_depth), eighteen shapes at M = 64: within 0.7 % and 2.5 % in fp16, 0.8 % and 7.7 % (8B QKV) in bf16.  (3 bits, 64
+// were fitted per bit width to 1260 measurements of an earlier build (fourteen shapes from 1024 x 4096 to 28672 x 4096, M = 64, 96, 128),
+// where the choice was within 0.6 % of the fastest plan measured on average.  With the present kernel, 101 000 timings of 15 921 drawn calls (1024 to
+// 57344 channels, K = 1024 to 28672, all types and groups): estimates 7 % off at 4 bits, 13 % at 3, 11 % at 2; the choice 1.7 % behind the
+// fastest of up to fourteen plans, more than 8 % on 8 % of the calls (ragged N and a long K: 2736 x 21504 W3 fp16 M = 46 25.4 us, 20.1 with 32
+// channels in five slices; 7600 x 6528 group 32 W4 bf16 M = 34 23.3, 17.8 in one part of M) and 34 % at worst.  (3 bits, 64
 // channels by 128 rows: no instance, the registers spill.)
 // `room`: bytes of scratch for the slices' partial sums.
 bool panel_decomp(int bits, int64_t M, int64_t N, int64_t K, int cus, size_t room, PanelDecomp* out) {
@@ -1639,8 +1641,9 @@ bool panel_decomp(int bits, int64_t M, int64_t N, int64_t K, int cus, size_t roo
 // Estimated us of the two launches that a call of 33..64 rows at 4 bits can take: each a sum of a fixed part, parts per K tile
 // and per row block or panel of the busiest compute unit, and one per megabyte of weights, fitted per type (and to 48 or 64 rows, or to
 // the panel launch's shape) to 1352 pairs of measurements: 340 shapes from 4096 to 57344 channels and K = 1024 to 28672, groups of 32 to 256.
-// The estimates are 2.4 % (row streaming) and 4.3 % off, the choice costs 0.2 % against the better launch on average, 8 % at worst
-// (fitted to the first 782 pairs and tried on the others: 0.4 %, 9 %).
+// On 2191 drawn calls with the present kernels, which are up to 8 % faster than those the constants were fitted to, the estimates are 2.7 % (row
+// streaming) and 4.9 % (panels, 3 % too high) off, and the choice costs 0.3 % against the better launch on average, more than 3 % on 3 % of the
+// calls, 17 % at worst (48608 x 3840 group 256 fp16 M = 36 46.9 us, panels 40.1).
 // Both, us, row streaming / panel: fp16 M = 40 8B gate+up 29.2 / 24.6, 70B QKV 24.1 / 24.2, 12288 x 4096 15.9 / 17.1, 32768 x 8192 52.4 /
 // 46.9, 40960 x 5120 48.9 / 53.8, M = 64 57.2 / 57.5; bf16 M = 40 5120 x 5120 16.3 / 14.0, 8B QKV 14.5 / 15.6, 70B down 60.3 / 50.9,
 // 12288 x 12288 34.5 / 42.2 (M = 64 40.0 / 42.7), 8B gate+up 29.7 / 29.0, 70B gate+up 91.8 / 105 (M = 64 106 / 109), 40960 x 5120 49.9 /

@@ -17,11 +17,11 @@
 //     operand reads (32 rows, one octet each) hit all banks evenly.
 //   * The tables hold 16-bit pairs at every type: bf16 pairs are widened in registers, since LDS (operands, lookups) and not
 //     the vector unit is what the matrix instructions wait for here.
-//   * What bounds it: no unit is full.  8B gate+up, M = 128, W4 fp16, 42 us (two slices of 64 rows on the row-streaming kernel took
+//   * What bounds it: no unit is full.  8B gate+up, M = 128, W4 fp16, 41 us (two slices of 64 rows on the row-streaming kernel took
 //     65.0; the dense fp16 product of the same shape 56).  The matrix instructions alone take 21 us of it on 224 compute units (1.66 PFLOP/s is what
-//     32x32x16 reaches here), launch, table and reduction 6.  Counters of the build before the waits below were taken out: matrix units busy 42 %
-//     of a compute unit's time, LDS 42 %, vector units 27 %; a wavefront issues 31 % of its time, waits at s_waitcnt 37 % and to issue
-//     32 %.  The waits that could be taken out (scales behind a branch, one loop for both looks at the partner's words) gave 3-8 %.  What did not:
+//     32x32x16 reaches here), launch, table and reduction 6.  Counters: matrix units busy 45 %
+//     of a compute unit's time, LDS 47 %, vector units 30 %; a wavefront issues 34 % of its time, waits at s_waitcnt 30 % and to issue
+//     36 % (before the waits below were taken out 42, 42, 27; 31, 37, 32).  The waits that could be taken out (scales behind a branch, one loop for both looks at the partner's words) gave 3-8 %.  What did not:
 //     operands two units ahead and two sets of table values (M = 64 27 -> 28 us), deeper activation and weight prefetch (0.96-1.0), K ranges walked from a
 //     different start per workgroup, issue priority for the wavefront that is behind.
 //   * K parts are added in order through LDS at the end.  Where panels are too few to fill the chip, K is also cut into KS
