@@ -5,7 +5,7 @@
 // units of 16, K 1024 to 28672, all bit widths, groups and types) they take 16 % (5..16 rows) and 42 % (17..32 rows) longer than the best of
 // some fifteen launches timed (7024 x 26624 group 256, W4 fp16, M = 31: 97.4 us, row streaming in K slices 32.9); on 5603 of 1..4 rows 5.7 %.
 // Fitted by least squares of the relative error to 159 000 timings of 5..32 rows on 50 000 problems (1..4 rows: 78 000; HBM-cold weights,
-// MI355X); on problems not fitted to the estimates are off by 6 to 13 % (row streaming), 7 to 10 % (teams) and 6 to 7 % (panels).
+// MI355X); on problems not fitted to the estimates are off by 6 to 12 % (row streaming), 7 to 11 % (teams) and 6 to 7 % (panels).
 // Three terms carry more than they seem to.  A workgroup that streams row blocks stages all their scale rows, whole, whatever its K
 // slice: 0.07 us per KiB, 5 us with group 32 and K = 20000 (880 x 20480 group 32 W3 fp16 M = 6, eight K slices: 15.1 us, the teams 10.3).  Workgroups
 // that share a row block cost by their number, and 2 to 3 us more where their parts do not end with it, each then adding two partial
