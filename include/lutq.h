@@ -293,7 +293,7 @@ lutq_status lutq_matmul_static(const void* X, const void* packed, const void* sc
  * M <= 4 with K / group_size a multiple of 8: the work-queue kernel with the tables of all of a
  * workgroup's row blocks built once and resident (sixteen copies per row block: the four lanes that
  * work on a row share one).  5 <= M <= 32: the row-streaming kernel with the tables of four or eight row blocks side by side, where
- * there are at least two row blocks per compute unit; on smaller matrices too from 9 or 17 rows up, if K is long, then with K cut into
+ * there are at least two row blocks per compute unit (but for a few classes of five to eight rows); on smaller matrices too from 9 or 17 rows up, if K is long, then with K cut into
  * up to sixteen slices across workgroups, whose partial sums and counters are in the workspace.  Otherwise a workgroup holds the tables
  * of one 16-row block at a time and
  * rebuilds its on-chip copies for every row block it works on (one row block per workgroup, K split

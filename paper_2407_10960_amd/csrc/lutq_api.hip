@@ -336,11 +336,16 @@ int rowlut_queue_lds(int bits, bool bf16, int amax, int nw, int items) {
 //     LDS (8B gate+up M = 6 / 16 / 32 20.6 / 24.0 / 27.1 in two passes of four -> 16.5 / 18.5 / 22.2; W3 bf16 M = 16 25.4 -> 21.8).
 //     (Twelve waves: sixteen took 24.0 us where twelve took 22.8.)  Scale rows that are not whole 16-byte units: at 2 and 4 bits and in fp16 1.05 to
 //     1.3 times as fast at 5..8 rows, from nine rows 1.2 to 2.2; 3-bit bf16 of five and six rows 0.95 (33264 x 3840 M = 6 25.9 -> 30.9), not taken.
+//     Nor where such a call of 5..8 rows ends in a pass of one row block (five or nine to a workgroup; at 3 bits ten too): 4-bit bf16 0.93 of the teams'
+//     speed with five (18304 x 1920 M = 5 13.0 -> 15.6), 1.05 to 1.2 with six to eight; 3 bits 0.93 to 0.97 with nine and ten (33696 x 5376 M = 6 31.5 -> 37.3).
 //   * up to two per unit, K slices: M = 17 / 32 4096 x 14336 20.4 / 30.3 -> 15.7 / 16.3, N = K = 8192 19.6 / 20.3 -> 16.6 / 17.4, 6144 x 4096 15.3 /
 //     20.7 -> 11.7 / 12.2, 1312 x 11264 16.5 / 20.0 -> 11.3 / 11.5 (W2 32.0 / 34.3 -> 11.8 / 11.6), 4096 x 6144 M = 32 15.3 -> 11.8; not 4096 x 4096 (M = 17 8.6 ->
 //     10.4) nor 4096 x 6144 at M = 17 (11.0 -> 11.6).  Nine to sixteen rows: only a long K, M = 12 4096 x 14336 15.5 -> 13.2, 1312 x 11264 11.6 -> 10.0, and
 //     between one and two row blocks per unit (all of K: 6144 x 4096 10.2 -> 9.8, W2 11.7 -> 8.9; not at 4 bits with a short K: 7312 x 1536 bf16
 //     M = 10 7.0 -> 7.7, fifteen of K = 1152..2304 0.95 together, thirty of K = 2560..8192 1.10); M = 8 4096 x 14336 12.1 -> 12.9.
+//     Not either: 3 bits, nine and ten rows, more than 160 row blocks and up to one per unit, where only four to six slices fit (0.82 to 1.05, 3600 x
+//     11520 M = 9 12.3 -> 15.0; eleven rows 1.05); 4-bit fp16 of 17..22 rows, between one and two row blocks per unit, K < 2048 (0.95, 5968 x 1152 M = 19
+//     7.9 -> 9.0; from 23 rows or K = 2048 1.02 and more).
 //     At most sixteen slices: the workgroup that adds their sums takes longer than the rest where there are more.  Times of 600 drawn calls
 //     of one to 128 row blocks and K from 4096 with no bound / 32 / 16 / 12 / 8 slices, us: of more than 64 possible ones 25.9 / 19.4 / 18.6 / 18.9 / 19.9 (17..32
 //     rows) and 20.2 / 14.6 / 13.9 / 14.1 / 14.6 (9..16), of 24..31 16.2 / 16.1 / 14.9 / 14.7 / 14.8.  Without the bound a third of the calls of
@@ -355,6 +360,8 @@ bool rowlut_rows_decomp(int bits, bool bf16, int64_t M, int64_t N, int64_t K, in
                                                        : M > 8 && nb < 2 * (int64_t)cus && (K >= 11264 || (nb > cus && (bits != 4 || K >= 2560))));
     if (!few && nb < 2 * (int64_t)cus) return false;
     if (bits == 3 && bf16 && M <= 6 && sg2 % 16 != 0) return false;
+    if (bits == 4 && !bf16 && M > 16 && M <= 22 && nb > cus && nb < 2 * (int64_t)cus && K < 2048) return false;
+    if (bits == 3 && M > 8 && M <= 10 && nb > 160 && nb <= cus) return false;
     const int64_t shares = (nb + 3) / 4;
     int64_t ks = few && (M > 16 || K >= 11264) ? cus / shares : 1;
     if (ks > 16) ks = 16;
@@ -376,6 +383,10 @@ bool rowlut_rows_decomp(int bits, bool bf16, int64_t M, int64_t N, int64_t K, in
         if (ks <= 1) d.nw = most > 12 ? 12 : most;
         if (d.nw > kt) d.nw = (int)(kt < 4 ? 4 : kt);
         if (d.nw >= 4 && d.nw <= most && rows_blocks_per_round(bits, d.r, sg2, mb, d.nw, tab16) >= 1) {
+            const int64_t blocks = (nb + d.grid - 1) / d.grid;
+            if (ks <= 1 && sg2 % 16 != 0 && M <= 8 && d.r == 4 && ((blocks == 5 && (bf16 || (bits == 4 && M <= 6))) || (blocks == 9 && bf16 && M <= 6) ||
+                                                                  (bits == 3 && (blocks == 9 || blocks == 10))))
+                return false;
             *out = d;
             return true;
         }

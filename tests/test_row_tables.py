@@ -46,12 +46,17 @@ def test_row_tables(shape, bits, dtype):
 LAUNCHED = [((3, 32, 11, 80, 17408, 1), "slices"), ((4, 32, 12, 64, 13312, 0), "slices"), ((3, 64, 9, 16, 29440, 0), "slices"),
             ((3, 32, 25, 64, 22528, 1), "slices"), ((2, 256, 30, 48, 12288, 0), "slices"),
             ((4, 128, 10, 7312, 1536, 1), "teams"), ((4, 128, 11, 5152, 1920, 1), "teams"), ((3, 64, 6, 33264, 3840, 1), "teams"),
+            ((4, 32, 5, 18304, 1920, 1), "teams"), ((4, 32, 5, 20560, 1920, 1), "rows"), ((4, 32, 5, 18304, 1920, 0), "teams"), ((4, 32, 7, 18304, 1920, 0), "rows"),
+            ((3, 64, 6, 33696, 5376, 0), "teams"), ((2, 128, 8, 18896, 7936, 1), "teams"), ((4, 64, 6, 33808, 5760, 1), "teams"), ((4, 64, 7, 33808, 5760, 1), "rows"),
+            ((3, 32, 9, 3600, 11520, 1), "teams"), ((3, 32, 11, 3600, 11520, 1), "slices"), ((3, 32, 10, 2560, 11520, 1), "slices"),
+            ((4, 32, 19, 5968, 1152, 0), "teams"), ((4, 32, 23, 5968, 1152, 0), "slices"), ((4, 32, 19, 5968, 2048, 0), "slices"), ((4, 32, 19, 5968, 1152, 1), "slices"),
             ((4, 128, 12, 4800, 5632, 0), "rows"), ((3, 128, 16, 7264, 2048, 1), "rows"), ((4, 64, 6, 33264, 3840, 0), "rows")]
 
 
 def test_launches_with_one_table_per_row():
     """At most sixteen K slices; four-bit calls of 9..16 rows with one to two row blocks per compute unit and a short K, and 3-bit bf16
-    calls of five and six rows with scale rows that are not whole 16-byte units, stay with the teams."""
+    calls of five and six rows with scale rows that are not whole 16-byte units, stay with the teams; so do 5..8 rows with such scale
+    rows that end in a pass of one row block, and two classes of K slices."""
     import paper_2407_10960_amd as lutq
     for p, what in LAUNCHED:
         plan = lutq.calib_plan(*p, row_tables=True)
